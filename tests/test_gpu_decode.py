@@ -40,6 +40,39 @@ def dev(a, dtype=None):
 
 
 # ------------------------------------------------------------------------------ quantise / slice
+@pytest.mark.parametrize("nest", [(8, 4), (6, 3), (4, 2)])
+@pytest.mark.parametrize("wdt,sdt", [("f32", "f32"), ("bf16", "bf16"), ("f32", "bf16")])
+@pytest.mark.parametrize("d,f,G", [(32, 32, 32),       # one quad per row, the last work-group nearly empty
+                                   (32, 64, 512),      # a group wider than the row
+                                   (1056, 160, 64),    # ragged last group, rows that straddle wavefronts
+                                   (608, 96, 256),     # groups of half a wavefront, ragged
+                                   (1024, 544, 512),   # a group is a wavefront; ragged down rows
+                                   (288, 192, 96),     # not a power of two: the general kernel
+                                   (2048, 64, 1024)])  # above 512: the general kernel
+def test_quantize_group_shapes_bit_exact(ctx, d, f, G, wdt, sdt, nest):
+    # (codes, planes, zero-points and scale bits are whole numbers: no tolerance)
+    say("quantize shapes", d, f, G, wdt, sdt, nest)
+    rng = np.random.default_rng(d + f + G)
+    n = 2
+    ws = []
+    for shape in ((n, f, d), (n, f, d), (n, d, f)):
+        w = rng.standard_normal(shape) * 0.02
+        w[0, :, : shape[2] // 2] = np.round(w[0, :, : shape[2] // 2] * 100) / 100     # many equal values, many halves of a step
+        w[1, ::3] *= np.float64(2.0) ** rng.integers(-130, 100, (len(w[1, ::3]), 1))  # scales in and out of the fast division's range
+        w[1, 1::5] = np.abs(w[1, 1::5])
+        w = torch.from_numpy(w.astype(np.float32))
+        ws.append(w if wdt == "f32" else w.bfloat16())
+    bank = B.Bank(ctx, n + 1, d, f, G, wdt, sdt, nest[0], nest[1])
+    B.smoe_quantize_slice(ctx, bank, 1, *(w.cuda().contiguous() for w in ws))
+    for e in range(n):
+        for mi, w in enumerate(ws):
+            ref = O.quantize(w[e].float().numpy(), G, nest[0], nest[1], sdt)
+            got = B.smoe_export_codes(ctx, bank, 1 + e, mi)
+            assert np.array_equal(got["scale"].view(np.uint32), ref.scale.view(np.uint32))
+            assert np.array_equal(got["zp"], ref.zp) and np.array_equal(got["q"], ref.q)
+            assert np.array_equal(got["msb"], ref.msb()) and np.array_equal(got["lsb"], ref.lsb())
+
+
 @pytest.mark.parametrize("d,f,G,dt", [(256, 128, 64, "f32"), (256, 160, 64, "bf16"), (2048, 1408, 128, "bf16"),
                                       (96, 64, 32, "f32")])
 def test_quantize_slice_bit_exact(ctx, d, f, G, dt):
