@@ -6,25 +6,26 @@
 //   gemm<1>      grouped GEMM  O = w * (H Wd^T)
 //   combine      Y[t] = sum over slots (slot order) O[(t, slot)]  (+ x)
 // Weights are read from the same nibble planes the decode path uses and expanded to
-// bf16 s*(16 msb + lsb - zp) on the way into LDS.
+// bf16 s*(16 msb + lsb - zp) in the registers of the wave that multiplies them.
 #include "route_device.hpp"
 #include <type_traits>
+#include <algorithm>
+#include <math.h>
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-struct __attribute__((packed)) U32x2Unaligned { uint32_t x, y; };
-struct __attribute__((packed, aligned(4))) U32x3Words { uint32_t x, y, z; };      // twelve bytes on a 4-byte boundary
 
-#define PF_BM 192          // token rows per work-group tile
-#define PF_BN 256          // weight rows per work-group tile
+#define PF_BN 128          // weight rows per work-group tile: 32 per wave
 #define PF_BK 64
-#define PF_NT 512          // threads per work-group
-#define PF_LDK 72          // padded LDS row length in bf16 (144 bytes)
+#define PF_NT 256          // threads per work-group
+#define PF_MAX_NF 5        // 32-row fragments of the tallest tile
+#define PF_MIN_BM 32
 
 // ------------------------------------------------------------------------------- small kernels
 #define GR_THREADS 1024
@@ -32,12 +33,11 @@ struct __attribute__((packed, aligned(4))) U32x3Words { uint32_t x, y, z; };    
 // every expert's selections in LDS, so it knows its own row offset and tile offset.  Writes
 //   hist[e]    number of (token, slot) pairs routed to e (the per-expert access count of the layer)
 //   offsets[e] first row of expert e in the grouped layout (offsets[E] = total)
-//   tiles[0]   number of row tiles; tiles[4 + 4i ..] = {expert, first row inside the expert, first row
-//              in the grouped layout, rows} of tile i, tiles with more rows first (equal sizes:
-//              expert, then row, ascending), so that the work-groups that start last are the short ones
+//   tiles[0]   number of row tiles of at most bm rows; tiles[4 + e] = first tile of expert e, whose
+//              ceil(hist[e] / bm) tiles follow each other
 //   rows[p]    flat (token*k + slot) index of the p-th row of the grouped layout, ascending inside an
 //              expert; pos = inverse of rows.
-__global__ __launch_bounds__(GR_THREADS) void group_kernel(const int32_t* idx, int n, int E, uint32_t* hist,
+__global__ __launch_bounds__(GR_THREADS) void group_kernel(const int32_t* idx, int n, int E, int bm, uint32_t* hist,
                                                            int32_t* offsets, int32_t* tiles, int32_t* rows, int32_t* pos) {
   __shared__ int cnt[SMOE_MAX_EXPERTS];
   __shared__ int wtot[GR_THREADS / 64];
@@ -74,26 +74,14 @@ __global__ __launch_bounds__(GR_THREADS) void group_kernel(const int32_t* idx, i
   if (lane == 63) wtot[wave] = incl;
   __syncthreads();
   // Wave 0 turns the counts into what the work-group needs (lane x takes experts x, x + 64, ...): rows
-  // and tiles of the experts before e, all full tiles, and the ragged tiles that precede e's ragged one
-  // (more rows first; equal sizes by expert).
-  __shared__ int summary[4];      // rows before e, full tiles before e, full tiles in all, ragged tiles before e's
+  // and tiles of the experts before e.
+  __shared__ int summary[2];
   const int ne = cnt[e];
-  const int rem = ne % PF_BM;
   if (wave == 0) {
-    int s_off = 0, s_fb = 0, s_fa = 0, s_rb = 0, s_ra = 0;
-    for (int x = lane; x < E; x += 64) {
-      const int cx = cnt[x], fx = cx / PF_BM, rx = cx - fx * PF_BM;
-      s_fa += fx;
-      s_ra += rx > 0;
-      if (x < e) { s_off += cx; s_fb += fx; }
-      s_rb += rx > rem || (rx == rem && x < e);
-    }
-    for (int m = 32; m >= 1; m >>= 1) {
-      s_off += __shfl_xor(s_off, m); s_fb += __shfl_xor(s_fb, m); s_fa += __shfl_xor(s_fa, m);
-      s_rb += __shfl_xor(s_rb, m); s_ra += __shfl_xor(s_ra, m);
-    }
-    if (lane == 0) { summary[0] = s_off; summary[1] = s_fb; summary[2] = s_fa; summary[3] = s_rb; }
-    if (lane == 0 && e == E - 1) { offsets[E] = s_off + ne; tiles[0] = s_fa + s_ra; }
+    int s_off = 0, s_tb = 0;
+    for (int x = lane; x < e; x += 64) { s_off += cnt[x]; s_tb += (cnt[x] + bm - 1) / bm; }
+    for (int m = 32; m >= 1; m >>= 1) { s_off += __shfl_xor(s_off, m); s_tb += __shfl_xor(s_tb, m); }
+    if (lane == 0) { summary[0] = s_off; summary[1] = s_tb; }
   }
   __syncthreads();
   int p = incl - mine;
@@ -111,37 +99,36 @@ __global__ __launch_bounds__(GR_THREADS) void group_kernel(const int32_t* idx, i
   if (tid == 0) {
     hist[e] = (uint32_t)ne;
     offsets[e] = off;
-  }
-  // Position of each of this expert's tiles in the list = number of tiles that precede it: every
-  // full tile precedes a ragged one; full tiles among themselves and ragged tiles of equal size go
-  // by expert (an expert has at most one ragged tile, its last).
-  const int n_full = ne / PF_BM;
-  for (int j = tid; j < n_full + (rem > 0); j += GR_THREADS) {
-    const int rank = j < n_full ? summary[1] + j : summary[2] + summary[3];
-    int4 rec;
-    rec.x = e; rec.y = j * PF_BM; rec.z = off + j * PF_BM; rec.w = min(PF_BM, ne - j * PF_BM);
-    *(int4*)(tiles + 4 + 4 * rank) = rec;
+    tiles[4 + e] = summary[1];
+    if (e == E - 1) { offsets[E] = off + ne; tiles[0] = summary[1] + (ne + bm - 1) / bm; }
   }
 }
 
 // ------------------------------------------------------------------------------- grouped GEMM
 struct GemmArgs {
   MatDev w;                 // gu (MODE 0) or dn (MODE 1) family of the bank
-  int sc_bf16, group_shift; // quantisation group = 1 << group_shift columns
-  const int32_t* offsets;   // [E+1]
-  const int32_t* tiles;     // tile list written by group_kernel
+  int group_shift;          // quantisation group = 1 << group_shift columns
+  int E, k, d_model, d_ff;
+  int n_col_tiles;          // column tiles of this GEMM
+  int super;                // row tiles that share a column tile before the next column tile starts
+  const int32_t* offsets;   // [E] first row of an expert     (written by group_kernel, like tiles and rows)
+  const int32_t* tiles;
+  const uint32_t* hist;     // [E] rows of an expert
   const int32_t* rows;      // [T*k]
   const uint16_t* x;        // MODE 0: X [T, d_model] bf16
   uint16_t* h;              // H [T*k, d_ff] bf16 (MODE 0 output, MODE 1 input)
   float* o;                 // MODE 1 output [T*k, d_model] fp32
   const float* wgt;         // [T*k] gate weights (flat token*k + slot)
-  int k, d_model, d_ff;
-  int n_col_tiles;          // column tiles of this GEMM (grid = 8 * ceil(max row tiles / 8) * n_col_tiles)
-  // dense_rows > 0: one expert (dense_expert) takes rows 0..dense_rows-1 = tokens in their own order
-  // (a shared expert): no tile list, no row list, H and O rows are token rows; wgt[t] scales row t
-  int dense_rows, dense_expert;
+  // dense_rows > 0: the n_dense experts from dense_expert on (shared experts) take every token: rows are
+  // the tokens in their own order, no tile list, no row list; wgt[t] scales row t.  H of the first of
+  // them is h, of the others h_more ([n_dense - 1, dense_rows, d_ff]); MODE 1 sums over the experts
+  int dense_rows, dense_expert, n_dense;
+  uint16_t* h_more;
+  uint32_t a_bytes;         // bytes of X (MODE 0) / of one H buffer (MODE 1)
   int accumulate;           // MODE 1: add to O instead of overwriting it
 };
+// one launch serves two sets of experts: work-groups below nb0 belong to g[0] (nb0 is a multiple of 8)
+struct GemmPair { GemmArgs g[2]; int nb0; };
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   f32x2 v = {a, b};
@@ -149,277 +136,368 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return *(uint32_t*)&r;
 }
 
-// Work-group barrier that orders LDS traffic only: the global loads of the prefetch stay in flight
-// across it (__syncthreads would wait for them and undo the prefetch).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ u32x4 pf_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t v = (uint64_t)base;
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) & 0xFFFFu,
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
+}
+// 64 lanes x 16 bytes from memory straight into LDS: lane i's bytes land at lds + 16 i (M0 is used for nothing
+// else here).  The compiler does not count these loads: see the K loop for what orders them.
+__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
 
-// One work-group of eight waves (two per SIMD) per CU: the tile is 192 token rows x 256 weight rows,
-// a wave owns 96 x 64 of it (3 x 2 MFMA fragments), and LDS holds two copies of the K slice so that
-// one barrier per K step is enough.
-template <int MODE, int SCB, int FMT>      // FMT 0: 8/4 nest, nibble planes; 1: 4/2 nest, 2-bit planes; 2: 6/3 nest, 3-bit planes
-__global__ __launch_bounds__(PF_NT) void grouped_gemm_kernel(GemmArgs a) {
-  // (separate arrays, so that the compiler knows a write into one buffer cannot alias a read of the other)
-  __shared__ __align__(16) uint16_t As0[PF_BM * PF_LDK], As1[PF_BM * PF_LDK];
-  __shared__ __align__(16) uint16_t Bs0[PF_BN * PF_LDK], Bs1[PF_BN * PF_LDK];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Work-groups go to the eight XCDs round-robin by their linear index.  All column tiles of one row
-  // tile are given to the same XCD, consecutively, so its rows of A are fetched into one L2 only and
-  // stay there while they are re-read.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int ti = (slot / a.n_col_tiles) * 8 + xcd, nt = slot % a.n_col_tiles;
-  int e, m0, row0, m_cnt;
-  if (a.dense_rows) {
-    if (ti * PF_BM >= a.dense_rows) return;
-    e = a.dense_expert; m0 = ti * PF_BM; row0 = 0;
-    m_cnt = min(PF_BM, a.dense_rows - m0);
-  } else {
-    const int n_tiles = a.tiles[0];
-    const int4 rec = *(const int4*)(a.tiles + 4 + 4 * ti);      // (read before the count is known: inside the list's allocation)
-    if (ti >= n_tiles) return;
-    e = rec.x; m0 = rec.y; row0 = rec.z - rec.y; m_cnt = rec.w;
-  }
-  const int K = MODE == 0 ? a.d_model : a.d_ff;
-  const int N = MODE == 0 ? a.d_ff : a.d_model;         // output columns of this GEMM
-  // MODE 1: the weight of every row of the tile, fetched now for the epilogue (the barriers of the
-  // K loop order it)
-  __shared__ float row_wt[PF_BM];
-  if (MODE == 1 && tid < PF_BM)
-    row_wt[tid] = tid < m_cnt ? a.wgt[a.dense_rows ? m0 + tid : a.rows[row0 + m0 + tid]] : 0.0f;
-  const int mh = wave >> 2, nq = wave & 3;
+// the same for one dword / one byte (zero-extended) per lane: lane i's dword lands at lds + 4 i
+__device__ __forceinline__ void dma4(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+__device__ __forceinline__ void dma1(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ubyte %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-  // ---- loader roles
-  // A: 192 rows x 8 sixteen-byte columns = 1536 vectors, 3 per thread
-  // (a row past the tile's last one repeats that row: rows of the product are independent and the
-  // epilogue stores none of the surplus ones)
-  const uint16_t* a_base = MODE == 0 ? a.x : (const uint16_t*)a.h;
-  uint32_t a_src[3];                        // element offsets into a_base (the host checks they fit 32 bits)
-  const int a_dst0 = (tid >> 3) * PF_LDK + (tid & 7) * 8;       // vector q goes 64 rows further down
-#pragma unroll
-  for (int q = 0; q < 3; q++) {
-    const int i = tid + PF_NT * q, r = min(i >> 3, m_cnt - 1), c = i & 7;
-    if (MODE == 0) a_src[q] = (uint32_t)(a.dense_rows ? m0 + r : a.rows[row0 + m0 + r] / a.k) * (uint32_t)a.d_model + c * 8;
-    else a_src[q] = (uint32_t)(row0 + m0 + r) * (uint32_t)a.d_ff + c * 8;
-  }
-  // B: thread -> (weight row b of the tile, half hb of the 64 columns of the K slice).  MODE 0: the 64
-  // rows of a wave's column block are [gate 32 | up 32] of 32 output columns, so that gate and up
-  // of one output element land in the same lane of two accumulators.
-  const int b = tid >> 1, hb = tid & 1;
-  int grow;                                   // row inside the bank's matrix family (clamped)
-  if (MODE == 0) {
-    const int col = nt * (PF_BN / 2) + (b >> 6) * 32 + (b & 31);
-    grow = 2 * min(col, N - 1) + ((b >> 5) & 1);
-  } else {
-    grow = min(nt * PF_BN + b, N - 1);
-  }
-  // uniform 64-bit section bases + 32-bit per-thread offsets (every section of a bank is below 2 GiB)
-  const uint8_t* pm = a.w.msb + (size_t)e * a.w.plane_stride;
-  const uint8_t* pl = a.w.lsb + (size_t)e * a.w.plane_stride;
-  const uint8_t* ps = a.w.sc + (size_t)e * a.w.sc_stride;
-  const uint8_t* pz = a.w.zp + (size_t)e * a.w.zp_stride;       // 4-byte aligned: zp_stride is a multiple of 4
+// One expert's 32 * NF token rows times 128 weight rows, four waves.  A wave owns all the token rows and 32 of
+// the weight rows; it expands its weights to bf16 in registers -- lane (n, h) holds columns 32 h .. 32 h + 31 of one
+// row of a K step (64 columns), and MFMA s of the step contracts columns {8 s ..} and {32 + 8 s ..} on both operands --
+// so every weight is expanded once per tile and LDS carries bf16 only for the token rows.  All memory reaches LDS
+// by direct loads: token rows one K step ahead into two buffers; planes, scales and zero-points 256 columns (a
+// whole 128-byte line of a nibble plane) at a time into an area of the wave's own, fetched while the previous 256
+// columns, by then in registers, are multiplied.
+// Bound: with few rows per expert the weights' bytes; with many the instruction issue of the waves (about 100 vector
+// instructions of expansion to 4 * NF products of 32 cycles per step and wave, two waves per SIMD: a third would
+// need a shorter tile).  Why this shape, measured on the gate/up GEMM of 60 experts of d_model 2048, d_ff 1408 at
+// 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use them, every lane of a
+// load in another cache line, 215 / 183 us; 128 columns at a time through LDS, half a line, 165 / 123 us; a whole line
+// and 32 instead of 64 weight rows per wave, with the epilogue below, 149 / 94 us.  (192 x 256 tiles, weights expanded
+// once more through LDS, one work-group per CU: 161 / 117 us, and 297 against 215 us on 4096 dense rows, d_ff 5632.)
+template <int MODE, int SCB, int FMT, int NF>      // FMT 0: 8/4 nest, nibble planes; 1: 4/2 nest, 2-bit planes; 2: 6/3 nest, 3-bit planes
+__global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(GemmPair pair) {
+  constexpr int BM = 32 * NF;
   constexpr int PB32 = FMT == 0 ? 16 : FMT == 1 ? 8 : 12;      // plane bytes of 32 columns
-  const uint32_t poff = (uint32_t)grow * (uint32_t)((K >> 5) * PB32) + hb * PB32;
-  const uint32_t srow = (uint32_t)grow * (uint32_t)a.w.sng;
-  const uint32_t zrow = (uint32_t)grow * (uint32_t)a.w.ng;
-  const int b_dst = b * PF_LDK + hb * 32;
+  constexpr int PROW = 8 * PB32, PPR = PROW / 16, NPL = 32 * PROW / 1024;      // of a row and 256 columns; 16-byte pieces of that; loads per plane
+  constexpr int PLANE = 32 * PROW, NSD = SCB ? 4 : 8;          // bytes of a wave's plane area; scale dwords per row and 256 columns
+  constexpr int ZP_AT = 2 * PLANE + NSD * 128, WAVE_LDS = ZP_AT + 8 * 128;     // the wave's area: MSB plane, LSB plane, scales, zero-points
+  __shared__ __align__(1024) uint8_t As[2 * BM * 128 + 4 * WAVE_LDS];      // two K steps of the token rows, 128 bytes per row; the waves' areas
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const bool second = (int)blockIdx.x >= pair.nb0;
+  const GemmArgs& a = pair.g[second ? 1 : 0];
+  const int bid = (int)blockIdx.x - (second ? pair.nb0 : 0);
 
-  // Two register sets of prefetched inputs: the loads of K step t+2 are issued while step t is
-  // computed.  The registers hold what the loads return, untouched: arithmetic on them at this
-  // point would make the wave wait for the loads.
-  struct PreA { u32x4 ra[3]; };
-  typedef typename std::conditional<FMT == 1, u32x2, u32x4>::type PlaneV;      // a thread's 32 codes of one plane (FMT 2: three words used)
-  struct Pre { PlaneV rm, rl; };
-  // Scales and zero-points of eight consecutive groups of the thread's row (the chunk that holds the
-  // groups of a K step), kept in registers and reloaded only when a step enters a new chunk: loading
-  // them step by step costs a cache line per thread and step.  Reads are clamped to the expert's
-  // section (what is read past the row's end belongs to groups the row does not have).
-  constexpr int NSD = SCB ? 4 : 8;
-  struct Meta { typename std::conditional<SCB != 0, u32x4, u32x8>::type s; u32x2 z; };     // (vector registers: picking one element by a run-time index stays in registers)
-  const uint32_t last_s = (uint32_t)(a.w.sc_stride >> 2) - 1u, last_z = (uint32_t)a.w.zp_stride - 8u;
-  auto chunk_of = [&](int k0) __attribute__((always_inline)) { return ((uint32_t)k0 >> a.group_shift) >> 3; };
-  auto mload = [&](int k0, Meta& m) __attribute__((always_inline)) {
-    const uint32_t c0 = chunk_of(k0) << 3;
-    const uint32_t sd = SCB ? (srow + c0) >> 1 : srow + c0;         // srow is even
-    const U32x2Unaligned zz = *(const U32x2Unaligned*)(pz + min(zrow + c0, last_z));    // eight bytes at any alignment
-    m.z = u32x2{zz.x, zz.y};
-#pragma unroll
-    for (int j = 0; j < NSD; j++) m.s[j] = ((const uint32_t*)ps)[min(sd + j, last_s)];
-  };
-  auto gload_a = [&](int k0, PreA& p) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 3; q++) p.ra[q] = *(const u32x4*)(a_base + (a_src[q] + (uint32_t)k0));
-  };
-  auto lstore_a = [&](const PreA& p, uint16_t* As) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 3; q++) *(u32x4*)(As + a_dst0 + q * 64 * PF_LDK) = p.ra[q];
-  };
-  auto gload = [&](int k0, Pre& p) __attribute__((always_inline)) {
-    const uint32_t o = poff + (uint32_t)((k0 >> 5) * PB32);
-    if constexpr (FMT == 2) {
-      const U32x3Words vm = *(const U32x3Words*)(pm + o), vl = *(const U32x3Words*)(pl + o);
-      p.rm = u32x4{vm.x, vm.y, vm.z, 0u};
-      p.rl = u32x4{vl.x, vl.y, vl.z, 0u};
-    } else {
-      p.rm = *(const PlaneV*)(pm + o);
-      p.rl = *(const PlaneV*)(pl + o);
-    }
-  };
-  auto lstore = [&](int k0, const Pre& p, const Meta& m, uint16_t* Bs) __attribute__((always_inline)) {
-    const uint32_t g = (uint32_t)(k0 + 32 * hb) >> a.group_shift, gi = g & 7u;
-    float rs;
-    if (SCB) {
-      const uint32_t d = m.s[gi >> 1];
-      rs = __uint_as_float((gi & 1u) ? d & 0xFFFF0000u : d << 16);
-    } else {
-      rs = __uint_as_float(m.s[gi]);
-    }
-    const uint32_t zb = zrow + (g & ~7u);
-    const uint32_t zo = zb - min(zb, last_z) + gi;                 // byte of the zero-point inside m.z
-    const uint32_t zw = m.z[(zo >> 2) & 1u];
-    const float c0 = -(float)((zw >> ((zo & 3u) * 8u)) & 0xFFu) * rs;
-    uint32_t out[16];
+  // ---- which tile.  The (row tile, column tile) items are listed in bands of a.super row tiles, column by
+  // column inside a band, and the list is cut into eight equal runs, one per XCD (work-groups go to the
+  // XCDs round-robin), so that the work-groups that share weight rows or token rows run side by side on one L2.
+  int e_base = 0, e_cnt = 0, e_first = 0, e = 0, n_tiles;
+  const int rt = a.dense_rows ? (a.dense_rows + BM - 1) / BM : 0;
+  int tstart[4], toff[4], tcnt[4];
+  if (!a.dense_rows) {
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-      uint32_t qe, qo;                          // codes of the even / odd columns of columns 8j .. 8j+7, one per byte
-      if constexpr (FMT == 0) {
-        // the planes hold n ^ 8 per nibble
-        const uint32_t wm = p.rm[j], wl = p.rl[j];
-        qe = (((wm & 0x0F0F0F0Fu) << 4) | (wl & 0x0F0F0F0Fu)) ^ 0x88888888u;
-        qo = ((wm & 0xF0F0F0F0u) | ((wl >> 4) & 0x0F0F0F0Fu)) ^ 0x88888888u;
-      } else if constexpr (FMT == 2) {
-        // column 8j + i: two low bits in word j >> 1 at bits 4i + 2(j & 1), third bit in word 2 at bit
-        // 4i + j; one value per nibble first, then code = 8 msb + lsb, one per byte
-        auto nib = [&](const PlaneV& w) {
-          const uint32_t lo = (w[j >> 1] >> (2 * (j & 1))) & 0x33333333u;
-          const uint32_t hi = w[2] & (0x11111111u << j);
-          return lo | (j < 2 ? hi << (2 - j) : hi >> (j - 2));
-        };
-        const uint32_t nm = nib(p.rm), nl = nib(p.rl);
-        qe = ((nm & 0x0F0F0F0Fu) << 3) | (nl & 0x0F0F0F0Fu);
-        qo = (((nm >> 4) & 0x0F0F0F0Fu) << 3) | ((nl >> 4) & 0x0F0F0F0Fu);
-      } else {
-        // sixteen 2-bit codes per plane word, column c in bits 2c, 2c+1: spread half a word to one
-        // code per nibble, then code = 4 msb + lsb
-        auto spread = [](uint32_t h) {
-          h = (h | (h << 8)) & 0x00FF00FFu;
-          h = (h | (h << 4)) & 0x0F0F0F0Fu;
-          return (h | (h << 2)) & 0x33333333u;
-        };
-        const uint32_t hm = (p.rm[j >> 1] >> (16 * (j & 1))) & 0xFFFFu, hl = (p.rl[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-        const uint32_t qn = (spread(hm) << 2) | spread(hl);
-        qe = qn & 0x0F0F0F0Fu;
-        qo = (qn >> 4) & 0x0F0F0F0Fu;
-      }
-#pragma unroll
-      for (int bb = 0; bb < 4; bb++) {
-        const float we = fmaf((float)((qe >> (8 * bb)) & 0xFF), rs, c0);
-        const float wo = fmaf((float)((qo >> (8 * bb)) & 0xFF), rs, c0);
-        out[4 * j + bb] = pack_bf16(we, wo);
-      }
+      const int x = lane + 64 * j;
+      tstart[j] = x < a.E ? a.tiles[4 + x] : 0x7FFFFFFF;
+      toff[j] = x < a.E ? a.offsets[x] : 0;
+      tcnt[j] = x < a.E ? (int)a.hist[x] : 0;
     }
+    n_tiles = uni(a.tiles[0]);
+  } else {
+    n_tiles = MODE == 0 ? rt * a.n_dense : rt;
+  }
+  const int n_items = n_tiles * a.n_col_tiles, run = (n_items + 7) >> 3;
+  const int slot = bid >> 3, item = (bid & 7) * run + slot;
+  if (slot >= run || item >= n_items) return;
+  const int band = uni(item / (a.super * a.n_col_tiles)), in_band = item - band * a.super * a.n_col_tiles;
+  const int band_rows = min(a.super, n_tiles - band * a.super);
+  const int nt = uni(in_band / band_rows), ti = band * a.super + in_band - nt * band_rows;
+  int row0;                                             // first row of the expert in the grouped layout
+  uint16_t* h = a.h;
+  if (a.dense_rows) {
+    const int ex = MODE == 0 ? uni(ti / rt) : 0;
+    e = a.dense_expert + ex; e_first = ex * rt; e_cnt = a.dense_rows; row0 = 0;
+    if (ex > 0) h = a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff;
+  } else {
+    // the last expert whose first tile is not past ti
+    int c = 0;
 #pragma unroll
-    for (int v = 0; v < 4; v++)
-      *(u32x4*)(Bs + b_dst + 8 * v) = u32x4{out[4 * v], out[4 * v + 1], out[4 * v + 2], out[4 * v + 3]};
-  };
+    for (int j = 0; j < 4; j++) c += (int)__builtin_popcountll(__ballot(tstart[j] <= ti));
+    e = uni(c - 1);
+    const int jl = e >> 6, l = e & 63;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      if (j == jl) {
+        e_first = __builtin_amdgcn_readlane(tstart[j], l);
+        e_base = __builtin_amdgcn_readlane(toff[j], l);
+        e_cnt = __builtin_amdgcn_readlane(tcnt[j], l);
+      }
+    row0 = e_base;
+  }
+  // an expert's rows are dealt to its tiles in whole fragments, as evenly as those go
+  const int e_tiles = (e_cnt + BM - 1) / BM, tile_rows = 32 * uni(((e_cnt + 31) / 32 + e_tiles - 1) / e_tiles);
+  const int m0 = uni((ti - e_first) * tile_rows), m_cnt = uni(min(tile_rows, e_cnt - m0));
+  if (m_cnt <= 0) return;                               // (fewer fragments than tiles cannot be: kept as a guard)
 
-  f32x16 acc[3][2];
-#pragma unroll
-  for (int i = 0; i < 3; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.0f;
-
-  // 32-row fragments of this wave are mh, mh+2, mh+4; the first nf of them hold rows of the tile
-  const int n_frag_total = (m_cnt + 31) >> 5;
-  const int nf = n_frag_total > mh ? (n_frag_total - mh + 1) >> 1 : 0;
+  const int K = MODE == 0 ? a.d_model : a.d_ff;
+  const int N = MODE == 0 ? a.d_ff : a.d_model;         // output columns of this GEMM
   const int nk = K / PF_BK;
+  const int nf = (m_cnt + 31) >> 5;
+  const int n = lane & 31, hh = lane >> 5;
 
-  // K loop for a wave with NF live fragments: step t multiplies out of LDS buffer t&1 while the
-  // inputs of step t+1 are expanded into the other buffer; the expansion (VALU) and the products
-  // (MFMA) are independent instruction streams of one basic block, which the compiler interleaves.  Loads run two steps ahead;
-  // past the end they repeat the last step (their results are not used).
+  // ---- the wave's 32 weight rows.  MODE 0: gate and up rows alternate in the bank, so they are the gate and up rows
+  // of 16 output columns; lanes 0 .. 15 take the gate rows, lanes 16 .. 31 the up rows.  Rows past the matrix read
+  // out of the section's range.
+  const uint32_t wrow = (uint32_t)(nt * PF_BN + wave * 32);
+  const uint32_t rowb = (uint32_t)(K >> 5) * PB32;
+  const int sh = a.group_shift;
+  const int n_grp = sh >= 8 ? 1 : 256 >> sh;                   // groups of 256 columns
+  // plane loads: lane i's 16 bytes land at 16 i, row after row of PROW bytes; the nibble planes' eight pieces of a row
+  // are stored permuted (piece p at p ^ (row / 2 % 8)), so that the operand reads hit all banks
+  constexpr int NPO = FMT == 0 ? 2 : FMT == 1 ? 1 : NPL;       // load q: p_off[q % NPO], PSTEP rows further down for every NPO loads
+  constexpr int PSTEP = NPO * 64 / PPR;
+  uint32_t p_off[NPO];
+#pragma unroll
+  for (int q = 0; q < NPO; q++) {
+    const uint32_t i = q * 64 + lane, r = i / PPR, c = i % PPR;
+    p_off[q] = (wrow + r) * rowb + (FMT == 0 ? c ^ ((r >> 1) & 7u) : c) * 16;
+  }
+  // scales and zero-points: lanes 0 .. 31 fetch the first of two dwords / groups of their row, lanes 32 .. 63 the second
+  // (a row holds an even number of scales, so a pair of bf16 scales is one aligned dword)
+  const uint32_t s_off = (wrow + n) * (uint32_t)a.w.sng * (SCB ? 2u : 4u) + hh * 4u, z_off = (wrow + n) * (uint32_t)a.w.ng + hh;
+  const uint32_t as_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As;
+  const uint32_t wofs = 2 * BM * 128 + (uint32_t)wave * WAVE_LDS;
+  const uint8_t* warea = As + wofs;
+  const uint32_t wr = MODE == 0 ? 2 * (n & 15) + (n >> 4) : n;                 // the lane's row of the 32
+  const uint32_t p_rd = wr * PROW + (FMT == 0 ? ((uint32_t)hh ^ ((wr >> 1) & 7u)) * 16 : (uint32_t)hh * PB32);
+  typedef typename std::conditional<FMT == 0, u32x4, typename std::conditional<FMT == 1, u32x2, u32x3>::type>::type PlaneV;
+  struct Planes { PlaneV m, l; };
+
+  f32x16 acc[NF];
+#pragma unroll
+  for (int i = 0; i < NF; i++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[i][r] = 0.0f;
+
+  // ---- token rows: a wave's direct load q moves rows 8 (4 q + wave) .. + 7 of the tile, lane i the 16-byte
+  // piece (i % 8) ^ (i / 8) of row i / 8 (of these eight), so that the operand reads, 32 rows of one piece, hit all banks.
+  // MODE 0 gathers the rows of X (a row past the tile's last one repeats that row); MODE 1 reads consecutive
+  // rows of H (past the last one: another tile's, or zeros from out of range).  Rows of the product are
+  // independent and the epilogue stores none of the surplus ones.
+  constexpr int NA = MODE == 0 ? NF : 1;
+  uint32_t a_off[NA];
+#pragma unroll
+  for (int q = 0; q < NA; q++) {
+    const int r = (4 * q + wave) * 8 + (lane >> 3), c = (lane & 7) ^ (lane >> 3);
+    uint32_t src;
+    if (MODE == 0) {
+      const int rc = m0 + min(r, m_cnt - 1);
+      src = (uint32_t)(a.dense_rows ? rc : a.rows[row0 + rc] / a.k) * (uint32_t)a.d_model;
+    } else {
+      src = (uint32_t)(row0 + m0 + r) * (uint32_t)a.d_ff;
+    }
+    a_off[q] = src * 2u + c * 16;
+  }
+  // operand reads: lane (n, hh) takes columns 32 hh + 8 s .. + 7 of row n: piece (4 hh + s) ^ (n % 8)
+  const uint32_t a_rd = n * 128 + (((4 * hh) ^ (n & 7)) * 16);
+  // MODE 1: the weight of row tid of the tile, for the epilogue
+  float my_wt = 0.0f;
+  if (MODE == 1 && tid < m_cnt) my_wt = a.wgt[a.dense_rows ? m0 + tid : a.rows[row0 + m0 + tid]];
+
   auto kloop = [&](auto nf_c) __attribute__((always_inline)) {
-    constexpr int NF = decltype(nf_c)::value;
-    auto compute = [&](const uint16_t* As, const uint16_t* Bs) __attribute__((always_inline)) {
+    constexpr int F = decltype(nf_c)::value;
+    const int n_pass = MODE == 1 && a.dense_rows ? a.n_dense : 1;
+    for (int ex = 0; ex < n_pass; ex++) {
+      if (ex) __syncthreads();                          // every wave is done with the LDS rows of the last pass
+      const size_t ee = (size_t)uni(e + ex);
+      const u32x4 rm = pf_rsrc(a.w.msb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
+      const u32x4 rl = pf_rsrc(a.w.lsb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
+      const u32x4 rs = pf_rsrc(a.w.sc + ee * a.w.sc_stride, (uint32_t)a.w.sc_stride);
+      const u32x4 rz = pf_rsrc(a.w.zp + ee * a.w.zp_stride, (uint32_t)a.w.zp_stride);
+      const u32x4 ra = pf_rsrc(MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff, a.a_bytes);
+      // planes, scales and zero-points of columns 256 i .. 256 i + 255 (past the row's end: bytes of the next row, not used)
+      auto load_weights = [&](int i) __attribute__((always_inline)) {
+        const uint32_t g0 = (uint32_t)(i * 256) >> sh, lds = as_base + wofs;
+        const int nsd = SCB ? (n_grp + 1) >> 1 : n_grp;
+        for (int j = 0; j < nsd; j += 2) dma4(rs, s_off, (SCB ? (g0 >> 1) : g0) * 4u + j * 4u, lds + 2 * PLANE + j * 128u);
+        for (int j = 0; j < n_grp; j += 2) dma1(rz, z_off, g0 + j, lds + ZP_AT + j * 128u);
 #pragma unroll
-      for (int s = 0; s < PF_BK / 16; s++) {
-        const int ko = s * 16 + (lane >> 5) * 8;
-        bf16x8 bf[2];
+        for (int q = 0; q < NPL; q++) {
+          const uint32_t so = (uint32_t)i * PROW + (uint32_t)(q / NPO) * PSTEP * rowb;
+          dma16(rm, p_off[q % NPO], so, lds + q * 1024u);
+          dma16(rl, p_off[q % NPO], so, lds + PLANE + q * 1024u);
+        }
+      };
+      auto load_rows = [&](int t) __attribute__((always_inline)) {
+        const uint32_t lds = as_base + ((t & 1) ? BM * 128u : 0u);
 #pragma unroll
-        for (int j = 0; j < 2; j++) bf[j] = *(const bf16x8*)(Bs + (nq * 64 + j * 32 + (lane & 31)) * PF_LDK + ko);
+        for (int q = 0; q < F; q++)
+          dma16(ra, a_off[MODE == 0 ? q : 0], (uint32_t)t * (PF_BK * 2) + (MODE == 0 ? 0u : (uint32_t)q * 64u * (uint32_t)a.d_ff),
+                lds + (uint32_t)(4 * q + wave) * 1024u);
+      };
+      auto read_planes = [&](int b, Planes& p) __attribute__((always_inline)) {
+        const uint8_t* q = warea + (FMT == 0 ? p_rd ^ (b * 32u) : p_rd + b * 2u * PB32);
+        if constexpr (FMT == 2) {                       // (twelve bytes on a 4-byte boundary)
+          const uint32_t *qm = (const uint32_t*)q, *ql = (const uint32_t*)(q + PLANE);
+          p.m = u32x3{qm[0], qm[1], qm[2]};
+          p.l = u32x3{ql[0], ql[1], ql[2]};
+        } else {
+          p.m = *(const PlaneV*)q;
+          p.l = *(const PlaneV*)(q + PLANE);
+        }
+      };
+      // scale and offset (weight = scale * code + offset) of the lane's row in step t
+      auto read_meta = [&](int t, float& sc, float& c0) __attribute__((always_inline)) {
+        const uint32_t g = (uint32_t)(t * PF_BK + (sh == 5 ? 32 * hh : 0)) >> sh, gl = g & (uint32_t)(n_grp - 1);      // group, its number inside the 256 columns
+        const uint32_t sw = *(const uint32_t*)(warea + 2 * PLANE + (SCB ? gl >> 1 : gl) * 128u + wr * 4);
+        const uint32_t zp = *(const uint32_t*)(warea + ZP_AT + gl * 128u + wr * 4) & 0xFFu;
+        sc = SCB ? __uint_as_float((g & 1u) ? sw & 0xFFFF0000u : sw << 16) : __uint_as_float(sw);
+        c0 = -(float)((SCB ? 1024u : 0u) + zp) * sc;
+      };
+      // codes of columns 8 s .. 8 s + 7 of the lane's 32 -> bf16 s (q - zp)
+      auto expand = [&](const PlaneV& m, const PlaneV& l, int s, float scale, float c0) __attribute__((always_inline)) {
+        uint32_t qe, qo;                          // codes of the even / odd columns, one per byte
+        if constexpr (FMT == 0) {
+          // (the planes hold n ^ 8 per nibble: taken back below)
+          const uint32_t wm = m[s], wl = l[s];
+          qe = ((wm << 4) & 0xF0F0F0F0u) | (wl & 0x0F0F0F0Fu);
+          qo = (wm & 0xF0F0F0F0u) | ((wl >> 4) & 0x0F0F0F0Fu);
+        } else if constexpr (FMT == 2) {
+          // column 8s + i: two low bits in word s >> 1 at bits 4i + 2(s & 1), third bit in word 2 at bit
+          // 4i + s; one value per nibble first, then code = 8 msb + lsb, one per byte
+          auto nib = [&](const PlaneV& w) {
+            const uint32_t lo = (w[s >> 1] >> (2 * (s & 1))) & 0x33333333u;
+            const uint32_t hi = w[2] & (0x11111111u << s);
+            return lo | (s < 2 ? hi << (2 - s) : hi >> (s - 2));
+          };
+          const uint32_t nm = nib(m), nl = nib(l);
+          qe = ((nm & 0x0F0F0F0Fu) << 3) | (nl & 0x0F0F0F0Fu);
+          qo = (((nm >> 4) & 0x0F0F0F0Fu) << 3) | ((nl >> 4) & 0x0F0F0F0Fu);
+        } else {
+          // sixteen 2-bit codes per plane word, column c in bits 2c, 2c+1: spread half a word to one
+          // code per nibble, then code = 4 msb + lsb
+          auto spread = [](uint32_t v) {
+            v = (v | (v << 8)) & 0x00FF00FFu;
+            v = (v | (v << 4)) & 0x0F0F0F0Fu;
+            return (v | (v << 2)) & 0x33333333u;
+          };
+          const uint32_t hm = (m[s >> 1] >> (16 * (s & 1))) & 0xFFFFu, hl = (l[s >> 1] >> (16 * (s & 1))) & 0xFFFFu;
+          const uint32_t qn = (spread(hm) << 2) | spread(hl);
+          qe = qn & 0x0F0F0F0Fu;
+          qo = (qn >> 4) & 0x0F0F0F0Fu;
+        }
+        u32x4 out;
+  #pragma unroll
+        for (int b = 0; b < 4; b++) {
+          if constexpr (SCB) {
+            // the codes of two columns as the halves 1024 + q (exact in fp16), which one mixed-precision FMA each turns
+            // into s (1024 + q) - s (1024 + zp); a bf16 scale times 11 bits is exact in fp32, so this is s (q - zp) rounded once
+            const f16x2 q2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(qo, qe, 0x0C000C00u | ((4u + b) << 16) | b) ^ (FMT == 0 ? 0x64886488u : 0x64006400u));
+            out[b] = pack_bf16(fmaf((float)q2[0], scale, c0), fmaf((float)q2[1], scale, c0));
+          } else {
+            const uint32_t f = FMT == 0 ? 0x88888888u : 0u;
+            const float we = fmaf((float)(((qe ^ f) >> (8 * b)) & 0xFF), scale, c0);
+            const float wo = fmaf((float)(((qo ^ f) >> (8 * b)) & 0xFF), scale, c0);
+            out[b] = pack_bf16(we, wo);
+          }
+        }
+        return __builtin_bit_cast(bf16x8, out);
+      };
+      auto multiply = [&](int t, const Planes& p, float sc, float c0) __attribute__((always_inline)) {
+        const uint8_t* rows = As + ((t & 1) ? BM * 128 : 0);
 #pragma unroll
-        for (int i = 0; i < NF; i++) {
-          const bf16x8 af = *(const bf16x8*)(As + ((mh + 2 * i) * 32 + (lane & 31)) * PF_LDK + ko);
+        for (int s = 0; s < 4; s++) {
+          const bf16x8 bf = expand(p.m, p.l, s, sc, c0);
 #pragma unroll
-          for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf[j], acc[i][j], 0, 0, 0);
+          for (int i = 0; i < F; i++) {
+            const bf16x8 af = *(const bf16x8*)(rows + (a_rd ^ (s * 16)) + i * 4096);
+            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc[i], 0, 0, 0);
+          }
+        }
+      };
+      // The direct loads are the only memory operations of the loop, so the waits count them.  Every wave has its share
+      // of the rows of step t in LDS (and, every fourth step, its weights) before the barrier at the top of step t, and
+      // has finished step t - 1, whose buffer the rows of step t + 1 then overwrite.  Loads complete in order: in the step
+      // after the weights were sent for, leaving the last 2 * NPL loads out (planes) means that the rows are there.
+      load_weights(0);
+      load_rows(0);
+      for (int t = 0; t < nk; t += 4) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (t + 1 < nk) load_rows(t + 1);
+        Planes p[4];
+        float sc[4], c0[4];
+#pragma unroll
+        for (int b = 0; b < 4; b++) { read_planes(b, p[b]); read_meta(t + b, sc[b], c0[b]); }
+        // (the weights have left LDS for the registers: the next ones may come)
+#pragma unroll
+        for (int b = 0; b < 4; b++) asm volatile("" : "+v"(sc[b]), "+v"(c0[b]), "+v"(p[b].m), "+v"(p[b].l));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const bool more = t + 4 < nk;
+        if (more) load_weights((t >> 2) + 1);
+        multiply(t, p[0], sc[0], c0[0]);
+#pragma unroll
+        for (int b = 1; b < 4; b++) {
+          if (t + b < nk) {
+            if (b == 1 && more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NPL) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (t + b + 1 < nk) load_rows(t + b + 1);
+            multiply(t + b, p[b], sc[b], c0[b]);
+          }
         }
       }
-    };
-    // The weight planes are prefetched two steps ahead in two register sets; the rows of A go
-    // through one set: they are written to LDS first thing in a step and reloaded at once.
-    Pre p0, p1;
-    Meta m0, m1;
-    PreA pa;
-    const int k1 = min(1, nk - 1) * PF_BK, k2 = min(2, nk - 1) * PF_BK;
-    gload_a(0, pa);
-    gload(0, p0);
-    mload(0, m0);
-    gload(k1, p1);
-    mload(k1, m1);
-    lstore_a(pa, As0);
-    gload_a(k1, pa);
-    lstore(0, p0, m0, Bs0);
-    gload(k2, p0);
-    if (chunk_of(k2) != chunk_of(0)) mload(k2, m0);
-    for (int t = 0; t < nk; t += 2) {
-      lds_barrier();
-      lstore_a(pa, As1);
-      gload_a(min(t + 2, nk - 1) * PF_BK, pa);
-      lstore((t + 1) * PF_BK, p1, m1, Bs1);
-      compute(As0, Bs0);
-      const int ka = min(t + 3, nk - 1) * PF_BK;
-      gload(ka, p1);
-      if (chunk_of(ka) != chunk_of(min(t + 1, nk - 1) * PF_BK)) mload(ka, m1);
-      if (t + 1 < nk) {
-        lds_barrier();
-        lstore_a(pa, As0);
-        gload_a(min(t + 3, nk - 1) * PF_BK, pa);
-        lstore((t + 2) * PF_BK, p0, m0, Bs0);
-        compute(As1, Bs1);
-        const int kb = min(t + 4, nk - 1) * PF_BK;
-        gload(kb, p0);
-          if (chunk_of(kb) != chunk_of(min(t + 2, nk - 1) * PF_BK)) mload(kb, m0);
-      }
     }
   };
-  if (nf == 3) kloop(std::integral_constant<int, 3>());
-  else if (nf == 2) kloop(std::integral_constant<int, 2>());
-  else if (nf == 1) kloop(std::integral_constant<int, 1>());
-  else kloop(std::integral_constant<int, 0>());
+  if (NF >= 5 && nf == 5) kloop(std::integral_constant<int, (NF >= 5 ? 5 : 1)>());
+  else if (NF >= 4 && nf == 4) kloop(std::integral_constant<int, (NF >= 4 ? 4 : 1)>());
+  else if (NF >= 3 && nf == 3) kloop(std::integral_constant<int, (NF >= 3 ? 3 : 1)>());
+  else if (NF >= 2 && nf == 2) kloop(std::integral_constant<int, (NF >= 2 ? 2 : 1)>());
+  else kloop(std::integral_constant<int, 1>());
 
-  // ---- epilogue.  D layout: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  // ---- epilogue.  D layout: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.  Stores go through a
+  // buffer resource that ends with the tile's last row, so surplus rows are dropped without a branch.
+  __syncthreads();
+  const size_t row_first = (size_t)(row0 + m0);
+  if constexpr (MODE == 0) {
+    // registers r and r + 8 of lanes 0 .. 15 (gate) and 16 .. 31 (up) are exchanged so that a lane holds gate and up of one
+    // element; the bf16 tile is then turned in LDS, so that a row of it, 64 columns, leaves as one 128-byte line
+    constexpr int HLD = 144;                            // bytes of a row in LDS
+    const uint32_t col = (uint32_t)wave * 16 + (n & 15), rb = 4 * hh + 16 * (n >> 4);
 #pragma unroll
-  for (int i = 0; i < 3; i++) {
-    if (i >= nf) continue;
-    const int frag = mh + 2 * i;
+    for (int i = 0; i < NF; i++) {
+      if (i >= nf) continue;
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int m = frag * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      if (m >= m_cnt) continue;
-      const size_t prow = (size_t)(row0 + m0 + m);
-      if (MODE == 0) {
-        const int col = nt * (PF_BN / 2) + nq * 32 + (lane & 31);
-        const float g = acc[i][0][r], u = acc[i][1][r];
-        const float hv = g / (1.0f + __expf(-g)) * u;
-        if (col < N) a.h[prow * a.d_ff + col] = (uint16_t)f32_to_bf16_bits(hv);
-      } else {
-        const float wt = row_wt[m];
+      for (int r = 0; r < 8; r++) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][r]), __float_as_uint(acc[i][r + 8]), false, false);
+        const float g = __uint_as_float(sw[0]), u = __uint_as_float(sw[1]);
+        const float hv = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+        *(uint16_t*)(As + (i * 32 + 8 * (r >> 2) + (r & 3) + rb) * HLD + col * 2) = (uint16_t)pack_bf16(hv, hv);
+      }
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(h + row_first * a.d_ff, 0, (int)((uint32_t)m_cnt * (uint32_t)a.d_ff * 2u), 0x00020000);
+    for (int q = 0; q < nf; q++) {
+      const uint32_t r = q * 32 + (tid >> 3), c = tid & 7;
+      __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)(As + r * HLD + c * 16), ro, (int)((r * (uint32_t)a.d_ff + nt * (PF_BN / 2) + c * 8) * 2u), 0, 0);
+    }
+  } else {
+    float* row_wt = (float*)As;
+    if (tid < BM) row_wt[tid] = my_wt;
+    __syncthreads();
+    if ((int)wrow < N) {                                // (a wave's 32 columns are inside or outside as a whole)
+      const uint32_t ldo = (uint32_t)a.d_model * 4u;
+      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(a.o + row_first * a.d_model, 0, (int)((uint32_t)m_cnt * ldo), 0x00020000);
+      const uint32_t vo = 4 * hh * ldo + (wrow + n) * 4u;
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-          const int col = nt * PF_BN + nq * 64 + j * 32 + (lane & 31);
-          if (col < N) {
-            float* dst = a.o + prow * a.d_model + col;
-            *dst = a.accumulate ? *dst + wt * acc[i][j][r] : wt * acc[i][j][r];
+      for (int i = 0; i < NF; i++) {
+        if (i >= nf) continue;
+#pragma unroll
+        for (int rq = 0; rq < 4; rq++) {
+          const float4 w4 = *(const float4*)(row_wt + i * 32 + 8 * rq + 4 * hh);
+          const float wt[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            const int so = (int)((uint32_t)(i * 32 + 8 * rq + r) * ldo);
+            float v = wt[r] * acc[i][4 * rq + r];
+            if (a.accumulate) v += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, (int)vo, so, 0));
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ro, (int)vo, so, 0);
           }
         }
       }
@@ -487,24 +565,37 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* o, const int3
 // ------------------------------------------------------------------------------- host entry
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// bits = plane bits per code of the bank (4: 8/4 nest, 3: 6/3 nest, 2: 4/2 nest)
-template <int MODE>
-static void launch_gemm(const GemmArgs& g, int bits, int grid, hipStream_t st) {
+template <int MODE, int NF>
+static void launch_gemm_nf(const GemmPair& g, int sc_bf16, int bits, int grid, hipStream_t st) {
   if (bits == 2) {
-    if (g.sc_bf16) grouped_gemm_kernel<MODE, 1, 1><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 1><<<grid, PF_NT, 0, st>>>(g);
+    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 1, NF><<<grid, PF_NT, 0, st>>>(g);
+    else grouped_gemm_kernel<MODE, 0, 1, NF><<<grid, PF_NT, 0, st>>>(g);
   } else if (bits == 3) {
-    if (g.sc_bf16) grouped_gemm_kernel<MODE, 1, 2><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 2><<<grid, PF_NT, 0, st>>>(g);
+    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 2, NF><<<grid, PF_NT, 0, st>>>(g);
+    else grouped_gemm_kernel<MODE, 0, 2, NF><<<grid, PF_NT, 0, st>>>(g);
   } else {
-    if (g.sc_bf16) grouped_gemm_kernel<MODE, 1, 0><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 0><<<grid, PF_NT, 0, st>>>(g);
+    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 0, NF><<<grid, PF_NT, 0, st>>>(g);
+    else grouped_gemm_kernel<MODE, 0, 0, NF><<<grid, PF_NT, 0, st>>>(g);
   }
+}
+// bits = plane bits per code of the bank (4: 8/4 nest, 3: 6/3 nest, 2: 4/2 nest); nf = fragments of the tallest tile
+template <int MODE>
+static void launch_gemm(const GemmPair& g, int sc_bf16, int bits, int nf, int grid, hipStream_t st) {
+  if (nf == 1) launch_gemm_nf<MODE, 1>(g, sc_bf16, bits, grid, st);
+  else if (nf == 2) launch_gemm_nf<MODE, 2>(g, sc_bf16, bits, grid, st);
+  else if (nf == 3) launch_gemm_nf<MODE, 3>(g, sc_bf16, bits, grid, st);
+  else launch_gemm_nf<MODE, 5>(g, sc_bf16, bits, grid, st);
+}
+// Tile height for experts of `rows` rows on average: one tile for nearly every expert (mean plus one and a half
+// standard deviations of even routing) if five fragments can do that, else the tallest tile.
+static int pick_nf(double rows) {
+  const double want = rows + 1.5 * sqrt(rows);
+  return want <= 32.0 ? 1 : want <= 64.0 ? 2 : want <= 96.0 ? 3 : 5;
 }
 
 struct PrefillLayout { size_t rows, pos, offsets, tiles, h, o, gamma, h_s, o_s, total; };
 
-static inline int max_tiles(int T, int E, int k) { return E + (T * k) / PF_BM; }
+static inline int max_tiles(int T, int E, int k, int bm) { return E + (T * k) / bm; }
 
 static PrefillLayout prefill_layout(int T, int E, int k, int d_model, int d_ff, int shared_d_ff) {
   PrefillLayout L;
@@ -512,7 +603,7 @@ static PrefillLayout prefill_layout(int T, int E, int k, int d_model, int d_ff, 
   L.rows = off;    off = up256(off + (size_t)T * k * 4);
   L.pos = off;     off = up256(off + (size_t)T * k * 4);
   L.offsets = off; off = up256(off + (size_t)(E + 1) * 4);
-  L.tiles = off;   off = up256(off + (size_t)(4 + 4 * (max_tiles(T, E, k) + 8)) * 4);   // the grid rounds the tile count up to 8
+  L.tiles = off;   off = up256(off + (size_t)(4 + 4 * (E + (T * k) / 192 + 8)) * 4);      // the list takes 4 + E words of it
   L.h = off;       off = up256(off + (size_t)T * k * d_ff * 2);
   L.o = off;       off = up256(off + (size_t)T * k * d_model * 4);
   L.gamma = L.h_s = L.o_s = off;
@@ -570,36 +661,73 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
 
   RouteArgs ra{E, k, d, logits_dev, x_dev, w_router_dev, nullptr, norm_topk, routed_scale, nullptr, idx_dev, w_dev};
   { const int rc = smoe_launch_route(ctx, ra, T, SMOE_BF16); if (rc) return rc; }
-  group_kernel<<<E, GR_THREADS, 0, st>>>(idx_dev, T * k, E, hist_dev, offsets, tiles, rows, pos);
+  const int nf = pick_nf((double)T * k / E), bm = 32 * nf;
+  group_kernel<<<E, GR_THREADS, 0, st>>>(idx_dev, T * k, E, bm, hist_dev, offsets, tiles, rows, pos);
 
   GemmArgs g{};
-  g.sc_bf16 = routed->dev.sc_bf16; g.group_shift = __builtin_ctz((unsigned)routed->dev.group); g.offsets = offsets; g.tiles = tiles; g.rows = rows;
-  g.x = (const uint16_t*)x_dev; g.h = h; g.o = o; g.wgt = w_dev; g.k = k; g.d_model = d; g.d_ff = f;
-  const int mt = max_tiles(T, E, k);             // upper bound of the tile count; surplus work-groups return at once
-  const int mt8 = (mt + 7) / 8 * 8;
-  g.w = routed->dev.gu; g.n_col_tiles = (2 * f + PF_BN - 1) / PF_BN;
-  launch_gemm<0>(g, routed->dev.bits, mt8 * g.n_col_tiles, st);
-  g.w = routed->dev.dn; g.n_col_tiles = (d + PF_BN - 1) / PF_BN;
-  launch_gemm<1>(g, routed->dev.bits, mt8 * g.n_col_tiles, st);
+  g.group_shift = __builtin_ctz((unsigned)routed->dev.group); g.offsets = offsets; g.tiles = tiles; g.rows = rows; g.hist = hist_dev;
+  g.x = (const uint16_t*)x_dev; g.h = h; g.o = o; g.wgt = w_dev; g.E = E; g.k = k; g.d_model = d; g.d_ff = f;
+  g.super = (double)T * k / E > bm ? 4 : 1;
+  const int mt = max_tiles(T, E, k, bm);         // upper bound of the tile count; surplus work-groups return at once
+  const int scb = routed->dev.sc_bf16, bits = routed->dev.bits;
+  auto grid_of = [](int n_tiles, int n_col) { return (n_tiles * n_col + 7) / 8 * 8; };
+  GemmPair gu{}, dn{};
+  gu.g[1] = dn.g[1] = g;
+  gu.g[1].a_bytes = (uint32_t)((size_t)T * d * 2); dn.g[1].a_bytes = (uint32_t)((size_t)T * k * f * 2);      // (below 4 GiB: checked above)
+  gu.g[1].w = routed->dev.gu; gu.g[1].n_col_tiles = (2 * f + PF_BN - 1) / PF_BN;
+  dn.g[1].w = routed->dev.dn; dn.g[1].n_col_tiles = (d + PF_BN - 1) / PF_BN;
+  const int gu_grid = grid_of(mt, gu.g[1].n_col_tiles), dn_grid = grid_of(mt, dn.g[1].n_col_tiles);
   float* o_s = nullptr;
-  if (shared) {
-    // the shared experts see every token: dense GEMMs over the token rows in their own order, one
-    // expert after the other into one H buffer, their gate-weighted outputs summed in O_s
+  if (!shared) {
+    launch_gemm<0>(gu, scb, bits, nf, gu_grid, st);
+    launch_gemm<1>(dn, scb, bits, nf, dn_grid, st);
+  } else {
+    // the shared experts see every token: dense GEMMs over the token rows in their own order, their
+    // gate-weighted outputs summed in O_s
     float* gamma = (float*)(s + L.gamma);
     o_s = (float*)(s + L.o_s);
     shared_gate_kernel<<<(T + 3) / 4, 256, 0, st>>>((const uint16_t*)x_dev, (const uint16_t*)shared_gate_w_dev, T, d, gamma);
     GemmArgs q{};
-    q.sc_bf16 = shared->dev.sc_bf16; q.group_shift = __builtin_ctz((unsigned)shared->dev.group);
-    q.x = (const uint16_t*)x_dev; q.h = (uint16_t*)(s + L.h_s); q.o = o_s; q.wgt = gamma; q.k = 1; q.d_model = d; q.d_ff = f_s;
-    q.dense_rows = T;
-    const int nt8 = ((T + PF_BM - 1) / PF_BM + 7) / 8 * 8;
-    for (int e = 0; e < shared->desc.n_experts; e++) {
-      q.dense_expert = e; q.accumulate = e > 0;
-      q.w = shared->dev.gu; q.n_col_tiles = (2 * f_s + PF_BN - 1) / PF_BN;
-      launch_gemm<0>(q, shared->dev.bits, nt8 * q.n_col_tiles, st);
-      q.w = shared->dev.dn; q.n_col_tiles = (d + PF_BN - 1) / PF_BN;
-      launch_gemm<1>(q, shared->dev.bits, nt8 * q.n_col_tiles, st);
+    q.group_shift = __builtin_ctz((unsigned)shared->dev.group);
+    q.x = (const uint16_t*)x_dev; q.h = (uint16_t*)(s + L.h_s); q.o = o_s; q.wgt = gamma; q.E = shared->desc.n_experts; q.k = 1; q.d_model = d; q.d_ff = f_s;
+    q.dense_rows = T; q.super = 8;
+    // H of one shared expert has its own place, that of others waits in the rows of O until the routed
+    // experts' down GEMM writes there: as many experts as fit are worked out together
+    q.h_more = (uint16_t*)o;
+    const int ns = shared->desc.n_experts;
+    const int at_once = (int)std::min<size_t>((size_t)ns, 1 + ((size_t)T * k * d * 4) / ((size_t)T * f_s * 2));
+    // few tokens: the shared experts' tiles ride in the routed experts' launches (same tile height) instead of
+    // leaving most of the chip idle in launches of their own
+    const bool same = shared->dev.sc_bf16 == scb && shared->dev.bits == bits;
+    const bool join = same && T <= 8 * bm;
+    const int nfs = pick_nf((double)T);
+    for (int e0 = 0; e0 < ns; e0 += at_once) {
+      q.dense_expert = e0; q.n_dense = std::min(at_once, ns - e0); q.accumulate = e0 > 0;
+      const bool j0 = join && e0 == 0, j1 = j0 && ns == 1;
+      const int nq = j0 ? nf : nfs, rt = (T + 32 * nq - 1) / (32 * nq);
+      GemmArgs qg = q, qd = q;
+      qg.a_bytes = (uint32_t)((size_t)T * d * 2); qd.a_bytes = (uint32_t)((size_t)T * f_s * 2);
+      qg.w = shared->dev.gu; qg.n_col_tiles = (2 * f_s + PF_BN - 1) / PF_BN;
+      qd.w = shared->dev.dn; qd.n_col_tiles = (d + PF_BN - 1) / PF_BN;
+      const int gg = grid_of(rt * q.n_dense, qg.n_col_tiles), gd = grid_of(rt, qd.n_col_tiles);
+      if (j0) {
+        gu.g[0] = qg; gu.nb0 = gg;
+        launch_gemm<0>(gu, scb, bits, nf, gg + gu_grid, st);
+      } else {
+        GemmPair one{};
+        one.g[0] = qg; one.nb0 = gg;
+        launch_gemm<0>(one, shared->dev.sc_bf16, shared->dev.bits, nq, gg, st);
+      }
+      if (j1) {
+        dn.g[0] = qd; dn.nb0 = gd;
+      } else {
+        GemmPair one{};
+        one.g[0] = qd; one.nb0 = gd;
+        launch_gemm<1>(one, shared->dev.sc_bf16, shared->dev.bits, nq, gd, st);
+      }
     }
+    if (!join) launch_gemm<0>(gu, scb, bits, nf, gu_grid, st);
+    launch_gemm<1>(dn, scb, bits, nf, dn.nb0 + dn_grid, st);
   }
   combine_kernel<<<T, 256, 0, st>>>(o, pos, o_s, (const uint16_t*)x_dev, (uint16_t*)y_dev, k, d, add_residual);
   HIPCHK(ctx, hipGetLastError());

@@ -92,6 +92,31 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     assert O.max_abs_rel(t2np(yd), t2np(y[t])) <= TOL
 
 
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank", [
+    (40, 4, 2, 64, 64, 32, 0, 0, (8, 4), "bf16"),        # one K step per GEMM, one fragment per tile
+    (130, 6, 2, 192, 320, 64, 1, 192, (8, 4), "f32"),    # odd numbers of K steps, two fragments, shared tiles in the same launches; fp32 scales
+    (33, 130, 5, 576, 128, 32, 2, 64, (8, 4), "bf16"),   # tile search over more than two lanes' worth of experts, most of them empty; nine steps
+    (400, 5, 1, 128, 448, 128, 2, 320, (6, 3), "f32"),   # three fragments; seven steps (a partial 256-column chunk); two shared experts
+    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16"), # five fragments, four tiles per expert; shared experts in launches of their own
+    (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16"),  # a group wider than the row; three shared experts at once
+    (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16"),      # shared experts whose H does not fit beside O: one after the other
+])
+def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
+    # tolerance: that of every bf16 prefill test
+    say("prefill tile shapes", T, E, k, d, f, G, n_sh, f_s, nest, bank)
+    shp = synth.LayerShape(d, E, f, k, G, n_shared=n_sh, shared_d_ff=f_s, act=bank, b_high=nest[0], b_low=nest[1])
+    pair = LayerPair(ctx, shp, seed=51)
+    x = synth.activations(51, T, d, "bf16").cuda()
+    wr = synth.router_weight(51, 0, E, d, std=0.05).cuda()
+    y, idx, w, hist = B.smoe_prefill_histogram(ctx, pair.routed, pair.shared, x, k, w_router=wr, add_residual=True)
+    ridx, rw = _check_routing(ctx, x, wr, k, idx, w, hist, E)
+    yref = O.prefill_layer(t2np(x).astype(np.float64), pair.oracle_routed(), ridx, rw.astype(np.float32).astype(np.float64),
+                           pair.oracle_shared(), None, add_residual=True)
+    yg = t2np(y)
+    for t in range(T):
+        assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
 @pytest.mark.parametrize("nest", [(4, 2), (6, 3)])
 @pytest.mark.parametrize("G,sdt", [(64, "bf16"), (32, "bf16")])
 def test_prefill_lower_nests(ctx, G, sdt, nest):
