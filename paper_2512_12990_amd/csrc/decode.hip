@@ -468,27 +468,9 @@ __device__ __forceinline__ void load_xr(XR<ACT>& x, const uint8_t* vec, const fl
 }
 
 // ---------------------------------------------------------------------------------- routing by one wave
-template <int CTRL, int ROWM, int BANKM> __device__ __forceinline__ uint32_t dpp_umax(uint32_t v) {
-  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWM, BANKM, true);
-  return t > v ? t : v;
-}
-// Unsigned maximum over the wave, returned in every lane.
-__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
-  v = dpp_umax<0xB1, 0xF, 0xF>(v);
-  v = dpp_umax<0x4E, 0xF, 0xF>(v);
-  v = dpp_umax<0x114, 0xF, 0xE>(v);
-  v = dpp_umax<0x118, 0xF, 0xC>(v);
-  v = dpp_umax<0x142, 0xA, 0xF>(v);
-  v = dpp_umax<0x143, 0xC, 0xF>(v);
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
 __device__ __forceinline__ float wave_sum_all(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to63(v)), 63));
 }
-__device__ __forceinline__ float unorderable(uint32_t o) {
-  return __uint_as_float((o & 0x80000000u) ? (o ^ 0x80000000u) : ~o);
-}
-
 // Same decision rule as select_topk_wave (route_device.hpp) -- k largest biased scores, ties to the
 // lower expert index, weights from the softmax of the unbiased logits -- executed by a single
 // wave with cross-lane DPP reductions only.  Lane e (+64j) holds logit, bias and slice mask of

@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const float* __restr
                                                             int E, int d, float* __restrict__ z) {
   const int lane = threadIdx.x & 63, e = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= E) return;
-  // Same sum as router_row_dots (lane l adds columns l, l+64, ... in that order by fused
+  // Same sum as router_logits_block (lane l adds columns l, l+64, ... in that order by fused
   // multiply-add, then the wave sum), but 32 columns per lane are fetched before the first is used:
   // one memory round trip per 2048 columns instead of four.
   const uint32_t* wrow = (const uint32_t*)(w_router + (size_t)e * d);
@@ -64,21 +64,30 @@ static int route_lds_grant(smoe_ctx* ctx, K kernel, size_t lds, size_t& granted)
   return SMOE_OK;
 }
 
-int smoe_launch_route(smoe_ctx* ctx, const RouteArgs& a, int T, int act_dtype) {
-  const bool given = a.logits != nullptr;
-  if (act_dtype == SMOE_BF16) {
-    const size_t lds = RouteLds<SMOE_BF16, 8>::bytes(a.E, a.d_model, given);
-    const int rc = route_lds_grant(ctx, route_batch_kernel<SMOE_BF16, 8>, lds, ctx->route_lds_granted[0]);
-    if (rc != SMOE_OK) return rc;
-    route_batch_kernel<SMOE_BF16, 8><<<(T + 7) / 8, RT_THREADS, lds, ctx->stream>>>(a, T);
-  } else {
-    const size_t lds = RouteLds<SMOE_F32, 4>::bytes(a.E, a.d_model, given);
-    const int rc = route_lds_grant(ctx, route_batch_kernel<SMOE_F32, 4>, lds, ctx->route_lds_granted[1]);
-    if (rc != SMOE_OK) return rc;
-    route_batch_kernel<SMOE_F32, 4><<<(T + 3) / 4, RT_THREADS, lds, ctx->stream>>>(a, T);
-  }
+template <int ACT, int NT>
+static int launch_route_t(smoe_ctx* ctx, const RouteArgs& a, int T) {
+  constexpr int slot = (ACT == SMOE_BF16 ? 0 : 4) + (NT == 8 ? 3 : NT == 4 ? 2 : NT == 2 ? 1 : 0);
+  const size_t lds = RouteLds<ACT, NT>::bytes(a.E, a.d_model, a.logits != nullptr);
+  const int rc = route_lds_grant(ctx, route_batch_kernel<ACT, NT>, lds, ctx->route_lds_granted[slot]);
+  if (rc != SMOE_OK) return rc;
+  route_batch_kernel<ACT, NT><<<(T + NT - 1) / NT, RT_THREADS, lds, ctx->stream>>>(a, T);
   HIPCHK(ctx, hipGetLastError());
   return SMOE_OK;
+}
+
+int smoe_launch_route(smoe_ctx* ctx, const RouteArgs& a, int T, int act_dtype) {
+  // what is accepted does not depend on the number of tokens: the limit is that of the widest form with 64-bit
+  // selection keys per wave beside the activations
+  const bool bf16 = act_dtype == SMOE_BF16;
+  const int nt = bf16 ? 8 : 4;
+  const size_t most = (size_t)nt * a.E * 4 + (size_t)RT_NW * a.E * 8 + RT_NW * SMOE_MAX_TOPK * 8 +
+                      (a.logits ? 0 : (size_t)(a.d_model + a.d_model / nt + 1) * 16);
+  if (most > 160u * 1024u) return SMOE_ESIZE;
+  const int cu = ctx->n_cu;
+  if (T <= cu) return bf16 ? launch_route_t<SMOE_BF16, 1>(ctx, a, T) : launch_route_t<SMOE_F32, 1>(ctx, a, T);
+  if (T <= 2 * cu) return bf16 ? launch_route_t<SMOE_BF16, 2>(ctx, a, T) : launch_route_t<SMOE_F32, 2>(ctx, a, T);
+  if (!bf16 || T <= 4 * cu) return bf16 ? launch_route_t<SMOE_BF16, 4>(ctx, a, T) : launch_route_t<SMOE_F32, 4>(ctx, a, T);
+  return launch_route_t<SMOE_BF16, 8>(ctx, a, T);
 }
 
 extern "C" int smoe_route(smoe_ctx* ctx, int T, int E, int k, int d_model, const float* logits_dev,

@@ -24,216 +24,239 @@ __device__ __forceinline__ uint32_t orderable(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-  for (int m = 32; m >= 1; m >>= 1) {
-    uint32_t lo = __shfl_xor((uint32_t)v, m), hi = __shfl_xor((uint32_t)(v >> 32), m);
-    unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    v = o > v ? o : v;
-  }
-  return v;
+__device__ __forceinline__ float unorderable(uint32_t o) {
+  return __uint_as_float((o & 0x80000000u) ? (o ^ 0x80000000u) : ~o);
 }
 
-// Top-k selection of one token by ONE wave.  z[0..E) are the token's logits (LDS), key[0..E) is
-// scratch (LDS).  Writes a.idx / a.w for token t and leaves the decision in sel[] / wsel[] (LDS).
+template <int CTRL, int ROWM, int BANKM> __device__ __forceinline__ uint32_t dpp_umax(uint32_t v) {
+  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWM, BANKM, true);
+  return t > v ? t : v;
+}
+// Unsigned maximum over the wave, returned in every lane.
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
+  v = dpp_umax<0xB1, 0xF, 0xF>(v);
+  v = dpp_umax<0x4E, 0xF, 0xF>(v);
+  v = dpp_umax<0x114, 0xF, 0xE>(v);
+  v = dpp_umax<0x118, 0xF, 0xC>(v);
+  v = dpp_umax<0x142, 0xA, 0xF>(v);
+  v = dpp_umax<0x143, 0xC, 0xF>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Top-k selection of one token by ONE wave.  z[0..E) are the token's logits (LDS); lane l keeps the experts l,
+// l + 64, ... (NJ of them) in registers, and every pick is one reduction over the wave's lanes.
 // Rule: k largest z + bias from the highest down, equal scores to the lower expert index; weights
 // = softmax of the unbiased logits at the selected experts (optionally renormalised), * scale.
-__device__ __forceinline__ void select_topk_wave(const RouteArgs& a, int t, const float* z, unsigned long long* key,
-                                                 int* sel, float* wsel, int lane) {
+template <int NJ>
+__device__ __forceinline__ void select_topk_wave(const RouteArgs& a, int t, const float* z, int lane) {
   const int E = a.E;
-  for (int e = lane; e < E; e += 64) {
-    const float score = z[e] + (a.bias ? a.bias[e] : 0.0f);          // one fp32 add
-    key[e] = ((unsigned long long)orderable(score) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)e);
+  float zv[NJ], p[NJ];
+  uint32_t ord[NJ], zmax = 0;      // ord: orderable biased score; 0 = absent or already taken
+#pragma unroll
+  for (int j = 0; j < NJ; j++) {
+    const int e = lane + 64 * j;
+    const bool ok = e < E;
+    zv[j] = ok ? z[e] : 0.0f;
+    const float score = zv[j] + (ok && a.bias ? a.bias[e] : 0.0f);          // one fp32 add
+    const uint32_t os = orderable(score), oz = orderable(zv[j]);
+    ord[j] = ok ? (os > 1u ? os : 1u) : 0u;
+    zmax = ok && oz > zmax ? oz : zmax;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  float m = -INFINITY;
-  for (int e = lane; e < E; e += 64) m = fmaxf(m, z[e]);
-  for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
+  const float m = unorderable(wave_umax(zmax));
   float den = 0.0f;
-  for (int e = lane; e < E; e += 64) den += expf(z[e] - m);
+#pragma unroll
+  for (int j = 0; j < NJ; j++) { p[j] = lane + 64 * j < E ? expf(zv[j] - m) : 0.0f; den += p[j]; }
   den = wave_sum(den);
-  float wsum = 0.0f;
-  for (int j = 0; j < a.k; j++) {
-    unsigned long long best = 0;
-    for (int e = lane; e < E; e += 64) best = key[e] > best ? key[e] : best;
-    best = wave_max_u64(best);
-    const int e_star = (int)(0xFFFFFFFFu - (uint32_t)best);
-    const float wj = expf(z[e_star] - m) / den;
+  float wsum = 0.0f, myw = 0.0f;
+  int mysel = 0;
+  for (int r = 0; r < a.k; r++) {
+    uint32_t best = ord[0];
+    int jb = 0;
+#pragma unroll
+    for (int j = 1; j < NJ; j++) if (ord[j] > best) { best = ord[j]; jb = j; }
+    const uint32_t top = wave_umax(best);
+    int ls, js;
+    if (NJ == 1) {                                            // lowest lane among equal scores
+      ls = (int)__builtin_ctzll(__ballot(best == top)); js = 0;
+    } else {
+      const int e_star = (int)~wave_umax(~(best == top ? (uint32_t)(lane + 64 * jb) : 0xFFFFFFFFu));      // lowest index among equal scores
+      ls = e_star & 63; js = e_star >> 6;
+    }
+    float pw = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+      const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p[j]), ls));
+      if (js == j) pw = u;
+      if (js == j && lane == ls) ord[j] = 0u;
+    }
+    const float wj = pw / den;
     wsum += wj;
-    if (lane == 0) { sel[j] = e_star; wsel[j] = wj; key[e_star] = 0; }
-    // the key write must be visible to the whole wave before the next scan
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
+    if (lane == r) { mysel = ls + 64 * js; myw = wj; }      // slot r belongs to lane r
   }
   const float mul = (a.norm_topk ? 1.0f / wsum : 1.0f) * a.routed_scale;
   if (lane < a.k) {
-    const float wj = wsel[lane] * mul;
-    wsel[lane] = wj;
-    a.idx[(size_t)t * a.k + lane] = sel[lane];
-    a.w[(size_t)t * a.k + lane] = wj;
+    a.idx[(size_t)t * a.k + lane] = mysel;
+    a.w[(size_t)t * a.k + lane] = myw * mul;
   }
 }
 
-// Dot products of one router row with NT activation vectors by one wave.  Lane l sums columns
-// l, l+64, l+128, ... in that order by fused multiply-add, then the wave sum: every kernel that
-// produces router logits uses this routine, so logits are bit-identical between entry points.
-// xget(q, i) returns activation i of vector q.  The results are valid in every lane.
-template <int NT, class XF>
-__device__ __forceinline__ void router_row_dots(const float* __restrict__ wrow, int d, int lane, XF xget, float* p) {
-#pragma unroll
-  for (int q = 0; q < NT; q++) p[q] = 0.0f;
-  int i0 = 0;
-  for (; i0 + 512 <= d; i0 += 512) {          // eight loads in flight per lane
-    float w[8];
-#pragma unroll
-    for (int u = 0; u < 8; u++) w[u] = wrow[i0 + u * 64 + lane];
-#pragma unroll
-    for (int u = 0; u < 8; u++)
-#pragma unroll
-      for (int q = 0; q < NT; q++) p[q] = fmaf(w[u], xget(q, i0 + u * 64 + lane), p[q]);
-  }
-  for (int i = i0 + lane; i < d; i += 64) {
-    const float w = wrow[i];
-#pragma unroll
-    for (int q = 0; q < NT; q++) p[q] = fmaf(w, xget(q, i), p[q]);
-  }
-#pragma unroll
-  for (int q = 0; q < NT; q++) p[q] = wave_sum(p[q]);
-}
-
-// Dot products of RT_R consecutive router rows (first row e0; rows past E repeat row E-1 and are
-// discarded by the caller) with the NT activation vectors of the work-group.  xs holds the vectors
-// column by column ([d][NT] in storage dtype, 16 bytes per column), so one LDS read feeds NT*RT_R
-// multiply-adds.  Every (row, vector) sum takes the columns in the order router_row_dots does.
+// Router logits of NT tokens by a work-group of RT_NW waves, then the selection, one wave per token.
+// Lane l of a wave sums columns l, l + 64, ... of a row in that order by fused multiply-add, then comes the wave
+// sum; router_logits_kernel does the same, so logits are bit-identical between entry points.
+// Bound: vector issue (T * E * d / 64 fused multiply-adds of a wave, and a conversion per four of them) with many
+// tokens, the latency of the router rows (E * d * 4 bytes per work-group out of L2) with few.  A wave takes RT_R rows at
+// a time against all NT vectors, 512 columns per batch, the next batch's weights in flight while one is summed.  The
+// vectors stand in LDS column by column, so that one LDS read feeds NT * RT_R multiply-adds.  NT is the
+// smallest of 1, 2, 4, 8 (fp32: 4) that needs no more work-groups than there are CUs.  64 experts, d 2048, bf16, top-6:
+// 173 / 1000 / 2048 / 4096 tokens in 18.7 / 18.7 / 19.4 / 36 us with eight tokens per work-group, cold batches and a
+// selection over LDS keys; 11.6 (what the host needs to send it off) / 12.1 / 16.4 / 30.5 us now.
 #define RT_R 4
-// Position (in 16-byte units) of column i of the staged activations: one unit of padding after every
-// nt columns, so the nt-column blocks that the staging threads of a wave write start in different banks.
-__device__ __forceinline__ int rt_col(int i, int nt) { return i + i / nt; }
-template <int ACT, int NT>
-__device__ __forceinline__ void router_rows_dots_lds(const float* __restrict__ w_router, int e0, int E, int d, int lane,
-                                                     const uint4* xs, float (&p)[RT_R][NT]) {
-  static_assert((ACT == SMOE_BF16 && NT == 8) || (ACT == SMOE_F32 && NT == 4), "one column of xs is 16 bytes");
-  const float* wrow[RT_R];
-#pragma unroll
-  for (int r = 0; r < RT_R; r++) {
-    wrow[r] = w_router + (size_t)min(e0 + r, E - 1) * d;
-#pragma unroll
-    for (int q = 0; q < NT; q++) p[r][q] = 0.0f;
+#define RT_NW 16
+#define RT_THREADS (RT_NW * 64)
+// Position of column i of the staged activations, in columns: one column of padding after every eight, so that the
+// blocks of columns that the staging threads of a wave write start in different banks.
+__device__ __forceinline__ int rt_col(int i) { return i + (i >> 3); }
+
+template <int ACT, int NT> struct RouteLds {      // NT * E logits, then (without given logits) the activations
+  static size_t bytes(int E, int d, bool given_logits) {
+    return (size_t)((NT * E * 4 + 15) & ~15) + (given_logits ? 0 : (size_t)(d + d / 8 + 1) * NT * (ACT == SMOE_BF16 ? 2 : 4));
   }
-  auto column = [&](int i, float (&xf)[NT]) {
-    const uint4 v = xs[rt_col(i, NT)];
-    if (ACT == SMOE_BF16) {
-      const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+};
+
+template <int ACT, int NT>
+__device__ __forceinline__ void router_logits_block(const RouteArgs& a, int t0, int nt, float* zt, uint8_t* xs) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int E = a.E, d = a.d_model;
+  constexpr int ESZ = ACT == SMOE_BF16 ? 2 : 4, VEC = 16 / ESZ, CB = NT * ESZ;      // elements of a 16-byte load, bytes of a column
+  const int nb = d >> 9;                                        // whole batches of 512 columns
+  float w0[RT_R][8], w1[RT_R][8];
+  const float* wrow[RT_R];
+  auto rows_of = [&](int e0) {
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        xf[(2 * j) % NT] = __uint_as_float(u[j] << 16);
-        xf[(2 * j + 1) % NT] = __uint_as_float(u[j] & 0xFFFF0000u);
-      }
-    } else {
-      xf[0] = __uint_as_float(v.x); xf[1] = __uint_as_float(v.y);
-      xf[2 % NT] = __uint_as_float(v.z); xf[3 % NT] = __uint_as_float(v.w);
-    }
+    for (int r = 0; r < RT_R; r++) wrow[r] = a.w_router + (size_t)min(e0 + r, E - 1) * d;      // (rows past E repeat the last one)
   };
-  int i0 = 0;
-  for (; i0 + 512 <= d; i0 += 512) {
-    float w[RT_R][8];
+  auto fetch = [&](int i, float (&w)[RT_R][8]) {
+    const int i0 = min(i, nb - 1) * 512 + lane;
 #pragma unroll
     for (int r = 0; r < RT_R; r++)
 #pragma unroll
-      for (int u = 0; u < 8; u++) w[r][u] = wrow[r][i0 + u * 64 + lane];
+      for (int u = 0; u < 8; u++) w[r][u] = wrow[r][i0 + u * 64];
+  };
+  rows_of(wave * RT_R);
+  constexpr bool AHEAD = NT * ESZ < 16;                         // the widest form has no registers for a second batch, and plenty of sums per batch
+  if (AHEAD && nb) fetch(0, w0);                                // on their way while the activations are staged
+  if (d % VEC == 0) {
+    // a thread moves VEC consecutive columns of one vector
+    for (int i = tid; i < NT * (d / VEC); i += RT_THREADS) {
+      const int q = i % NT, cb = i / NT;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (q < nt) v = *(const uint4*)((const uint8_t*)a.x + ((size_t)(t0 + q) * d + (size_t)cb * VEC) * ESZ);
+      const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int u = 0; u < 8; u++) {
-      float xf[NT];
-      column(i0 + u * 64 + lane, xf);
-#pragma unroll
-      for (int r = 0; r < RT_R; r++)
-#pragma unroll
-        for (int q = 0; q < NT; q++) p[r][q] = fmaf(w[r][u], xf[q], p[r][q]);
+      for (int j = 0; j < VEC; j++) {
+        uint8_t* dst = xs + (size_t)rt_col(cb * VEC + j) * CB + q * ESZ;
+        if (ACT == SMOE_BF16) *(uint16_t*)dst = (uint16_t)(u[j / 2] >> ((j & 1) * 16));
+        else *(uint32_t*)dst = u[j % 4];
+      }
     }
-  }
-  for (int i = i0 + lane; i < d; i += 64) {
-    float xf[NT];
-    column(i, xf);
-#pragma unroll
-    for (int r = 0; r < RT_R; r++) {
-      const float w = wrow[r][i];
-#pragma unroll
-      for (int q = 0; q < NT; q++) p[r][q] = fmaf(w, xf[q], p[r][q]);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < RT_R; r++)
-#pragma unroll
-    for (int q = 0; q < NT; q++) p[r][q] = wave_sum(p[r][q]);
-}
-
-// Routes NT tokens per work-group of RT_NW waves: every router row is read once per group, each wave
-// then selects for its share of the tokens.
-// Dynamic LDS: NT*E floats, RT_NW*E 64-bit keys, RT_NW*16 ints, RT_NW*16 floats, then (without given logits)
-// the activations, 16 bytes per column plus padding.
-#define RT_NW 16
-#define RT_THREADS (RT_NW * 64)
-template <int ACT, int NT>
-__device__ __forceinline__ void route_tokens_block(const RouteArgs& a, int T, uint8_t* dyn) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int E = a.E, d = a.d_model;
-  const int t0 = blockIdx.x * NT, nt = min(NT, T - t0);
-  float* zt = (float*)dyn;                                            // [NT][E]
-  unsigned long long* key = (unsigned long long*)(zt + NT * E);      // [RT_NW waves][E]
-  int* sel = (int*)(key + RT_NW * E);                                 // [RT_NW][16]
-  float* wsel = (float*)(sel + RT_NW * SMOE_MAX_TOPK);                // [RT_NW][16]
-  if (a.logits) {
-    for (int i = tid; i < nt * E; i += RT_THREADS) zt[i] = a.logits[(size_t)t0 * E + i];
   } else {
-    uint8_t* xs = (uint8_t*)(wsel + RT_NW * SMOE_MAX_TOPK);           // 16 bytes per column, see rt_col()
-    constexpr int ESZ = ACT == SMOE_BF16 ? 2 : 4;
-    if (d % NT == 0) {
-      // a thread moves NT consecutive columns of one vector: one 16-byte load, NT LDS stores
-      const int q = tid % NT;
-      for (int cb = tid / NT; cb * NT < d; cb += RT_THREADS / NT) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (q < nt) v = *(const uint4*)((const uint8_t*)a.x + ((size_t)(t0 + q) * d + (size_t)cb * NT) * ESZ);
-        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+    for (int i = tid; i < NT * d; i += RT_THREADS) {
+      const int q = i / d, c = i - q * d;
+      uint8_t* dst = xs + (size_t)rt_col(c) * CB + q * ESZ;
+      if (ACT == SMOE_BF16) *(uint16_t*)dst = q < nt ? ((const uint16_t*)a.x)[(size_t)t0 * d + i] : (uint16_t)0;
+      else *(float*)dst = q < nt ? ((const float*)a.x)[(size_t)t0 * d + i] : 0.0f;
+    }
+  }
+  __syncthreads();
+  auto column = [&](int i, float (&xf)[NT]) {
+    const uint8_t* c = xs + (size_t)rt_col(i) * CB;
+    if constexpr (ACT == SMOE_BF16) {
+      if constexpr (NT == 1) {
+        xf[0] = bf16_bits_to_f32(*(const uint16_t*)c);
+      } else {
+        struct alignas(CB) Words { uint32_t u[NT / 2 ? NT / 2 : 1]; };
+        const Words w = *(const Words*)c;
 #pragma unroll
-        for (int j = 0; j < NT; j++) {
-          uint8_t* dst = xs + (size_t)rt_col(cb * NT + j, NT) * 16 + q * ESZ;
-          if (ACT == SMOE_BF16) *(uint16_t*)dst = (uint16_t)(u[j / 2] >> ((j & 1) * 16));
-          else *(uint32_t*)dst = u[j % 4];
+        for (int j = 0; j < NT / 2; j++) { xf[2 * j] = __uint_as_float(w.u[j] << 16); xf[2 * j + 1] = __uint_as_float(w.u[j] & 0xFFFF0000u); }
+      }
+    } else {
+      struct alignas(CB) Vals { float f[NT]; };
+      const Vals w = *(const Vals*)c;
+#pragma unroll
+      for (int j = 0; j < NT; j++) xf[j] = w.f[j];
+    }
+  };
+  for (int e0 = wave * RT_R; e0 < E; e0 += RT_NW * RT_R) {
+    float p[RT_R][NT];
+#pragma unroll
+    for (int r = 0; r < RT_R; r++)
+#pragma unroll
+      for (int q = 0; q < NT; q++) p[r][q] = 0.0f;
+    auto batch = [&](int i, const float (&w)[RT_R][8]) {
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        float xf[NT];
+        column(i * 512 + u * 64 + lane, xf);
+#pragma unroll
+        for (int r = 0; r < RT_R; r++)
+#pragma unroll
+          for (int q = 0; q < NT; q++) p[r][q] = fmaf(w[r][u], xf[q], p[r][q]);
+      }
+    };
+    if (e0 != wave * RT_R) {
+      rows_of(e0);
+      if (AHEAD && nb) fetch(0, w0);
+    }
+    if constexpr (AHEAD) {
+      for (int i = 0; i < nb; i += 2) {
+        fetch(i + 1, w1);
+        batch(i, w0);
+        if (i + 1 < nb) {
+          fetch(i + 2, w0);
+          batch(i + 1, w1);
         }
       }
     } else {
-      for (int i = tid; i < NT * d; i += RT_THREADS) {
-        const int q = i / d, c = i - q * d;
-        uint8_t* dst = xs + (size_t)rt_col(c, NT) * 16 + q * ESZ;
-        if (ACT == SMOE_BF16) *(uint16_t*)dst = q < nt ? ((const uint16_t*)a.x)[(size_t)t0 * d + i] : (uint16_t)0;
-        else *(float*)dst = q < nt ? ((const float*)a.x)[(size_t)t0 * d + i] : 0.0f;
+      for (int i = 0; i < nb; i++) {
+        fetch(i, w0);
+        batch(i, w0);
       }
     }
-    __syncthreads();
-    for (int e0 = wave * RT_R; e0 < E; e0 += RT_NW * RT_R) {
-      float p[RT_R][NT];
-      router_rows_dots_lds<ACT, NT>(a.w_router, e0, E, d, lane, (const uint4*)xs, p);
-      if (lane == 0)
+    for (int i = nb * 512 + lane; i < d; i += 64) {
+      float xf[NT];
+      column(i, xf);
 #pragma unroll
-        for (int r = 0; r < RT_R; r++)
-          if (e0 + r < E)
+      for (int r = 0; r < RT_R; r++) {
+        const float w = wrow[r][i];
 #pragma unroll
-            for (int q = 0; q < NT; q++) zt[q * E + e0 + r] = p[r][q];
+        for (int q = 0; q < NT; q++) p[r][q] = fmaf(w, xf[q], p[r][q]);
+      }
     }
+#pragma unroll
+    for (int r = 0; r < RT_R; r++)
+#pragma unroll
+      for (int q = 0; q < NT; q++) {
+        const float s = wave_sum(p[r][q]);
+        if (lane == 0 && e0 + r < E) zt[q * E + e0 + r] = s;
+      }
+  }
+}
+
+template <int ACT, int NT>
+__device__ __forceinline__ void route_tokens_block(const RouteArgs& a, int T, uint8_t* dyn) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int E = a.E, t0 = blockIdx.x * NT, nt = min(NT, T - t0);
+  float* zt = (float*)dyn;                                            // [NT][E]
+  if (a.logits) {
+    for (int i = tid; i < nt * E; i += RT_THREADS) zt[i] = a.logits[(size_t)t0 * E + i];
+  } else {
+    router_logits_block<ACT, NT>(a, t0, nt, zt, dyn + ((NT * E * 4 + 15) & ~15));
   }
   __syncthreads();
   if (a.logits_out)
     for (int i = tid; i < nt * E; i += RT_THREADS) a.logits_out[(size_t)t0 * E + i] = zt[i];
   for (int q = wave; q < nt; q += RT_NW) {
-    select_topk_wave(a, t0 + q, zt + q * E, key + wave * E, sel + wave * SMOE_MAX_TOPK, wsel + wave * SMOE_MAX_TOPK, lane);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
+    if (E <= 64) select_topk_wave<1>(a, t0 + q, zt + q * E, lane);
+    else select_topk_wave<4>(a, t0 + q, zt + q * E, lane);
   }
 }
-
-template <int ACT, int NT> struct RouteLds {
-  static size_t bytes(int E, int d, bool given_logits) {
-    return (size_t)NT * E * 4 + (size_t)RT_NW * E * 8 + RT_NW * SMOE_MAX_TOPK * 8 +
-           (given_logits ? 0 : (size_t)(d + d / NT + 1) * 16);
-  }
-};

@@ -169,6 +169,28 @@ def test_route_given_logits(ctx, E, k, T):
         np.testing.assert_allclose(w.cpu().numpy(), rw, rtol=2e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("T,E,k,d,dt", [(256, 8, 2, 512, "bf16"), (257, 60, 4, 1032, "bf16"), (513, 70, 6, 520, "bf16"),
+                                        (1025, 13, 3, 1544, "bf16"), (300, 200, 16, 40, "bf16"), (5, 9, 3, 75, "bf16"),
+                                        (256, 64, 6, 516, "f32"), (511, 5, 5, 1027, "f32"), (1030, 130, 8, 512, "f32")])
+def test_route_token_tiles(ctx, T, E, k, d, dt):
+    # one, two, four and eight tokens per work-group, ragged last work-groups, rows of no, one and several whole batches
+    # of 512 columns with and without a remainder, odd widths; fp32 sums of d terms: a few rounding steps of |w| . |x|
+    say("route tiles", T, E, k, d, dt)
+    x = synth.activations(9, T, d, dt).cuda()
+    wr = synth.router_weight(9, 0, E, d, std=0.05).cuda()
+    bias = torch.linspace(0, 0.5, E, device="cuda:0")
+    idx, w, z = B.smoe_route(ctx, k, x=x, w_router=wr, bias=bias, norm_topk=True, want_logits=True)
+    zr = x.double().cpu() @ wr.double().cpu().T
+    bound = 64 * 2.0 ** -24 * (x.double().abs().cpu() @ wr.double().abs().cpu().T)
+    assert bool(((z.double().cpu() - zr).abs() <= bound).all())
+    ridx, rw = O.route(z.cpu().numpy(), bias.cpu().numpy(), k, norm_topk=True)
+    assert np.array_equal(idx.cpu().numpy(), ridx)
+    np.testing.assert_allclose(w.cpu().numpy(), rw, rtol=2e-5, atol=1e-7)
+    # the same logits through the given-logits form
+    idx2, w2 = B.smoe_route(ctx, k, logits=z, bias=bias, norm_topk=True)
+    assert torch.equal(idx, idx2) and torch.equal(w, w2)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_route_from_activations(ctx, dt):
     say("route from x", dt)
