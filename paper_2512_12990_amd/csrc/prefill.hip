@@ -202,7 +202,8 @@ __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlan
 // need a shorter tile).  Why this shape, measured on the gate/up GEMM of 60 experts of d_model 2048, d_ff 1408 at
 // 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use them, every lane of a
 // load in another cache line, 215 / 183 us; 128 columns at a time through LDS, half a line, 165 / 123 us; a whole line
-// and 32 instead of 64 weight rows per wave, with the epilogue below, 149 / 94 us.  (192 x 256 tiles, weights expanded
+// and 32 instead of 64 weight rows per wave, with the epilogue below, 149 / 94 us; products, reads and expansion dealt out
+// in turn, the first weights sent for before the token rows are looked up, 143 / 91 us.  (192 x 256 tiles, weights expanded
 // once more through LDS, one work-group per CU: 161 / 117 us, and 297 against 215 us on 4096 dense rows, d_ff 5632.)
 template <int MODE, int SCB, int FMT, int NF>      // FMT 0: 8/4 nest, nibble planes; 1: 4/2 nest, 2-bit planes; 2: 6/3 nest, 3-bit planes
 __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(GemmPair pair) {
@@ -319,6 +320,26 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[i][r] = 0.0f;
 
+  // planes, scales and zero-points of columns 256 i .. 256 i + 255 (past the row's end: bytes of the next row, not used)
+  auto load_weights = [&](int ex, int i) __attribute__((always_inline)) {
+    const size_t ee = (size_t)uni(e + ex);
+    const u32x4 rm = pf_rsrc(a.w.msb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
+    const u32x4 rl = pf_rsrc(a.w.lsb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
+    const u32x4 rs = pf_rsrc(a.w.sc + ee * a.w.sc_stride, (uint32_t)a.w.sc_stride);
+    const u32x4 rz = pf_rsrc(a.w.zp + ee * a.w.zp_stride, (uint32_t)a.w.zp_stride);
+    const uint32_t g0 = (uint32_t)(i * 256) >> sh, lds = as_base + wofs;
+    const int nsd = SCB ? (n_grp + 1) >> 1 : n_grp;
+    for (int j = 0; j < nsd; j += 2) dma4(rs, s_off, (SCB ? (g0 >> 1) : g0) * 4u + j * 4u, lds + 2 * PLANE + j * 128u);
+    for (int j = 0; j < n_grp; j += 2) dma1(rz, z_off, g0 + j, lds + ZP_AT + j * 128u);
+#pragma unroll
+    for (int q = 0; q < NPL; q++) {
+      const uint32_t so = (uint32_t)i * PROW + (uint32_t)(q / NPO) * PSTEP * rowb;
+      dma16(rm, p_off[q % NPO], so, lds + q * 1024u);
+      dma16(rl, p_off[q % NPO], so, lds + PLANE + q * 1024u);
+    }
+  };
+  load_weights(0, 0);                                   // on their way while the token rows are looked up
+
   // ---- token rows: a wave's direct load q moves rows 8 (4 q + wave) .. + 7 of the tile, lane i the 16-byte
   // piece (i % 8) ^ (i / 8) of row i / 8 (of these eight), so that the operand reads, 32 rows of one piece, hit all banks.
   // MODE 0 gathers the rows of X (a row past the tile's last one repeats that row); MODE 1 reads consecutive
@@ -349,25 +370,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
     const int n_pass = MODE == 1 && a.dense_rows ? a.n_dense : 1;
     for (int ex = 0; ex < n_pass; ex++) {
       if (ex) __syncthreads();                          // every wave is done with the LDS rows of the last pass
-      const size_t ee = (size_t)uni(e + ex);
-      const u32x4 rm = pf_rsrc(a.w.msb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
-      const u32x4 rl = pf_rsrc(a.w.lsb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
-      const u32x4 rs = pf_rsrc(a.w.sc + ee * a.w.sc_stride, (uint32_t)a.w.sc_stride);
-      const u32x4 rz = pf_rsrc(a.w.zp + ee * a.w.zp_stride, (uint32_t)a.w.zp_stride);
       const u32x4 ra = pf_rsrc(MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff, a.a_bytes);
-      // planes, scales and zero-points of columns 256 i .. 256 i + 255 (past the row's end: bytes of the next row, not used)
-      auto load_weights = [&](int i) __attribute__((always_inline)) {
-        const uint32_t g0 = (uint32_t)(i * 256) >> sh, lds = as_base + wofs;
-        const int nsd = SCB ? (n_grp + 1) >> 1 : n_grp;
-        for (int j = 0; j < nsd; j += 2) dma4(rs, s_off, (SCB ? (g0 >> 1) : g0) * 4u + j * 4u, lds + 2 * PLANE + j * 128u);
-        for (int j = 0; j < n_grp; j += 2) dma1(rz, z_off, g0 + j, lds + ZP_AT + j * 128u);
-#pragma unroll
-        for (int q = 0; q < NPL; q++) {
-          const uint32_t so = (uint32_t)i * PROW + (uint32_t)(q / NPO) * PSTEP * rowb;
-          dma16(rm, p_off[q % NPO], so, lds + q * 1024u);
-          dma16(rl, p_off[q % NPO], so, lds + PLANE + q * 1024u);
-        }
-      };
       auto load_rows = [&](int t) __attribute__((always_inline)) {
         const uint32_t lds = as_base + ((t & 1) ? BM * 128u : 0u);
 #pragma unroll
@@ -443,23 +446,41 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
         }
         return __builtin_bit_cast(bf16x8, out);
       };
-      auto multiply = [&](int t, const Planes& p, float sc, float c0) __attribute__((always_inline)) {
+      // bf: the first quarter's weights, already expanded; returns those of the next step.  While a quarter is multiplied, the
+      // token rows of the next one are read and its weights expanded; the schedule deals one read and a fifth (a third, ...)
+      // of the expansion to every product, because a wave issues in order and gets less than every second slot of its SIMD.
+      auto multiply = [&](auto last_c, int t, bf16x8 bf, const Planes& p, float sc, float c0, const Planes& pn, float scn, float c0n) __attribute__((always_inline)) {
         const uint8_t* rows = As + ((t & 1) ? BM * 128 : 0);
+        bf16x8 af[2][F];
+#pragma unroll
+        for (int i = 0; i < F; i++) af[0][i] = *(const bf16x8*)(rows + a_rd + i * 4096);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < 4; s++) {
-          const bf16x8 bf = expand(p.m, p.l, s, sc, c0);
+          if (s < 3)
+#pragma unroll
+            for (int i = 0; i < F; i++) af[(s + 1) & 1][i] = *(const bf16x8*)(rows + (a_rd ^ ((s + 1) * 16)) + i * 4096);
+          bf16x8 bn = bf;
+          if (s < 3) bn = expand(p.m, p.l, s + 1, sc, c0);
+          else if (!decltype(last_c)::value) bn = expand(pn.m, pn.l, 0, scn, c0n);      // (the last step of a chunk does not have the next planes yet)
+#pragma unroll
+          for (int i = 0; i < F; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][i], bf, acc[i], 0, 0, 0);
 #pragma unroll
           for (int i = 0; i < F; i++) {
-            const bf16x8 af = *(const bf16x8*)(rows + (a_rd ^ (s * 16)) + i * 4096);
-            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc[i], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                   // a product
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                 // an LDS read
+            __builtin_amdgcn_sched_group_barrier(0x2, (26 + F - 1) / F, 0);    // vector instructions
           }
+          __builtin_amdgcn_sched_barrier(0);
+          bf = bn;
         }
+        return bf;
       };
       // The direct loads are the only memory operations of the loop, so the waits count them.  Every wave has its share
       // of the rows of step t in LDS (and, every fourth step, its weights) before the barrier at the top of step t, and
       // has finished step t - 1, whose buffer the rows of step t + 1 then overwrite.  Loads complete in order: in the step
       // after the weights were sent for, leaving the last 2 * NPL loads out (planes) means that the rows are there.
-      load_weights(0);
+      if (ex) load_weights(ex, 0);
       load_rows(0);
       for (int t = 0; t < nk; t += 4) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -473,17 +494,21 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
         for (int b = 0; b < 4; b++) asm volatile("" : "+v"(sc[b]), "+v"(c0[b]), "+v"(p[b].m), "+v"(p[b].l));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         const bool more = t + 4 < nk;
-        if (more) load_weights((t >> 2) + 1);
-        multiply(t, p[0], sc[0], c0[0]);
-#pragma unroll
-        for (int b = 1; b < 4; b++) {
+        if (more) load_weights(ex, (t >> 2) + 1);
+        bf16x8 bf = expand(p[0].m, p[0].l, 0, sc[0], c0[0]);
+        bf = multiply(std::false_type(), t, bf, p[0], sc[0], c0[0], p[1], sc[1], c0[1]);
+        auto next = [&](auto b_c) __attribute__((always_inline)) {
+          constexpr int b = decltype(b_c)::value, n1 = b < 3 ? b + 1 : b;
           if (t + b < nk) {
             if (b == 1 && more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NPL) : "memory");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
             if (t + b + 1 < nk) load_rows(t + b + 1);
-            multiply(t + b, p[b], sc[b], c0[b]);
+            bf = multiply(std::integral_constant<bool, b == 3>(), t + b, bf, p[b], sc[b], c0[b], p[n1], sc[n1], c0[n1]);
           }
-        }
+        };
+        next(std::integral_constant<int, 1>());
+        next(std::integral_constant<int, 2>());
+        next(std::integral_constant<int, 3>());
       }
     }
   };
@@ -708,19 +733,24 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
     q.group_shift = __builtin_ctz((unsigned)shared->dev.group);
     q.x = (const uint16_t*)x_dev; q.h = (uint16_t*)(s + L.h_s); q.o = o_s; q.wgt = gamma; q.E = shared->desc.n_experts; q.k = 1; q.d_model = d; q.d_ff = f_s;
     q.dense_rows = T; q.super = 8;
-    // H of one shared expert has its own place, that of others waits in the rows of O until the routed
-    // experts' down GEMM writes there: as many experts as fit are worked out together
-    q.h_more = (uint16_t*)o;
     const int ns = shared->desc.n_experts;
-    const int at_once = (int)std::min<size_t>((size_t)ns, 1 + ((size_t)T * k * d * 4) / ((size_t)T * f_s * 2));
-    // few tokens: the shared experts' tiles ride in the routed experts' launches (same tile height) instead of
-    // leaving most of the chip idle in launches of their own
     const bool same = shared->dev.sc_bf16 == scb && shared->dev.bits == bits;
-    const bool join = same && T <= 8 * bm;
+    // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
+    // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both
+    // want the same tile height or there are too few tokens for the taller one to matter.
     const int nfs = pick_nf((double)T);
+    const bool join = same && (nf == nfs || T <= 8 * bm);
+    // H of one shared expert has its own place.  That of others waits in Y, which nothing else writes before the last
+    // kernel, if Y is not X and they fit there; else in the rows of O until the routed experts' down GEMM
+    // writes those: then the shared experts' down GEMM comes before it, and as many experts as fit are worked out together.
+    const uint8_t *x0 = (const uint8_t*)x_dev, *y0 = (const uint8_t*)y_dev;
+    const size_t td2 = (size_t)T * d * 2;
+    const bool in_y = (size_t)(ns - 1) * f_s <= (size_t)d && (y0 + td2 <= x0 || x0 + td2 <= y0);
+    q.h_more = in_y ? (uint16_t*)y_dev : (uint16_t*)o;
+    const int at_once = in_y ? ns : (int)std::min<size_t>((size_t)ns, 1 + ((size_t)T * k * d * 4) / ((size_t)T * f_s * 2));
     for (int e0 = 0; e0 < ns; e0 += at_once) {
       q.dense_expert = e0; q.n_dense = std::min(at_once, ns - e0); q.accumulate = e0 > 0;
-      const bool j0 = join && e0 == 0, j1 = j0 && ns == 1;
+      const bool j0 = join && e0 == 0, j1 = j0 && (in_y || ns == 1);
       const int nq = j0 ? nf : nfs, rt = (T + 32 * nq - 1) / (32 * nq);
       GemmArgs qg = q, qd = q;
       qg.a_bytes = (uint32_t)((size_t)T * d * 2); qd.a_bytes = (uint32_t)((size_t)T * f_s * 2);

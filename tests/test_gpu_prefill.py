@@ -1,5 +1,6 @@
 """GPU parity of the prefill path: routing indices and the per-expert histogram bit-exact,
 grouped-GEMM outputs within the bf16 tolerance, top-N retention order from the GPU histogram."""
+import ctypes as C
 import sys
 
 import numpy as np
@@ -115,6 +116,26 @@ def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
     yg = t2np(y)
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
+def test_prefill_in_place(ctx):
+    # Y on top of X: the second shared expert's H then waits beside O and not in Y; the same sums in the same order, so the
+    # result is the one of two buffers, bit for bit
+    T, E, k, d, f, G = 90, 6, 2, 256, 128, 64
+    shp = synth.LayerShape(d, E, f, k, G, n_shared=2, shared_d_ff=128, act="bf16")
+    pair = LayerPair(ctx, shp, seed=61)
+    x = synth.activations(61, T, d, "bf16").cuda()
+    z = synth.normal_logits(61, T, E).cuda()
+    y, idx, w, hist = B.smoe_prefill_histogram(ctx, pair.routed, pair.shared, x, k, logits=z, add_residual=True)
+    scratch = torch.empty(B.smoe_prefill_bytes(T, E, k, d, f, 128), dtype=torch.uint8, device="cuda:0")
+    xy = x.clone()
+    p = lambda t: C.c_void_p(t.data_ptr())
+    rc = B.lib().smoe_prefill_histogram(ctx.h, pair.routed.h, pair.shared.h, C.c_int(T), p(xy), C.c_int(B.BF16), C.c_int(k), p(z),
+                                        C.c_void_p(0), C.c_int(0), C.c_float(1.0), C.c_void_p(0), C.c_int(1), p(scratch),
+                                        C.c_size_t(scratch.numel()), p(xy), p(idx), p(w), p(hist))
+    assert rc == 0
+    torch.cuda.synchronize()
+    assert torch.equal(xy, y)
 
 
 @pytest.mark.parametrize("nest", [(4, 2), (6, 3)])
