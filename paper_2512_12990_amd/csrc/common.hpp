@@ -45,7 +45,7 @@ struct smoe_ctx {
   // measurement aid (smoe_ctx_timing): events around the two decode launches of every call
   int timing;
   void* timing_events;   // std::vector<hipEvent_t>*, four events per decode call
-  size_t down_lds_granted[48];   // dynamic LDS already granted to each down_kernel instantiation on this device
+  size_t down_lds_granted[60];   // dynamic LDS already granted to each down_kernel instantiation on this device
   size_t route_lds_granted[8];   // likewise for the instantiations of route_batch_kernel
   // single-launch decode (smoe_ctx_single_launch)
   int one_launch;                // the mode is on

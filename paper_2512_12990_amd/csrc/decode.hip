@@ -31,6 +31,7 @@
 #include <hip/hip_ext.h>
 #include <vector>
 #include <mutex>
+#include <algorithm>
 
 #define DEC_NT 512                  // threads per work-group
 #define DEC_NW (DEC_NT / 64)
@@ -1080,8 +1081,8 @@ __device__ __forceinline__ void grid_wait(unsigned* sync, unsigned par, int n_wg
 // decision in LDS, a wave first puts the loads of its piece's first rows in flight and only then joins
 // the hand-over (the last wave, which does the polling, issues no loads before it: a poll's answer would
 // queue behind them), and h and the gate weights are read after it.
-template <int ACT, int SCB, int FMT, int RPW, bool ONE>
-__device__ __forceinline__ void down_body(const int* rec, const float* h, int n_combo_s, int n_pieces, int psh, int f_s, int f_r, int ks_s,
+template <int ACT, int SCB, int FMT, bool ONE, bool RAGGED>      // RAGGED: the last work-group of a token may own fewer than RPW rows
+__device__ __forceinline__ void down_body(const int RPW, const int* rec, const float* h, int n_combo_s, int n_pieces, int psh, int f_s, int f_r, int ks_s,
                                           int ks_r, int inv_ks_s, int inv_ks_r, int nsf, const DecodeArgs& a, uint8_t* dyn, int wg, int tok,
                                           const int* sel_lds, const int* prec_lds, const OneArgs* one, int n_wg, unsigned par) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -1210,7 +1211,7 @@ __device__ __forceinline__ void down_body(const int* rec, const float* h, int n_
     }
   }
   __syncthreads();
-  if (tid < RPW) {
+  if (tid < RPW && (!RAGGED || n0 + tid < a.d_model)) {
     const int n_combo = n_pieces >> psh;
     float acc = 0.0f;
     for (int c = n_combo_s; c < n_combo; c++) acc += part[c * RPW + tid];      // routed slots in slot order
@@ -1221,7 +1222,7 @@ __device__ __forceinline__ void down_body(const int* rec, const float* h, int n_
   }
 }
 
-template <int ACT, int SCB, int FMT, int RPW>      // RPW output rows per work-group
+template <int ACT, int SCB, int FMT, int RPWT>      // output rows per work-group; 0: psh >> 8
 __global__ __launch_bounds__(DEC_NT) void down_kernel(const int* rec, const float* h, int n_combo_s, int n_pieces, int psh, int f_s,
                                                       int f_r, int ks_s, int ks_r, int inv_ks_s, int inv_ks_r, int nsf,
                                                       DecodeArgs a) {
@@ -1231,8 +1232,10 @@ __global__ __launch_bounds__(DEC_NT) void down_kernel(const int* rec, const floa
     rec += tok * (int)(sizeof(RouteRec) / 4);
     h += (size_t)tok * DEC_H_STRIDE(nsf, f_r);
   }
-  down_body<ACT, SCB, FMT, RPW, false>(rec, h, n_combo_s, n_pieces, psh, f_s, f_r, ks_s, ks_r, inv_ks_s, inv_ks_r, nsf, a, dyn,
-                                       (int)blockIdx.x + 8 * (int)blockIdx.z, tok, nullptr, nullptr, nullptr, 0, 0u);
+  const int wg = (int)blockIdx.x + 8 * (int)blockIdx.z, rpw = RPWT ? RPWT : psh >> 8;
+  if (!RPWT && wg * rpw >= a.d_model) return;           // (the grid rounds the work-groups of a token up to eight)
+  down_body<ACT, SCB, FMT, false, RPWT == 0>(rpw, rec, h, n_combo_s, n_pieces, RPWT ? psh : psh & 255, f_s, f_r, ks_s, ks_r, inv_ks_s, inv_ks_r, nsf, a, dyn,
+                                  wg, tok, nullptr, nullptr, nullptr, 0, 0u);
 }
 
 // ---------------------------------------------------------------------------------- single-launch kernel
@@ -1262,7 +1265,7 @@ __global__ __launch_bounds__(DEC_NT, ACT == SMOE_F32 ? 2 : 4) void decode_one_ke
   const int wg = blockIdx.x;
   if (threadIdx.x == 0) grid_set_flag(o.sync, par, wg);
   if (wg >= o.n_dn) return;
-  down_body<ACT, SCB, FMT, DEC_RPW, true>((const int*)a.rec, a.h, o.n_combo_s, o.n_pieces, o.psh, a.f_s, a.f_r, a.ks_s, a.ks_r, a.inv_ks_s,
+  down_body<ACT, SCB, FMT, true, false>(DEC_RPW, (const int*)a.rec, a.h, o.n_combo_s, o.n_pieces, o.psh, a.f_s, a.f_r, a.ks_s, a.ks_r, a.inv_ks_s,
                                           a.inv_ks_r, a.n_shared * a.f_s, a, dyn, wg, 0, sel_lds, prec_lds, &o, n_wg, par);
 }
 
@@ -1273,20 +1276,39 @@ static int ilog2_exact(int v) {
   return (1 << s) == v ? s : -1;
 }
 
-template <int ACT, int SCB, int FMT, int RPW>
+template <int ACT, int SCB, int FMT, bool MULTI>
 static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int n_wg, int T) {
   // down kernel: pieces = combos x parts
   const int n_combo_s = a.n_shared * a.ks_s, n_combo = n_combo_s + a.k * a.ks_r;
-  int psh = RPW == 64 ? 6 : RPW == 32 ? 5 : RPW == 16 ? 4 : 3;      // at most RPW parts of one row each
+  int psh = 3;                                       // at most eight parts
   while (psh > 0 && (n_combo << psh) > DEC_NW) psh--;
+  // Several tokens per launch: a down work-group owns as many output rows (a multiple of its parts and of the four
+  // rows of a batch) as it takes for all tokens' work-groups to be resident at once, two per CU.  With more, smaller
+  // work-groups each one pays its own start-up and rewrites h as digits for fewer rows, and a second, nearly empty
+  // round of them costs as much as the first.  Work-group w of every token runs on XCD w % 8, so it is an XCD's slots that are
+  // shared out.  Widths of 16, 32 and 64 rows have a kernel with the width built in (about 1 % faster).  Step of 5 / 6 / 9 / 10 / 12
+  // tokens (DeepSeek-V2-Lite-shaped layer), both kernels' work-groups shared out so: 40.8 / 45.8 / 59.7 / 64.5 / 74.4 us, against
+  // 48.4 / 51.4 / 80.9 / 82.4 / 88.0 with powers of two (T = 5: 320 work-groups on 512 slots).
+  int RPW = DEC_RPW;
+  if (MULTI) {
+    if (a.d_model & 63) return SMOE_ESHAPE;           // (the entry point's stated limit)
+    const int q = psh == 3 ? 8 : 4, per_tok = 8 * std::max(1, ctx->n_cu / 4 / T);
+    RPW = std::min(256, std::max(DEC_RPW, ((a.d_model + per_tok - 1) / per_tok + q - 1) / q * q));
+    while (RPW > DEC_RPW && n_combo * RPW * 4 > 32 * 1024) RPW -= q;      // (their partial sums stay small beside the h digits)
+  }
   const int n_pieces = n_combo << psh;
   const size_t lds = (size_t)DEC_NW * (StageTraits<ACT>::COMBO_BYTES + 64 * 8) + (size_t)n_combo * RPW * 4;
   if (lds > 160u * 1024u) return SMOE_ESIZE;
+  // a built-in width only where it divides the rows into a multiple of eight work-groups: those kernels check nothing
+  const bool built_in = RPW == DEC_RPW || ((RPW == 16 || RPW == 32 || RPW == 64) && a.d_model % (8 * RPW) == 0);
+  const int width = built_in ? RPW : 0;
+  auto down = width == DEC_RPW ? &down_kernel<ACT, SCB, FMT, DEC_RPW> : width == 16 ? &down_kernel<ACT, SCB, FMT, 16>
+              : width == 32 ? &down_kernel<ACT, SCB, FMT, 32> : width == 64 ? &down_kernel<ACT, SCB, FMT, 64> : &down_kernel<ACT, SCB, FMT, 0>;
   if (lds > 64u * 1024u) {       // beyond the default per-work-group limit: ask for the larger carve-out
     // (kept per context, that is per device: the attribute belongs to the function on the current device)
-    size_t& granted = ctx->down_lds_granted[((ACT * 2 + SCB) * 3 + FMT) * 4 + (RPW == 16) + 2 * (RPW == 32) + 3 * (RPW == 64)];
+    size_t& granted = ctx->down_lds_granted[((ACT * 2 + SCB) * 3 + FMT) * 5 + (width == 16 ? 1 : width == 32 ? 2 : width == 64 ? 3 : width == 0 ? 4 : 0)];
     if (lds > granted) {
-      if (hipFuncSetAttribute((const void*)down_kernel<ACT, SCB, FMT, RPW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+      if (hipFuncSetAttribute((const void*)down, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
         (void)hipGetLastError();
         return SMOE_ESIZE;
       }
@@ -1294,10 +1316,9 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
     }
   }
   std::vector<hipEvent_t>* evs = (ctx->timing && ctx->timing_events) ? (std::vector<hipEvent_t>*)ctx->timing_events : nullptr;
-  const int n_dn = a.d_model / RPW;
-  if (T > 1 && ((n_wg & 7) || (n_dn & 7))) return SMOE_ESHAPE;      // the multi-token grid is (8, T, n / 8)
+  const int n_dn = MULTI ? ((a.d_model + RPW - 1) / RPW + 7) & ~7 : a.d_model / RPW;      // the multi-token grid is (8, T, n / 8)
   const dim3 g1 = T > 1 ? dim3(8, T, n_wg / 8) : dim3(n_wg), g2 = T > 1 ? dim3(8, T, n_dn / 8) : dim3(n_dn), blk(DEC_NT);
-  const int n_se = a.n_shared * a.cap_s;
+  const int n_se = a.n_shared * a.cap_s, psh_arg = built_in ? psh : psh | RPW << 8;
   const bool wide = a.d_model > 2048;                 // rows of more than 64 chunks: the k-sliced gate/up kernel
   const int* recw = (const int*)a.rec;
   const int nsf = a.n_shared * a.f_s;
@@ -1305,7 +1326,7 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
   // chunks, 8 output rows per down work-group, no more down work-groups than gate/up work-groups, the
   // context's own workspace (its hand-over words were cleared when the mode was switched on), and all
   // work-groups resident at once
-  if (ctx->one_launch && T == 1 && !wide && RPW == DEC_RPW && n_dn <= n_wg && n_wg <= ONE_MAX_WG && !evs && (uint8_t*)a.rec == ctx->ws + WS_REC_OFF) {
+  if (!MULTI && ctx->one_launch && !wide && n_dn <= n_wg && n_wg <= ONE_MAX_WG && !evs && (uint8_t*)a.rec == ctx->ws + WS_REC_OFF) {
     const size_t lds1 = lds;
     int& per_cu = ctx->one_blocks_per_cu[((ACT * 2 + SCB) * 3 + FMT)];
     size_t& lds_seen = ctx->one_lds_seen[((ACT * 2 + SCB) * 3 + FMT)];
@@ -1348,8 +1369,8 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
     else
       hipExtLaunchKernelGGL((gateup_kernel<ACT, SCB, FMT>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
                             in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
-    hipExtLaunchKernelGGL((down_kernel<ACT, SCB, FMT, RPW>), g2, blk, (unsigned)lds, ctx->stream, ev[2], ev[3], 0, recw, (const float*)a.h,
-                          n_combo_s, n_pieces, psh, a.f_s, a.f_r, a.ks_s, a.ks_r, a.inv_ks_s, a.inv_ks_r, nsf, a);
+    hipExtLaunchKernelGGL(down, g2, blk, (unsigned)lds, ctx->stream, ev[2], ev[3], 0, recw, (const float*)a.h,
+                          n_combo_s, n_pieces, psh_arg, a.f_s, a.f_r, a.ks_s, a.ks_r, a.inv_ks_s, a.inv_ks_r, nsf, a);
   } else {
     if (wide && a.d_model <= 4096)
       gateup_wide_kernel<ACT, SCB, FMT, 2><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route, a.d_model,
@@ -1360,7 +1381,7 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
     else
       gateup_kernel<ACT, SCB, FMT><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route, a.d_model, n_wg, n_se,
                                                            a);
-    down_kernel<ACT, SCB, FMT, RPW><<<g2, blk, lds, ctx->stream>>>(recw, (const float*)a.h, n_combo_s, n_pieces, psh, a.f_s, a.f_r, a.ks_s,
+    down<<<g2, blk, lds, ctx->stream>>>(recw, (const float*)a.h, n_combo_s, n_pieces, psh_arg, a.f_s, a.f_r, a.ks_s,
                                                          a.ks_r, a.inv_ks_s, a.inv_ks_r, nsf, a);
   }
   HIPCHK(ctx, hipGetLastError());
@@ -1410,10 +1431,8 @@ static int launch_decode(smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank
   // 15.9 with one 16-wave work-group per CU and 16.3 - 17.5 with three, five, six or eight halves);
   // several tokens share them, and the work-groups of different tokens run side by side on a CU.
   int wg_cap = 2 * ctx->n_cu;
-  if (T > 1) {      // about two per CU over all tokens (measured at 2 .. 16 tokens: better than four or eight per CU)
-    wg_cap = ctx->n_cu;
-    while (wg_cap > 8 && wg_cap * T > 2 * ctx->n_cu) wg_cap >>= 1;
-  }
+  // (several tokens: two per CU over all of them, all resident at once, an XCD's slots shared out evenly: see the down split)
+  if (T > 1) wg_cap = 8 * std::max(1, ctx->n_cu / 4 / T);
   n_wg = n_wg < 1 ? 1 : (n_wg > wg_cap ? wg_cap : n_wg);
   if (T > 1) n_wg = n_wg < 8 ? 8 : (n_wg & ~7);            // the multi-token grid is (8, T, n_wg / 8)
   a.cap_r = a.f_r ? (a.f_r + n_wg - 1) / n_wg : 1;
@@ -1434,11 +1453,7 @@ static int launch_decode(smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank
   const int scb = routed ? routed->dev.sc_bf16 : shared->dev.sc_bf16;
   if (routed && shared && routed->dev.sc_bf16 != shared->dev.sc_bf16) return SMOE_ENOTIMPL;   // one scale dtype per layer
   const int bits = routed ? routed->dev.bits : shared->dev.bits;
-  // Several tokens per launch: a down work-group owns 8 * 2^n output rows, so that again about two
-  // work-groups per CU cover all tokens (8 rows up to 2 tokens, 16 up to 4, 32 up to 8, 64 beyond): with
-  // more, smaller work-groups each one pays its own start-up and rewrites h as digits for fewer rows.
-  const bool rows16 = T >= 3 && d_model % 128 == 0, rows32 = T >= 6 && d_model % 256 == 0, rows64 = T >= 12 && d_model % 512 == 0;
-#define DEC_LAUNCH(A, S, F) (rows64 ? launch_decode_t<A, S, F, 64>(ctx, in, a, n_wg, T) : rows32 ? launch_decode_t<A, S, F, 32>(ctx, in, a, n_wg, T) : rows16 ? launch_decode_t<A, S, F, 16>(ctx, in, a, n_wg, T) : launch_decode_t<A, S, F, DEC_RPW>(ctx, in, a, n_wg, T))
+#define DEC_LAUNCH(A, S, F) (T > 1 ? launch_decode_t<A, S, F, true>(ctx, in, a, n_wg, T) : launch_decode_t<A, S, F, false>(ctx, in, a, n_wg, T))
   if (bits == 2) {
     if (act_dtype == SMOE_F32) return scb ? DEC_LAUNCH(SMOE_F32, 1, 1) : DEC_LAUNCH(SMOE_F32, 0, 1);
     return scb ? DEC_LAUNCH(SMOE_BF16, 1, 1) : DEC_LAUNCH(SMOE_BF16, 0, 1);

@@ -354,6 +354,31 @@ def test_multi_token_layer(ctx, T, dt):
                                        C.c_void_p(y.data_ptr()), None, None, None) == -1
 
 
+@pytest.mark.parametrize("T,d,k,n_sh,dt", [(3, 2048, 3, 1, "bf16"),      # 16 rows per down work-group
+                                           (5, 1984, 8, 0, "bf16"),      # 24, the last one with 16
+                                           (5, 2048, 1, 0, "f32"),       # 24 in eight parts of three
+                                           (9, 2048, 7, 1, "bf16"),      # 40 rows
+                                           (11, 1920, 6, 2, "bf16"),     # 48
+                                           (4, 1984, 6, 1, "bf16"),      # 16, but 124 work-groups are no multiple of eight
+                                           (13, 3968, 4, 0, "bf16"),     # wider than the built-in widths, wide gate/up rows
+                                           (16, 64, 2, 1, "bf16")])      # fewer rows than work-groups
+def test_multi_token_down_widths(ctx, T, d, k, n_sh, dt):
+    # the output rows of a down work-group follow the number of tokens: every token as from its own call, bit for bit
+    say("multi-token widths", T, d, k, n_sh, dt)
+    shp = synth.LayerShape(d, 12, 96, k, 32, n_shared=n_sh, shared_d_ff=160 if n_sh else 0, act=dt)
+    pair = LayerPair(ctx, shp, seed=29)
+    x = synth.activations(29, T, d, dt).cuda()
+    z = synth.normal_logits(29, T, 12).cuda()
+    mask = dev(synth.bernoulli_masks(29, 1, 12)[0])
+    buf = torch.full((T + 2, d), 77.0, dtype=x.dtype, device="cuda:0")      # a row of guard values on either side
+    y = buf[1:T + 1]
+    B.smoe_decode_layer_multi(ctx, pair.routed, pair.shared, x, k, z, slice_mask=mask, add_residual=True, y=y)
+    for t in range(T):
+        y1 = B.smoe_decode_layer(ctx, pair.routed, pair.shared, x[t].clone(), k, logits=z[t].clone(), slice_mask=mask, add_residual=True)
+        assert torch.equal(y1, y[t]), t
+    assert bool((buf[0] == 77.0).all()) and bool((buf[T + 1] == 77.0).all())
+
+
 @pytest.mark.parametrize("nest", [(4, 2), (6, 3)])
 @pytest.mark.parametrize("dt,G", [("bf16", 128), ("bf16", 32), ("f32", 64)])
 def test_lower_nest_layer(ctx, dt, G, nest):
