@@ -56,6 +56,21 @@ EXPORTS = [
 ]
 
 
+# Argument types of the calls a decode or prefill loop makes (p pointer or handle, i int, f float, z size_t): with
+# them ctypes converts plain numbers and addresses itself, which costs a third of building an object per argument (a
+# one-token step of a tiny layer is as long as its host work).
+_SIGNATURES = {
+    "smoe_quantize_slice": "ppiippp",
+    "smoe_route": "piiiippippifppp",
+    "smoe_expert_ffn": "ppppiipppfpipp",
+    "smoe_decode_layer": "ppppiipppifpfpipppp",
+    "smoe_decode_layer_static": "ppppiipppifpfpipppp",
+    "smoe_decode_layer_multi": "pppipiippifpfpipppp",
+    "smoe_prefill_histogram": "pppipiippifpipzpppp",
+}
+_CT = {"p": C.c_void_p, "i": C.c_int, "f": C.c_float, "z": C.c_size_t}
+
+
 def lib() -> C.CDLL:
     global _lib
     if _lib is None:
@@ -67,6 +82,8 @@ def lib() -> C.CDLL:
         _lib.smoe_strerror.argtypes = [C.c_int]
         for name in EXPORTS:
             getattr(_lib, name)            # fail loudly on a missing symbol
+        for name, sig in _SIGNATURES.items():
+            getattr(_lib, name).argtypes = [_CT[c] for c in sig]
     return _lib
 
 
@@ -80,9 +97,9 @@ def _chk(rc: int, what: str, ctx=None):
 
 def _p(t: Optional[torch.Tensor]):
     if t is None:
-        return C.c_void_p(0)
+        return None
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous CUDA/HIP tensors"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def smoe_workspace_bytes(tokens: int, k: int, d_ff: int, n_shared: int = 0, shared_d_ff: int = 0) -> int:
@@ -178,7 +195,7 @@ def smoe_quantize_slice(ctx: Ctx, bank: Bank, e0: int, w_gate: torch.Tensor, w_u
     assert tuple(w_gate.shape) == (n, f, d) and tuple(w_up.shape) == (n, f, d) and tuple(w_down.shape) == (n, d, f)
     want = torch.float32 if bank.desc.w_dtype == F32 else torch.bfloat16
     assert w_gate.dtype == want and w_up.dtype == want and w_down.dtype == want
-    _chk(lib().smoe_quantize_slice(ctx.h, bank.h, C.c_int(e0), C.c_int(n), _p(w_gate), _p(w_up), _p(w_down)),
+    _chk(lib().smoe_quantize_slice(ctx.h, bank.h, e0, n, _p(w_gate), _p(w_up), _p(w_down)),
          "smoe_quantize_slice", ctx.h)
 
 
@@ -210,8 +227,8 @@ def smoe_route(ctx: Ctx, k: int, logits: Optional[torch.Tensor] = None, x: Optio
     idx = torch.empty((T, k), dtype=torch.int32, device=dev)
     w = torch.empty((T, k), dtype=torch.float32, device=dev)
     zout = torch.empty((T, E), dtype=torch.float32, device=dev) if want_logits else None
-    _chk(lib().smoe_route(ctx.h, C.c_int(T), C.c_int(E), C.c_int(k), C.c_int(d), _p(logits), _p(x), C.c_int(act),
-                          _p(w_router), _p(bias), C.c_int(int(norm_topk)), C.c_float(routed_scale), _p(zout),
+    _chk(lib().smoe_route(ctx.h, T, E, k, d, _p(logits), _p(x), act,
+                          _p(w_router), _p(bias), int(norm_topk), routed_scale, _p(zout),
                           _p(idx), _p(w)), "smoe_route", ctx.h)
     return (idx, w, zout) if want_logits else (idx, w)
 
@@ -222,8 +239,8 @@ def smoe_expert_ffn(ctx: Ctx, routed: Optional[Bank], shared: Optional[Bank], x:
     if y is None:
         y = torch.empty_like(x)
     _chk(lib().smoe_expert_ffn(ctx.h, routed.h if routed else None, shared.h if shared else None, _p(x),
-                               C.c_int(_DT[x.dtype]), C.c_int(k), _p(idx), _p(w), _p(slice_mask),
-                               C.c_float(tau_head), _p(shared_gate_w), C.c_int(int(add_residual)), _p(y),
+                               _DT[x.dtype], k, _p(idx), _p(w), _p(slice_mask),
+                               tau_head, _p(shared_gate_w), int(add_residual), _p(y),
                                _p(prec_out)), "smoe_expert_ffn", ctx.h)
     return y
 
@@ -234,10 +251,10 @@ def smoe_decode_layer(ctx: Ctx, routed: Bank, shared: Optional[Bank], x: torch.T
                       w_out=None, prec_out=None):
     if y is None:
         y = torch.empty_like(x)
-    _chk(lib().smoe_decode_layer(ctx.h, routed.h, shared.h if shared else None, _p(x), C.c_int(_DT[x.dtype]),
-                                 C.c_int(k), _p(logits), _p(w_router), _p(bias), C.c_int(int(norm_topk)),
-                                 C.c_float(routed_scale), _p(slice_mask), C.c_float(tau_head), _p(shared_gate_w),
-                                 C.c_int(int(add_residual)), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
+    _chk(lib().smoe_decode_layer(ctx.h, routed.h, shared.h if shared else None, _p(x), _DT[x.dtype],
+                                 k, _p(logits), _p(w_router), _p(bias), int(norm_topk),
+                                 routed_scale, _p(slice_mask), tau_head, _p(shared_gate_w),
+                                 int(add_residual), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
          "smoe_decode_layer", ctx.h)
     return y
 
@@ -253,10 +270,10 @@ def smoe_decode_layer_static(ctx: Ctx, routed: Bank, shared: Optional[Bank], x: 
                              slice_mask=None, tau_head: float = 0.0, shared_gate_w=None, add_residual: bool = False,
                              idx_out=None, w_out=None, prec_out=None):
     """smoe_decode_layer over the library's static workspace; the caller passes every buffer (y included)."""
-    _chk(lib().smoe_decode_layer_static(ctx.h, routed.h, shared.h if shared else None, _p(x), C.c_int(_DT[x.dtype]),
-                                        C.c_int(k), _p(logits), _p(w_router), _p(bias), C.c_int(int(norm_topk)),
-                                        C.c_float(routed_scale), _p(slice_mask), C.c_float(tau_head), _p(shared_gate_w),
-                                        C.c_int(int(add_residual)), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
+    _chk(lib().smoe_decode_layer_static(ctx.h, routed.h, shared.h if shared else None, _p(x), _DT[x.dtype],
+                                        k, _p(logits), _p(w_router), _p(bias), int(norm_topk),
+                                        routed_scale, _p(slice_mask), tau_head, _p(shared_gate_w),
+                                        int(add_residual), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
          "smoe_decode_layer_static", ctx.h)
     return y
 
@@ -268,10 +285,10 @@ def smoe_decode_layer_multi(ctx: Ctx, routed: Bank, shared: Optional[Bank], x: t
     T = x.shape[0]
     if y is None:
         y = torch.empty_like(x)
-    _chk(lib().smoe_decode_layer_multi(ctx.h, routed.h, shared.h if shared else None, C.c_int(T), _p(x),
-                                       C.c_int(_DT[x.dtype]), C.c_int(k), _p(logits), _p(bias), C.c_int(int(norm_topk)),
-                                       C.c_float(routed_scale), _p(slice_mask), C.c_float(tau_head), _p(shared_gate_w),
-                                       C.c_int(int(add_residual)), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
+    _chk(lib().smoe_decode_layer_multi(ctx.h, routed.h, shared.h if shared else None, T, _p(x),
+                                       _DT[x.dtype], k, _p(logits), _p(bias), int(norm_topk),
+                                       routed_scale, _p(slice_mask), tau_head, _p(shared_gate_w),
+                                       int(add_residual), _p(y), _p(idx_out), _p(w_out), _p(prec_out)),
          "smoe_decode_layer_multi", ctx.h)
     return y
 
@@ -296,10 +313,10 @@ def smoe_prefill_histogram(ctx: Ctx, routed: Bank, shared: Optional[Bank], x: to
     idx = torch.empty((T, k), dtype=torch.int32, device=dev)
     w = torch.empty((T, k), dtype=torch.float32, device=dev)
     hist = torch.empty((E,), dtype=torch.int32, device=dev)     # bit pattern of uint32 counts
-    _chk(lib().smoe_prefill_histogram(ctx.h, routed.h, shared.h if shared else None, C.c_int(T), _p(x),
-                                      C.c_int(_DT[x.dtype]), C.c_int(k), _p(logits), _p(w_router),
-                                      C.c_int(int(norm_topk)), C.c_float(routed_scale), _p(shared_gate_w),
-                                      C.c_int(int(add_residual)), _p(scratch), C.c_size_t(scratch.numel()), _p(y),
+    _chk(lib().smoe_prefill_histogram(ctx.h, routed.h, shared.h if shared else None, T, _p(x),
+                                      _DT[x.dtype], k, _p(logits), _p(w_router),
+                                      int(norm_topk), routed_scale, _p(shared_gate_w),
+                                      int(add_residual), _p(scratch), scratch.numel(), _p(y),
                                       _p(idx), _p(w), _p(hist)), "smoe_prefill_histogram", ctx.h)
     return y, idx, w, hist
 
