@@ -159,7 +159,8 @@ struct GemmArgs {
   int accumulate;           // MODE 1: add to O instead of overwriting it
 };
 // one launch serves two sets of experts: work-groups below nb0 belong to g[0] (nb0 is a multiple of 8)
-struct GemmPair { GemmArgs g[2]; int nb0; };
+// (zp_at, wave_lds: where a wave's zero-points start in its LDS area, and the area's size, by the smallest group of the two)
+struct GemmPair { GemmArgs g[2]; int nb0, zp_at, wave_lds; };
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   f32x2 v = {a, b};
@@ -190,11 +191,21 @@ __device__ __forceinline__ void dma1(u32x4 rsrc, uint32_t voff, uint32_t soff, u
 }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// LDS of a GEMM work-group.  A step of a short tile (32 or 64 rows) is over before its token rows have come from L2: four
+// buffers let those be sent for three steps ahead, without costing a resident work-group (three per CU with 32 rows, two
+// with 64): 173 tokens through 64 experts 173.5 -> 166.6 us per layer.  Taller tiles have room for two.
+// (That third work-group also needs the waves' areas cut to the groups at hand; for taller tiles their size is fixed.)
+template <int SCB, int FMT, int NF> struct PfLds {
+  static constexpr int NBUF = NF <= 2 ? 4 : 2, ROWS = NBUF * 32 * NF * 128, PLANE = FMT == 0 ? 4096 : FMT == 1 ? 2048 : 3072;
+  static constexpr bool FIT = NF <= 2;
+  static constexpr int ZP_AT = 2 * PLANE + (SCB ? 4 : 8) * 128, WAVE = ZP_AT + 8 * 128;      // two planes, scale dwords, zero-points of 32 rows and 256 columns in groups of 32
+};
+
 // One expert's 32 * NF token rows times 128 weight rows, four waves.  A wave owns all the token rows and 32 of
 // the weight rows; it expands its weights to bf16 in registers -- lane (n, h) holds columns 32 h .. 32 h + 31 of one
 // row of a K step (64 columns), and MFMA s of the step contracts columns {8 s ..} and {32 + 8 s ..} on both operands --
 // so every weight is expanded once per tile and LDS carries bf16 only for the token rows.  All memory reaches LDS
-// by direct loads: token rows one K step ahead into two buffers; planes, scales and zero-points 256 columns (a
+// by direct loads: token rows one K step ahead (short tiles three) into as many buffers and one; planes, scales and zero-points 256 columns (a
 // whole 128-byte line of a nibble plane) at a time into an area of the wave's own, fetched while the previous 256
 // columns, by then in registers, are multiplied.
 // Bound: with few rows per expert the weights' bytes; with many the instruction issue of the waves (about 100 vector
@@ -210,9 +221,11 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   constexpr int BM = 32 * NF;
   constexpr int PB32 = FMT == 0 ? 16 : FMT == 1 ? 8 : 12;      // plane bytes of 32 columns
   constexpr int PROW = 8 * PB32, PPR = PROW / 16, NPL = 32 * PROW / 1024;      // of a row and 256 columns; 16-byte pieces of that; loads per plane
-  constexpr int PLANE = 32 * PROW, NSD = SCB ? 4 : 8;          // bytes of a wave's plane area; scale dwords per row and 256 columns
-  constexpr int ZP_AT = 2 * PLANE + NSD * 128, WAVE_LDS = ZP_AT + 8 * 128;     // the wave's area: MSB plane, LSB plane, scales, zero-points
-  __shared__ __align__(1024) uint8_t As[2 * BM * 128 + 4 * WAVE_LDS];      // two K steps of the token rows, 128 bytes per row; the waves' areas
+  constexpr int PLANE = 32 * PROW;                             // bytes of one plane in a wave's area: MSB plane, LSB plane, scales, zero-points
+  typedef PfLds<SCB, FMT, NF> Lds;
+  constexpr int NBUF = Lds::NBUF, AHEAD = NBUF - 1;
+  extern __shared__ __align__(1024) uint8_t As[];              // NBUF K steps of the token rows, 128 bytes per row; the waves' areas
+  const int ZP_AT = Lds::FIT ? pair.zp_at : Lds::ZP_AT;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const bool second = (int)blockIdx.x >= pair.nb0;
   const GemmArgs& a = pair.g[second ? 1 : 0];
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   // (a row holds an even number of scales, so a pair of bf16 scales is one aligned dword)
   const uint32_t s_off = (wrow + n) * (uint32_t)a.w.sng * (SCB ? 2u : 4u) + hh * 4u, z_off = (wrow + n) * (uint32_t)a.w.ng + hh;
   const uint32_t as_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As;
-  const uint32_t wofs = 2 * BM * 128 + (uint32_t)wave * WAVE_LDS;
+  const uint32_t wofs = NBUF * BM * 128 + (uint32_t)wave * (uint32_t)(Lds::FIT ? pair.wave_lds : Lds::WAVE);
   const uint8_t* warea = As + wofs;
   const uint32_t wr = MODE == 0 ? 2 * (n & 15) + (n >> 4) : n;                 // the lane's row of the 32
   const uint32_t p_rd = wr * PROW + (FMT == 0 ? ((uint32_t)hh ^ ((wr >> 1) & 7u)) * 16 : (uint32_t)hh * PB32);
@@ -372,7 +385,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       if (ex) __syncthreads();                          // every wave is done with the LDS rows of the last pass
       const u32x4 ra = pf_rsrc(MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff, a.a_bytes);
       auto load_rows = [&](int t) __attribute__((always_inline)) {
-        const uint32_t lds = as_base + ((t & 1) ? BM * 128u : 0u);
+        const uint32_t lds = as_base + (uint32_t)(t & (NBUF - 1)) * (BM * 128u);
 #pragma unroll
         for (int q = 0; q < F; q++)
           dma16(ra, a_off[MODE == 0 ? q : 0], (uint32_t)t * (PF_BK * 2) + (MODE == 0 ? 0u : (uint32_t)q * 64u * (uint32_t)a.d_ff),
@@ -450,7 +463,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       // token rows of the next one are read and its weights expanded; the schedule deals one read and a fifth (a third, ...)
       // of the expansion to every product, because a wave issues in order and gets less than every second slot of its SIMD.
       auto multiply = [&](auto last_c, int t, bf16x8 bf, const Planes& p, float sc, float c0, const Planes& pn, float scn, float c0n) __attribute__((always_inline)) {
-        const uint8_t* rows = As + ((t & 1) ? BM * 128 : 0);
+        const uint8_t* rows = As + (t & (NBUF - 1)) * (BM * 128);
         bf16x8 af[2][F];
 #pragma unroll
         for (int i = 0; i < F; i++) af[0][i] = *(const bf16x8*)(rows + a_rd + i * 4096);
@@ -478,13 +491,22 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       };
       // The direct loads are the only memory operations of the loop, so the waits count them.  Every wave has its share
       // of the rows of step t in LDS (and, every fourth step, its weights) before the barrier at the top of step t, and
-      // has finished step t - 1, whose buffer the rows of step t + 1 then overwrite.  Loads complete in order: in the step
-      // after the weights were sent for, leaving the last 2 * NPL loads out (planes) means that the rows are there.
+      // has finished step t - 1, whose buffer the rows of step t + AHEAD then overwrite.  Loads complete in order, and
+      // younger than the rows of step t are only those of the next AHEAD - 1 steps and, in the first AHEAD steps after they
+      // were sent for, the next weights (at least 2 * NPL loads): so many may be left out.  Near the end, where there
+      // are fewer, nothing is.
       if (ex) load_weights(ex, 0);
-      load_rows(0);
+#pragma unroll
+      for (int t = 0; t < AHEAD; t++)
+        if (t < nk) load_rows(t);
+      auto arrive = [&](auto left_c, bool all) __attribute__((always_inline)) {
+        if (all) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(decltype(left_c)::value) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      };
+      constexpr int YOUNG = (AHEAD - 1) * F;
       for (int t = 0; t < nk; t += 4) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (t + 1 < nk) load_rows(t + 1);
+        arrive(std::integral_constant<int, YOUNG>(), t + AHEAD - 1 < nk);
+        if (t + AHEAD < nk) load_rows(t + AHEAD);
         Planes p[4];
         float sc[4], c0[4];
 #pragma unroll
@@ -500,9 +522,8 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
         auto next = [&](auto b_c) __attribute__((always_inline)) {
           constexpr int b = decltype(b_c)::value, n1 = b < 3 ? b + 1 : b;
           if (t + b < nk) {
-            if (b == 1 && more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NPL) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (t + b + 1 < nk) load_rows(t + b + 1);
+            arrive(std::integral_constant<int, YOUNG + (b <= AHEAD ? 2 * NPL : 0)>(), more && t + b + AHEAD - 1 < nk);
+            if (t + b + AHEAD < nk) load_rows(t + b + AHEAD);
             bf = multiply(std::integral_constant<bool, b == 3>(), t + b, bf, p[b], sc[b], c0[b], p[n1], sc[n1], c0[n1]);
           }
         };
@@ -608,26 +629,40 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* o, const int3
 // ------------------------------------------------------------------------------- host entry
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-template <int MODE, int NF>
-static void launch_gemm_nf(const GemmPair& g, int sc_bf16, int bits, int grid, hipStream_t st) {
-  if (bits == 2) {
-    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 1, NF><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 1, NF><<<grid, PF_NT, 0, st>>>(g);
-  } else if (bits == 3) {
-    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 2, NF><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 2, NF><<<grid, PF_NT, 0, st>>>(g);
-  } else {
-    if (sc_bf16) grouped_gemm_kernel<MODE, 1, 0, NF><<<grid, PF_NT, 0, st>>>(g);
-    else grouped_gemm_kernel<MODE, 0, 0, NF><<<grid, PF_NT, 0, st>>>(g);
+template <int MODE, int SCB, int FMT, int NF>
+static int launch_gemm_t(smoe_ctx* ctx, GemmPair& g, int grid) {
+  // groups of 256 columns of the set with the smallest groups: two scale dwords / zero-points of 32 rows per 256 bytes
+  int sh = 8;
+  if (g.nb0) sh = std::min(sh, g.g[0].group_shift);
+  if (grid > g.nb0) sh = std::min(sh, g.g[1].group_shift);
+  const int n_grp = 256 >> sh, nsd = SCB ? (n_grp + 1) / 2 : n_grp;
+  typedef PfLds<SCB, FMT, NF> Lds;
+  g.zp_at = 2 * Lds::PLANE + (nsd + 1) / 2 * 256;
+  g.wave_lds = g.zp_at + (n_grp + 1) / 2 * 256;
+  const size_t lds = (size_t)Lds::ROWS + 4 * (size_t)(Lds::FIT ? g.wave_lds : Lds::WAVE);
+  if (lds > 64u * 1024u) {       // beyond the default per-work-group limit: granted once per device
+    size_t& granted = ctx->gemm_lds_granted[((MODE * 2 + SCB) * 3 + FMT) * 4 + (NF == 5 ? 3 : NF - 1)];
+    if (lds > granted) {
+      HIPCHK(ctx, hipFuncSetAttribute((const void*)grouped_gemm_kernel<MODE, SCB, FMT, NF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      granted = lds;
+    }
   }
+  grouped_gemm_kernel<MODE, SCB, FMT, NF><<<grid, PF_NT, lds, ctx->stream>>>(g);
+  return SMOE_OK;
+}
+template <int MODE, int NF>
+static int launch_gemm_nf(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int grid) {
+  if (bits == 2) return sc_bf16 ? launch_gemm_t<MODE, 1, 1, NF>(ctx, g, grid) : launch_gemm_t<MODE, 0, 1, NF>(ctx, g, grid);
+  if (bits == 3) return sc_bf16 ? launch_gemm_t<MODE, 1, 2, NF>(ctx, g, grid) : launch_gemm_t<MODE, 0, 2, NF>(ctx, g, grid);
+  return sc_bf16 ? launch_gemm_t<MODE, 1, 0, NF>(ctx, g, grid) : launch_gemm_t<MODE, 0, 0, NF>(ctx, g, grid);
 }
 // bits = plane bits per code of the bank (4: 8/4 nest, 3: 6/3 nest, 2: 4/2 nest); nf = fragments of the tallest tile
 template <int MODE>
-static void launch_gemm(const GemmPair& g, int sc_bf16, int bits, int nf, int grid, hipStream_t st) {
-  if (nf == 1) launch_gemm_nf<MODE, 1>(g, sc_bf16, bits, grid, st);
-  else if (nf == 2) launch_gemm_nf<MODE, 2>(g, sc_bf16, bits, grid, st);
-  else if (nf == 3) launch_gemm_nf<MODE, 3>(g, sc_bf16, bits, grid, st);
-  else launch_gemm_nf<MODE, 5>(g, sc_bf16, bits, grid, st);
+static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf, int grid) {
+  if (nf == 1) return launch_gemm_nf<MODE, 1>(ctx, g, sc_bf16, bits, grid);
+  if (nf == 2) return launch_gemm_nf<MODE, 2>(ctx, g, sc_bf16, bits, grid);
+  if (nf == 3) return launch_gemm_nf<MODE, 3>(ctx, g, sc_bf16, bits, grid);
+  return launch_gemm_nf<MODE, 5>(ctx, g, sc_bf16, bits, grid);
 }
 // Tile height for experts of `rows` rows on average: one tile for nearly every expert (mean plus one and a half
 // standard deviations of even routing) if five fragments can do that, else the tallest tile.
@@ -723,8 +758,8 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
   const int gu_grid = grid_of(mt, gu.g[1].n_col_tiles), dn_grid = grid_of(mt, dn.g[1].n_col_tiles);
   float* o_s = nullptr;
   if (!shared) {
-    launch_gemm<0>(gu, scb, bits, nf, gu_grid, st);
-    launch_gemm<1>(dn, scb, bits, nf, dn_grid, st);
+    { const int rc = launch_gemm<0>(ctx, gu, scb, bits, nf, gu_grid); if (rc) return rc; }
+    { const int rc = launch_gemm<1>(ctx, dn, scb, bits, nf, dn_grid); if (rc) return rc; }
   } else {
     // the shared experts see every token: dense GEMMs over the token rows in their own order, their
     // gate-weighted outputs summed in O_s
@@ -759,22 +794,22 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
       const int gg = grid_of(rt * q.n_dense, qg.n_col_tiles), gd = grid_of(rt, qd.n_col_tiles);
       if (j0) {
         gu.g[0] = qg; gu.nb0 = gg;
-        launch_gemm<0>(gu, scb, bits, nf, gg + gu_grid, st);
+        { const int rc = launch_gemm<0>(ctx, gu, scb, bits, nf, gg + gu_grid); if (rc) return rc; }
       } else {
         GemmPair one{};
         one.g[0] = qg; one.nb0 = gg;
-        launch_gemm<0>(one, shared->dev.sc_bf16, shared->dev.bits, nq, gg, st);
+        { const int rc = launch_gemm<0>(ctx, one, shared->dev.sc_bf16, shared->dev.bits, nq, gg); if (rc) return rc; }
       }
       if (j1) {
         dn.g[0] = qd; dn.nb0 = gd;
       } else {
         GemmPair one{};
         one.g[0] = qd; one.nb0 = gd;
-        launch_gemm<1>(one, shared->dev.sc_bf16, shared->dev.bits, nq, gd, st);
+        { const int rc = launch_gemm<1>(ctx, one, shared->dev.sc_bf16, shared->dev.bits, nq, gd); if (rc) return rc; }
       }
     }
-    if (!join) launch_gemm<0>(gu, scb, bits, nf, gu_grid, st);
-    launch_gemm<1>(dn, scb, bits, nf, dn.nb0 + dn_grid, st);
+    if (!join) { const int rc = launch_gemm<0>(ctx, gu, scb, bits, nf, gu_grid); if (rc) return rc; }
+    { const int rc = launch_gemm<1>(ctx, dn, scb, bits, nf, dn.nb0 + dn_grid); if (rc) return rc; }
   }
   combine_kernel<<<T, 256, 0, st>>>(o, pos, o_s, (const uint16_t*)x_dev, (uint16_t*)y_dev, k, d, add_residual);
   HIPCHK(ctx, hipGetLastError());
