@@ -772,9 +772,13 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
     const bool same = shared->dev.sc_bf16 == scb && shared->dev.bits == bits;
     // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
     // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both
-    // want the same tile height or there are too few tokens for the taller one to matter.
+    // want the same tile height, or if at the routed experts' (lower) height there is little to expand: a dense tile
+    // expands its weights again, 600 million of them in about 55 us over the chip, which is what launches of their own lose to
+    // their empty ends.  64 experts of d_ff 512, one shared of 1024, d_model 1024, 500 tokens: 101 -> 72 us; 96 experts, two
+    // shared of 3840, d_model 2560, 500 tokens, all joined, would be 482 -> 515.
     const int nfs = pick_nf((double)T);
-    const bool join = same && (nf == nfs || T <= 8 * bm);
+    const double again = 3.0 * d * f_s * shared->desc.n_experts * ((T + bm - 1) / bm);
+    const bool join = same && (nf == nfs || T <= 8 * bm || (T <= 24 * bm && again <= 600e6));
     // H of one shared expert has its own place.  That of others waits in Y, which nothing else writes before the last
     // kernel, if Y is not X and they fit there; else in the rows of O until the routed experts' down GEMM
     // writes those: then the shared experts' down GEMM comes before it, and as many experts as fit are worked out together.
