@@ -233,6 +233,8 @@ int smoe_prefill_bytes(int T, int E, int k, int d_model, int d_ff, int shared_d_
  * add_residual), gamma[t] = sigmoid(shared_gate_w . x[t]) or 1 without a gate vector (act dtype
  * [d_model]); the shared experts see every token and run as dense GEMMs.
  * x_dev, y_dev: act_dtype [T, d_model] (bf16 only); idx_dev int32 [T,k]; w_dev fp32 [T,k].
+ * y_dev may be x_dev (the call then works in place); apart from that it must not overlap x_dev, and it
+ * holds intermediate values until the call's work on the stream is done.
  * d_model and every d_ff must be multiples of 64, groups powers of two >= 32. */
 int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank* shared, int T,
                            const void* x_dev, int act_dtype, int k, const float* logits_dev,

@@ -24,8 +24,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #define PF_BN 128          // weight rows per work-group tile: 32 per wave
 #define PF_BK 64
 #define PF_NT 256          // threads per work-group
-#define PF_MAX_NF 5        // 32-row fragments of the tallest tile
-#define PF_MIN_BM 32
 
 // ------------------------------------------------------------------------------- small kernels
 #define GR_THREADS 1024
