@@ -553,7 +553,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       for (int r = 0; r < 8; r++) {
         const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][r]), __float_as_uint(acc[i][r + 8]), false, false);
         const float g = __uint_as_float(sw[0]), u = __uint_as_float(sw[1]);
-        const float hv = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+        const float hv = g / (1.0f + __expf(-g)) * u;      // (a true division: the reciprocal unit flushes what is below 2^-126, gates from -87.4 down)
         *(uint16_t*)(As + (i * 32 + 8 * (r >> 2) + (r & 3) + rb) * HLD + col * 2) = (uint16_t)pack_bf16(hv, hv);
       }
     }

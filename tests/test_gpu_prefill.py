@@ -183,6 +183,36 @@ def test_prefill_empty_expert_and_given_logits(ctx):
     assert O.max_abs_rel(t2np(y), yref) <= TOL
 
 
+def _layer_of(ctx, mats, G, nest=(8, 4)):
+    """One-expert bank and oracle expert from dense bf16 matrices (gate [f, d], up [f, d], down [d, f])."""
+    f, d = mats[0].shape
+    bank = B.Bank(ctx, 1, d, f, G, "bf16", "bf16", *nest)
+    B.smoe_quantize_slice(ctx, bank, 0, *(m.cuda()[None].contiguous() for m in mats))
+    return bank, O.quantize_expert(*(t2np(m) for m in mats), G, *nest, scale_dtype="bf16")
+
+
+def test_prefill_swiglu_of_gates_far_below_zero(ctx):
+    # gates of -87.5 .. -88.5: 1 + exp(-g) is a normal number, its reciprocal is not (below 2^-126), g over it is one again;
+    # up values of 2^119 bring h back to about 1.  Scales are exact powers of two (0.5 and 2^112), so gates and ups are exact.
+    T, d, f, G = 40, 64, 128, 64
+    say("prefill, gates far below zero")
+    g = torch.Generator().manual_seed(71)
+    v = 87.5 + 0.5 * torch.randint(0, 3, (f,), generator=g)
+    wg, wu = torch.zeros(f, d), torch.zeros(f, d)
+    wg[:, 0], wg[:, 1] = -v, 127.5 - v
+    wu[:, 0], wu[:, 1] = 2.0 ** 119, 255.0 * 2.0 ** 112
+    wd = torch.randn(d, f, generator=g) * 0.02
+    bank, ref = _layer_of(ctx, [m.bfloat16() for m in (wg, wu, wd)], G)
+    x = torch.zeros(T, d, dtype=torch.bfloat16)
+    x[:, 0] = 1.0
+    y, idx, w, _ = B.smoe_prefill_histogram(ctx, bank, None, x.cuda(), 1, logits=torch.zeros(T, 1).cuda())
+    yref = O.prefill_layer(t2np(x).astype(np.float64), [ref], idx.cpu().numpy(), w.cpu().numpy().astype(np.float64))
+    assert np.abs(yref).max() > 1e-3
+    yg = t2np(y)
+    for t in range(T):
+        assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
 def test_prefill_qwen_layer_full_size_sampled_tokens(ctx):
     """2048 tokens through one Qwen1.5-MoE-shaped layer (60 experts of 2048x1408, top-4, all
     high-bit): every index and the histogram exactly, sampled token rows against the oracle."""
