@@ -376,9 +376,61 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   float my_wt = 0.0f;
   if (MODE == 1 && tid < m_cnt) my_wt = a.wgt[a.dense_rows ? m0 + tid : a.rows[row0 + m0 + tid]];
 
+  // codes of columns 8 s .. 8 s + 7 of the lane's 32 -> bf16 scale (q - zp).  With bf16 scales the K loop takes the codes as 1024 + q
+  // (BIASED) and c0 = -(1024 + zp) scale; otherwise c0 = -zp scale.
+  constexpr bool BIASED = SCB != 0;
+  auto expand = [&](auto biased_c, const PlaneV& m, const PlaneV& l, int s, float scale, float c0) __attribute__((always_inline)) {
+    uint32_t qe, qo;                          // codes of the even / odd columns, one per byte
+    if constexpr (FMT == 0) {
+      // (the planes hold n ^ 8 per nibble: taken back below)
+      const uint32_t wm = m[s], wl = l[s];
+      qe = ((wm << 4) & 0xF0F0F0F0u) | (wl & 0x0F0F0F0Fu);
+      qo = (wm & 0xF0F0F0F0u) | ((wl >> 4) & 0x0F0F0F0Fu);
+    } else if constexpr (FMT == 2) {
+      // column 8s + i: two low bits in word s >> 1 at bits 4i + 2(s & 1), third bit in word 2 at bit
+      // 4i + s; one value per nibble first, then code = 8 msb + lsb, one per byte
+      auto nib = [&](const PlaneV& w) {
+        const uint32_t lo = (w[s >> 1] >> (2 * (s & 1))) & 0x33333333u;
+        const uint32_t hi = w[2] & (0x11111111u << s);
+        return lo | (s < 2 ? hi << (2 - s) : hi >> (s - 2));
+      };
+      const uint32_t nm = nib(m), nl = nib(l);
+      qe = ((nm & 0x0F0F0F0Fu) << 3) | (nl & 0x0F0F0F0Fu);
+      qo = (((nm >> 4) & 0x0F0F0F0Fu) << 3) | ((nl >> 4) & 0x0F0F0F0Fu);
+    } else {
+      // sixteen 2-bit codes per plane word, column c in bits 2c, 2c+1: spread half a word to one
+      // code per nibble, then code = 4 msb + lsb
+      auto spread = [](uint32_t v) {
+        v = (v | (v << 8)) & 0x00FF00FFu;
+        v = (v | (v << 4)) & 0x0F0F0F0Fu;
+        return (v | (v << 2)) & 0x33333333u;
+      };
+      const uint32_t hm = (m[s >> 1] >> (16 * (s & 1))) & 0xFFFFu, hl = (l[s >> 1] >> (16 * (s & 1))) & 0xFFFFu;
+      const uint32_t qn = (spread(hm) << 2) | spread(hl);
+      qe = qn & 0x0F0F0F0Fu;
+      qo = (qn >> 4) & 0x0F0F0F0Fu;
+    }
+    u32x4 out;
+#pragma unroll
+    for (int b = 0; b < 4; b++) {
+      if constexpr (decltype(biased_c)::value) {
+        // the codes of two columns as the halves 1024 + q (exact in fp16), which one mixed-precision FMA each turns
+        // into s (1024 + q) - s (1024 + zp); a bf16 scale times 11 bits is exact in fp32, so this is s (q - zp) rounded once
+        const f16x2 q2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(qo, qe, 0x0C000C00u | ((4u + b) << 16) | b) ^ (FMT == 0 ? 0x64886488u : 0x64006400u));
+        out[b] = pack_bf16(fmaf((float)q2[0], scale, c0), fmaf((float)q2[1], scale, c0));
+      } else {
+        const uint32_t f = FMT == 0 ? 0x88888888u : 0u;
+        const float we = fmaf((float)(((qe ^ f) >> (8 * b)) & 0xFF), scale, c0);
+        const float wo = fmaf((float)(((qo ^ f) >> (8 * b)) & 0xFF), scale, c0);
+        out[b] = pack_bf16(we, wo);
+      }
+    }
+    return __builtin_bit_cast(bf16x8, out);
+  };
+  const int n_pass = MODE == 1 && a.dense_rows ? a.n_dense : 1;
+  const std::integral_constant<bool, BIASED> biased{};
   auto kloop = [&](auto nf_c) __attribute__((always_inline)) {
     constexpr int F = decltype(nf_c)::value;
-    const int n_pass = MODE == 1 && a.dense_rows ? a.n_dense : 1;
     for (int ex = 0; ex < n_pass; ex++) {
       if (ex) __syncthreads();                          // every wave is done with the LDS rows of the last pass
       const u32x4 ra = pf_rsrc(MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff, a.a_bytes);
@@ -406,56 +458,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
         const uint32_t sw = *(const uint32_t*)(warea + 2 * PLANE + (SCB ? gl >> 1 : gl) * 128u + wr * 4);
         const uint32_t zp = *(const uint32_t*)(warea + ZP_AT + gl * 128u + wr * 4) & 0xFFu;
         sc = SCB ? __uint_as_float((g & 1u) ? sw & 0xFFFF0000u : sw << 16) : __uint_as_float(sw);
-        c0 = -(float)((SCB ? 1024u : 0u) + zp) * sc;
-      };
-      // codes of columns 8 s .. 8 s + 7 of the lane's 32 -> bf16 s (q - zp)
-      auto expand = [&](const PlaneV& m, const PlaneV& l, int s, float scale, float c0) __attribute__((always_inline)) {
-        uint32_t qe, qo;                          // codes of the even / odd columns, one per byte
-        if constexpr (FMT == 0) {
-          // (the planes hold n ^ 8 per nibble: taken back below)
-          const uint32_t wm = m[s], wl = l[s];
-          qe = ((wm << 4) & 0xF0F0F0F0u) | (wl & 0x0F0F0F0Fu);
-          qo = (wm & 0xF0F0F0F0u) | ((wl >> 4) & 0x0F0F0F0Fu);
-        } else if constexpr (FMT == 2) {
-          // column 8s + i: two low bits in word s >> 1 at bits 4i + 2(s & 1), third bit in word 2 at bit
-          // 4i + s; one value per nibble first, then code = 8 msb + lsb, one per byte
-          auto nib = [&](const PlaneV& w) {
-            const uint32_t lo = (w[s >> 1] >> (2 * (s & 1))) & 0x33333333u;
-            const uint32_t hi = w[2] & (0x11111111u << s);
-            return lo | (s < 2 ? hi << (2 - s) : hi >> (s - 2));
-          };
-          const uint32_t nm = nib(m), nl = nib(l);
-          qe = ((nm & 0x0F0F0F0Fu) << 3) | (nl & 0x0F0F0F0Fu);
-          qo = (((nm >> 4) & 0x0F0F0F0Fu) << 3) | ((nl >> 4) & 0x0F0F0F0Fu);
-        } else {
-          // sixteen 2-bit codes per plane word, column c in bits 2c, 2c+1: spread half a word to one
-          // code per nibble, then code = 4 msb + lsb
-          auto spread = [](uint32_t v) {
-            v = (v | (v << 8)) & 0x00FF00FFu;
-            v = (v | (v << 4)) & 0x0F0F0F0Fu;
-            return (v | (v << 2)) & 0x33333333u;
-          };
-          const uint32_t hm = (m[s >> 1] >> (16 * (s & 1))) & 0xFFFFu, hl = (l[s >> 1] >> (16 * (s & 1))) & 0xFFFFu;
-          const uint32_t qn = (spread(hm) << 2) | spread(hl);
-          qe = qn & 0x0F0F0F0Fu;
-          qo = (qn >> 4) & 0x0F0F0F0Fu;
-        }
-        u32x4 out;
-  #pragma unroll
-        for (int b = 0; b < 4; b++) {
-          if constexpr (SCB) {
-            // the codes of two columns as the halves 1024 + q (exact in fp16), which one mixed-precision FMA each turns
-            // into s (1024 + q) - s (1024 + zp); a bf16 scale times 11 bits is exact in fp32, so this is s (q - zp) rounded once
-            const f16x2 q2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(qo, qe, 0x0C000C00u | ((4u + b) << 16) | b) ^ (FMT == 0 ? 0x64886488u : 0x64006400u));
-            out[b] = pack_bf16(fmaf((float)q2[0], scale, c0), fmaf((float)q2[1], scale, c0));
-          } else {
-            const uint32_t f = FMT == 0 ? 0x88888888u : 0u;
-            const float we = fmaf((float)(((qe ^ f) >> (8 * b)) & 0xFF), scale, c0);
-            const float wo = fmaf((float)(((qo ^ f) >> (8 * b)) & 0xFF), scale, c0);
-            out[b] = pack_bf16(we, wo);
-          }
-        }
-        return __builtin_bit_cast(bf16x8, out);
+        c0 = -(float)((BIASED ? 1024u : 0u) + zp) * sc;
       };
       // bf: the first quarter's weights, already expanded; returns those of the next step.  While a quarter is multiplied, the
       // token rows of the next one are read and its weights expanded; the schedule deals one read and a fifth (a third, ...)
@@ -472,8 +475,8 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
 #pragma unroll
             for (int i = 0; i < F; i++) af[(s + 1) & 1][i] = *(const bf16x8*)(rows + (a_rd ^ ((s + 1) * 16)) + i * 4096);
           bf16x8 bn = bf;
-          if (s < 3) bn = expand(p.m, p.l, s + 1, sc, c0);
-          else if (!decltype(last_c)::value) bn = expand(pn.m, pn.l, 0, scn, c0n);      // (the last step of a chunk does not have the next planes yet)
+          if (s < 3) bn = expand(biased, p.m, p.l, s + 1, sc, c0);
+          else if (!decltype(last_c)::value) bn = expand(biased, pn.m, pn.l, 0, scn, c0n);      // (the last step of a chunk does not have the next planes yet)
 #pragma unroll
           for (int i = 0; i < F; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][i], bf, acc[i], 0, 0, 0);
 #pragma unroll
@@ -515,7 +518,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         const bool more = t + 4 < nk;
         if (more) load_weights(ex, (t >> 2) + 1);
-        bf16x8 bf = expand(p[0].m, p[0].l, 0, sc[0], c0[0]);
+        bf16x8 bf = expand(biased, p[0].m, p[0].l, 0, sc[0], c0[0]);
         bf = multiply(std::false_type(), t, bf, p[0], sc[0], c0[0], p[1], sc[1], c0[1]);
         auto next = [&](auto b_c) __attribute__((always_inline)) {
           constexpr int b = decltype(b_c)::value, n1 = b < 3 ? b + 1 : b;
@@ -536,6 +539,53 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   else if (NF >= 3 && nf == 3) kloop(std::integral_constant<int, (NF >= 3 ? 3 : 1)>());
   else if (NF >= 2 && nf == 2) kloop(std::integral_constant<int, (NF >= 2 ? 2 : 1)>());
   else kloop(std::integral_constant<int, 1>());
+
+  // Scales from 2^128 / 1279 on overflow c0 of the biased form: such a weight is -inf, and any product with it leaves the sums of
+  // its row not finite.  So a wave that finds its first sums not finite looks for such scales among its rows and, if there
+  // are any, forms all its sums again from the unbiased form, straight from memory: slow, but only ever for such weights.
+  if constexpr (BIASED) {
+    if (__any(!(fabsf(acc[0][0]) < INFINITY)) && (int)wrow < (MODE == 0 ? 2 * N : N)) {
+      const uint32_t row = wrow + wr;
+      auto scale_at = [&](size_t ee, uint32_t g) { return bf16_bits_to_f32(((const uint16_t*)(a.w.sc + ee * a.w.sc_stride))[row * (uint32_t)a.w.sng + g]); };
+      float top = 0.0f;
+      for (int ex = 0; ex < n_pass; ex++)
+        for (int g = 0; g < a.w.ng; g++) top = fmaxf(top, scale_at((size_t)(e + ex), g));
+      if (__any(!(top * 1279.0f < INFINITY))) {
+        uint32_t src[NF];                               // token rows (past the tile's last one: that row again)
+#pragma unroll
+        for (int i = 0; i < NF; i++) {
+          const int r = m0 + min(32 * i + n, m_cnt - 1);
+          src[i] = (MODE == 0 ? (uint32_t)(a.dense_rows ? r : a.rows[row0 + r] / a.k) : (uint32_t)(row0 + r)) * (uint32_t)K;
+#pragma unroll
+          for (int q = 0; q < 16; q++) acc[i][q] = 0.0f;
+        }
+        for (int ex = 0; ex < n_pass; ex++) {
+          const size_t ee = (size_t)(e + ex);
+          const uint16_t* av = MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff;
+          const uint8_t* pm = a.w.msb + ee * a.w.plane_stride + (size_t)row * rowb;
+          const uint8_t* pl = a.w.lsb + ee * a.w.plane_stride + (size_t)row * rowb;
+          const uint8_t* pz = a.w.zp + ee * a.w.zp_stride + (size_t)row * a.w.ng;
+          for (int t = 0; t < nk; t++) {
+            const uint32_t g = (uint32_t)(t * PF_BK + 32 * hh) >> sh;
+            const float scale = scale_at(ee, g), c0 = -(float)pz[g] * scale;
+            PlaneV m, l;
+#pragma unroll
+            for (int j = 0; j < PB32 / 4; j++) {
+              m[j] = ((const uint32_t*)(pm + (2 * t + hh) * PB32))[j];
+              l[j] = ((const uint32_t*)(pl + (2 * t + hh) * PB32))[j];
+            }
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+              const bf16x8 bf = expand(std::false_type(), m, l, s, scale, c0);
+#pragma unroll
+              for (int i = 0; i < NF; i++)
+                if (i < nf) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(av + src[i] + t * PF_BK + 32 * hh + 8 * s), bf, acc[i], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+  }
 
   // ---- epilogue.  D layout: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.  Stores go through a
   // buffer resource that ends with the tile's last row, so surplus rows are dropped without a branch.

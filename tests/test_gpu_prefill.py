@@ -183,12 +183,13 @@ def test_prefill_empty_expert_and_given_logits(ctx):
     assert O.max_abs_rel(t2np(y), yref) <= TOL
 
 
-def _layer_of(ctx, mats, G, nest=(8, 4)):
-    """One-expert bank and oracle expert from dense bf16 matrices (gate [f, d], up [f, d], down [d, f])."""
-    f, d = mats[0].shape
-    bank = B.Bank(ctx, 1, d, f, G, "bf16", "bf16", *nest)
-    B.smoe_quantize_slice(ctx, bank, 0, *(m.cuda()[None].contiguous() for m in mats))
-    return bank, O.quantize_expert(*(t2np(m) for m in mats), G, *nest, scale_dtype="bf16")
+def _layer_of(ctx, experts, G, nest=(8, 4)):
+    """Bank and oracle experts from dense bf16 matrices (gate [f, d], up [f, d], down [d, f]) per expert."""
+    f, d = experts[0][0].shape
+    bank = B.Bank(ctx, len(experts), d, f, G, "bf16", "bf16", *nest)
+    for e, mats in enumerate(experts):
+        B.smoe_quantize_slice(ctx, bank, e, *(m.cuda()[None].contiguous() for m in mats))
+    return bank, [O.quantize_expert(*(t2np(m) for m in mats), G, *nest, scale_dtype="bf16") for mats in experts]
 
 
 def test_prefill_swiglu_of_gates_far_below_zero(ctx):
@@ -202,12 +203,39 @@ def test_prefill_swiglu_of_gates_far_below_zero(ctx):
     wg[:, 0], wg[:, 1] = -v, 127.5 - v
     wu[:, 0], wu[:, 1] = 2.0 ** 119, 255.0 * 2.0 ** 112
     wd = torch.randn(d, f, generator=g) * 0.02
-    bank, ref = _layer_of(ctx, [m.bfloat16() for m in (wg, wu, wd)], G)
+    bank, ref = _layer_of(ctx, [[m.bfloat16() for m in (wg, wu, wd)]], G)
     x = torch.zeros(T, d, dtype=torch.bfloat16)
     x[:, 0] = 1.0
     y, idx, w, _ = B.smoe_prefill_histogram(ctx, bank, None, x.cuda(), 1, logits=torch.zeros(T, 1).cuda())
-    yref = O.prefill_layer(t2np(x).astype(np.float64), [ref], idx.cpu().numpy(), w.cpu().numpy().astype(np.float64))
+    yref = O.prefill_layer(t2np(x).astype(np.float64), ref, idx.cpu().numpy(), w.cpu().numpy().astype(np.float64))
     assert np.abs(yref).max() > 1e-3
+    yg = t2np(y)
+    for t in range(T):
+        assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
+@pytest.mark.parametrize("big,T,d,f,G,n_sh,nest", [
+    ("up", 3, 128, 64, 64, 0, (8, 4)),       # a tile of three rows
+    ("up", 700, 576, 128, 32, 0, (4, 2)),    # tall tiles, a partial 256-column chunk
+    ("up", 90, 256, 64, 128, 0, (6, 3)),
+    ("down", 40, 192, 320, 128, 2, (8, 4)),  # two shared experts summed by one work-group; a ragged column tile
+    ("down", 230, 64, 256, 512, 1, (6, 3)),
+])
+def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest):
+    # weights of up to 2^126 in magnitude: a group's range is 2^127, its scale at least 2^119, and 1024 scales overflow fp32 while
+    # every weight scale * (code - zero point) is finite.  The activations are small enough for h and y to be ordinary numbers.
+    say("prefill, largest scales", big, T, d, f, G, n_sh, nest)
+    g = torch.Generator().manual_seed(72)
+    def expert():
+        m = {"gate": torch.randn(f, d, generator=g) * 0.02, "up": torch.randn(f, d, generator=g) * 0.02,
+             "down": torch.randn(d, f, generator=g) * 0.02}
+        m[big] = (2.0 * torch.rand(m[big].shape, generator=g) - 1.0) * 2.0 ** 126
+        return [m[n].bfloat16() for n in ("gate", "up", "down")]
+    bank, ref = _layer_of(ctx, [expert()], G, nest)
+    shared, sref = _layer_of(ctx, [expert() for _ in range(n_sh)], G, nest) if n_sh else (None, [])
+    x = (torch.randn(T, d, generator=g) * 2.0 ** (-100 if big == "up" else -50)).bfloat16()
+    y, idx, w, _ = B.smoe_prefill_histogram(ctx, bank, shared, x.cuda(), 1, logits=torch.zeros(T, 1).cuda())
+    yref = O.prefill_layer(t2np(x).astype(np.float64), ref, idx.cpu().numpy(), w.cpu().numpy().astype(np.float64), sref)
     yg = t2np(y)
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
