@@ -77,13 +77,14 @@ def lib() -> C.CDLL:
         if not os.path.exists(LIB_PATH):
             raise SmoeError("libslicemoe.so is not built: run `python -m paper_2512_12990_amd.build` "
                             "(there is no CPU fallback)")
-        _lib = C.CDLL(LIB_PATH)
-        _lib.smoe_strerror.restype = C.c_char_p
-        _lib.smoe_strerror.argtypes = [C.c_int]
+        handle = C.CDLL(LIB_PATH)
+        handle.smoe_strerror.restype = C.c_char_p
+        handle.smoe_strerror.argtypes = [C.c_int]
         for name in EXPORTS:
-            getattr(_lib, name)            # fail loudly on a missing symbol
+            getattr(handle, name)            # fail loudly on a missing symbol
         for name, sig in _SIGNATURES.items():
-            getattr(_lib, name).argtypes = [_CT[c] for c in sig]
+            getattr(handle, name).argtypes = [_CT[c] for c in sig]
+        _lib = handle                        # last: another host thread must not see it without its signatures
     return _lib
 
 

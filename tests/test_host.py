@@ -198,3 +198,34 @@ int main() {
     subprocess.run(["g++", "-O2", "-I", os.path.join(ROOT, "paper_2512_12990_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
+
+
+def test_library_handle_is_published_with_its_signatures(monkeypatch):
+    """A second host thread may call lib() while the first one is still inside it: it must either load the library itself or get
+    a handle on which every signature is set (without them ctypes passes a device pointer as a 32-bit int)."""
+    handed_out = []
+
+    class Function:
+        def __init__(self):
+            self.__dict__["set"] = set()
+
+        def __setattr__(self, name, value):
+            handed_out.append(B._lib)                    # what another thread would be handed at this moment
+            self.set.add(name)
+
+    class Library:
+        def __init__(self, path):
+            self.functions = {name: Function() for name in B.EXPORTS}
+
+        def __getattr__(self, name):
+            handed_out.append(B._lib)
+            return self.functions[name]
+
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B.C, "CDLL", Library)
+    try:
+        handle = B.lib()
+    finally:
+        monkeypatch.undo()
+    assert handed_out and all(h is None for h in handed_out)
+    assert all("argtypes" in handle.functions[name].set for name in B._SIGNATURES)
