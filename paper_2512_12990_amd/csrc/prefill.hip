@@ -171,20 +171,21 @@ __device__ __forceinline__ u32x4 pf_rsrc(const void* base, uint32_t bytes) {
   return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) & 0xFFFFu,
                (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
 }
-// 64 lanes x 16 bytes from memory straight into LDS: lane i's bytes land at lds + 16 i (M0 is used for nothing
-// else here).  The compiler does not count these loads: see the K loop for what orders them.
+// 64 lanes x 16 bytes from memory straight into LDS: lane i's bytes land at lds + 16 i.  The LDS address is an operand in M0, so
+// the compiler writes that register and knows its contents (one wait state between the write and the load).  It does not count
+// these loads: see the K loop for what orders them.
 __device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
                : "memory");
 }
 
 // the same for one dword / one byte (zero-extended) per lane: lane i's dword lands at lds + 4 i
 __device__ __forceinline__ void dma4(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+  asm volatile("s_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
                : "memory");
 }
 __device__ __forceinline__ void dma1(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ubyte %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+  asm volatile("s_nop 0\n\tbuffer_load_ubyte %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
                : "memory");
 }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }

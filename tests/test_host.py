@@ -229,3 +229,20 @@ def test_library_handle_is_published_with_its_signatures(monkeypatch):
         monkeypatch.undo()
     assert handed_out and all(h is None for h in handed_out)
     assert all("argtypes" in handle.functions[name].set for name in B._SIGNATURES)
+
+
+def test_inline_assembly_leaves_m0_to_the_compiler():
+    """A direct load into LDS takes its address from M0.  The statement has to name that register as an operand: one that writes
+    it unannounced may take it from under code the compiler placed around it."""
+    csrc = os.path.join(ROOT, "paper_2512_12990_amd", "csrc")
+    n_loads = 0
+    for name in sorted(os.listdir(csrc)):
+        if not name.endswith((".hip", ".hpp")):
+            continue
+        for stmt in re.findall(r"asm volatile\s*\((.*?)\);", open(os.path.join(csrc, name)).read(), flags=re.S):
+            template = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', stmt.split(":")[0]))
+            assert "m0" not in template, (name, stmt)
+            if re.search(r"buffer_load\w+ .* lds", template):
+                assert '"{m0}"(' in stmt, (name, stmt)
+                n_loads += 1
+    assert n_loads >= 3
