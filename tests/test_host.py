@@ -3,6 +3,7 @@ argument validation that needs no GPU, and the host bookkeeping against the orac
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -246,3 +247,55 @@ def test_inline_assembly_leaves_m0_to_the_compiler():
                 assert '"{m0}"(' in stmt, (name, stmt)
                 n_loads += 1
     assert n_loads >= 3
+
+
+def test_direct_lds_loads_keep_clear_of_vector_writes_to_their_scalars(tmp_path):
+    """A memory instruction may read a scalar register five wait states after a vector instruction wrote it, not earlier.  The
+    compiler sees to that for its own instructions but does not look into inline assembly, and a spilled scalar comes back by a
+    vector instruction (v_readlane), so the distance is checked on the code that was built: back from every direct load into
+    LDS, along every path."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    so = tmp_path / "lib.so"
+    so.write_bytes(open(B.LIB_PATH, "rb").read())
+    subprocess.run([objdump, "--offloading", str(so)], check=True, capture_output=True)
+
+    def scalars(text):
+        regs = set()
+        for a, b, c in re.findall(r"\bs(?:\[(\d+):(\d+)\]|(\d+)\b)", text):
+            regs |= {int(c)} if c else set(range(int(a), int(b) + 1))
+        return regs
+
+    n_loads = 0
+    for obj in sorted(tmp_path.glob("*gfx950")):
+        text = subprocess.run([objdump, "-d", str(obj)], check=True, capture_output=True, text=True).stdout
+        if "offen lds" not in text:
+            continue
+        ins = [(m[1], int(m[2], 16)) for m in re.finditer(r"^\t(\S.*?)\s*// ([0-9A-F]+):", text, flags=re.M)]
+        at = {addr: i for i, (_, addr) in enumerate(ins)}
+        jumps_to = {}
+        for i, (op, addr) in enumerate(ins):
+            m = re.match(r"s_c?branch\w* (\d+)", op)
+            if m:
+                off = int(m[1]) - (65536 if int(m[1]) >= 32768 else 0)
+                jumps_to.setdefault(at[addr + 4 + 4 * off], []).append(i)
+        for i, (op, _) in enumerate(ins):
+            if not (op.startswith("buffer_load") and op.endswith("lds")):
+                continue
+            n_loads += 1
+            need, todo, seen = scalars(op), [(i, 0)], set()
+            while todo:
+                j, waited = todo.pop()
+                before = list(jumps_to.get(j, []))
+                if j and not re.match(r"s_branch|s_endpgm|s_setpc", ins[j - 1][0]):
+                    before.append(j - 1)
+                for b in before:
+                    bop = ins[b][0]
+                    written = scalars(bop.split(None, 1)[1].split(",")[0]) if bop.startswith("v_") and " " in bop else set()
+                    assert not (written & need), (op, bop, waited)
+                    w = waited + (int(bop.split()[1], 0) + 1 if bop.startswith("s_nop") else 1)
+                    if w < 5 and (b, w) not in seen:
+                        seen.add((b, w))
+                        todo.append((b, w))
+    assert n_loads > 0
