@@ -44,9 +44,9 @@ def _check_routing(ctx, x, wr, k, idx, w, hist, E):
 @pytest.mark.parametrize("T,E,k,d,f,G", [(200, 6, 2, 256, 128, 64), (37, 5, 3, 128, 192, 32), (450, 3, 1, 128, 64, 64),
                                           (70, 4, 2, 4096, 128, 128)])
 def test_prefill_small_all_tokens(ctx, T, E, k, d, f, G):
-    # 200 tokens over 6 experts: one expert tile is ragged; 37 tokens: a single partial fragment;
-    # 450 tokens over 3 experts top-1: some expert gets more than one 192-row tile; d_model 4096: the
-    # router's activations need more than 64 KB of LDS
+    # 200 tokens over 6 experts: three fragments per tile, the last one ragged; 37 tokens: a single partial fragment;
+    # 450 tokens over 3 experts top-1: about 150 rows per expert, tiles of five fragments; d_model 4096: two
+    # experts per token out of four, wide rows
     say("prefill small", T, E, k, d, f, G)
     shp = synth.LayerShape(d, E, f, k, G, act="bf16")
     pair = LayerPair(ctx, shp, seed=21)
@@ -66,8 +66,8 @@ def test_prefill_small_all_tokens(ctx, T, E, k, d, f, G):
 @pytest.mark.parametrize("n_shared,f_s,gate", [(1, 320, True), (2, 128, False)])
 def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     # the shared-expert group sees every token (dense GEMMs over the token rows): one wide shared expert
-    # behind a sigmoid gate (Qwen shape) or two plain ones (DeepSeek shape); 230 tokens = one full
-    # 192-row tile and a ragged one; 320 = 2.5 column tiles of the gate/up GEMM
+    # behind a sigmoid gate (Qwen shape) or two plain ones (DeepSeek shape); 230 tokens = three dense tiles of
+    # up to 96 rows, in the routed experts' launches; 320 = five column tiles of the gate/up GEMM
     T, E, k, d, f, G = 230, 6, 2, 256, 128, 64
     say("prefill with shared experts", n_shared, f_s, gate)
     shp = synth.LayerShape(d, E, f, k, G, n_shared=n_shared, shared_d_ff=f_s, shared_gate=gate, act="bf16")
@@ -98,7 +98,7 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     (130, 6, 2, 192, 320, 64, 1, 192, (8, 4), "f32"),    # odd numbers of K steps, two fragments, shared tiles in the same launches; fp32 scales
     (33, 130, 5, 576, 128, 32, 2, 64, (8, 4), "bf16"),   # tile search over more than two lanes' worth of experts, most of them empty; nine steps
     (400, 5, 1, 128, 448, 128, 2, 320, (6, 3), "f32"),   # three fragments; seven steps (a partial 256-column chunk); two shared experts
-    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16"), # five fragments, four tiles per expert; shared experts in launches of their own
+    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16"), # five fragments, four tiles per expert; the shared expert's tiles as tall, in the same launches
     (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16"),  # a group wider than the row; three shared experts at once
     (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16"),      # shared experts whose H does not fit beside O: one after the other
 ])
@@ -116,6 +116,40 @@ def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
     yg = t2np(y)
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,s_nest,s_bank,s_G", [
+    # 64 experts top-1 want 32-row tiles, the shared experts 160-row ones.  Up to 24 short tiles of tokens the shared experts' tiles ride
+    # in the routed launches (768 tokens), beyond that they have launches of their own (769, 900)
+    (768, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64),
+    (769, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64),
+    (900, 64, 1, 256, 64, 64, 2, 128, (8, 4), "bf16", 64),     # own launches; the second shared expert's H waits in Y
+    (900, 64, 1, 128, 64, 32, 2, 192, (8, 4), "bf16", 32),     # ... in the rows of O
+    (900, 64, 1, 64, 64, 64, 2, 192, (8, 4), "bf16", 64),      # ... does not fit there: one after the other
+    # from nine short tiles on, also only as long as the dense tiles expand at most 600 million weights again
+    (760, 64, 1, 2048, 64, 128, 1, 4032, (8, 4), "bf16", 128),
+    (760, 64, 1, 2048, 64, 128, 1, 4160, (8, 4), "bf16", 128),
+    # a shared bank of another nest or scale type cannot ride along, one of another group can
+    (130, 6, 2, 192, 128, 64, 2, 64, (4, 2), "bf16", 64),
+    (130, 6, 2, 192, 128, 64, 1, 192, (8, 4), "f32", 32),
+    (130, 6, 2, 192, 128, 32, 1, 192, (8, 4), "bf16", 128),
+])
+def test_prefill_shared_experts_beside_the_routed_ones(ctx, T, E, k, d, f, G, n_sh, f_s, s_nest, s_bank, s_G):
+    # tolerance: that of every bf16 prefill test; the wide layers on a sample of the tokens
+    say("prefill, shared launches", T, E, k, d, f, G, n_sh, f_s, s_nest, s_bank, s_G)
+    rp = LayerPair(ctx, synth.LayerShape(d, E, f, k, G, act="bf16"), seed=53)
+    sp = LayerPair(ctx, synth.LayerShape(d, E, f, k, s_G, n_shared=n_sh, shared_d_ff=f_s, act=s_bank, b_high=s_nest[0], b_low=s_nest[1]),
+                   seed=53, routed=False)
+    x = synth.activations(53, T, d, "bf16").cuda()
+    wr = synth.router_weight(53, 0, E, d, std=0.05).cuda()
+    y, idx, w, hist = B.smoe_prefill_histogram(ctx, rp.routed, sp.shared, x, k, w_router=wr, add_residual=True)
+    ridx, rw = _check_routing(ctx, x, wr, k, idx, w, hist, E)
+    toks = np.arange(T) if d < 1024 else np.unique(np.append(np.arange(0, T, 31), [31, 32, 159, 160, T - 1]))
+    yref = O.prefill_layer(t2np(x).astype(np.float64)[toks], rp.oracle_routed(), ridx[toks], rw[toks].astype(np.float32).astype(np.float64),
+                           sp.oracle_shared(), None, add_residual=True)
+    yg = t2np(y)[toks]
+    for i, t in enumerate(toks):
+        assert O.max_abs_rel(yg[i], yref[i]) <= TOL, t
 
 
 def test_prefill_in_place(ctx):
@@ -270,11 +304,12 @@ def test_prefill_qwen_layer_full_size_sampled_tokens(ctx):
         assert err <= TOL
 
 
-def test_prefill_more_pairs_than_the_grouping_registers_hold(ctx):
-    # 4100 tokens top-3 = 12300 (token, slot) pairs: every thread of the grouping kernel owns a run of 13,
-    # more than the eight it keeps in registers, so the pairs are read one by one in both passes; every
-    # expert gets a dozen 192-row tiles.  (8192 tokens top-4, the long-prompt bench line, runs the same path.)
-    T, E, k, d, f, G = 4100, 5, 3, 128, 64, 32
+@pytest.mark.parametrize("T", [4100, 5501])
+def test_prefill_more_pairs_than_the_grouping_registers_hold(ctx, T):
+    # 5501 tokens top-3 = 16503 (token, slot) pairs: every thread of the grouping kernel owns a run of 20 (the last one shorter),
+    # more than the 16 it keeps in registers, so the pairs are read one by one in both passes; 4100 tokens are 12300 pairs
+    # in runs of 16, the longest that stay in registers.  Every expert gets more than a dozen 160-row tiles.
+    E, k, d, f, G = 5, 3, 128, 64, 32
     say("prefill, long pair list", T, E, k)
     shp = synth.LayerShape(d, E, f, k, G, n_shared=1, shared_d_ff=64, act="bf16")
     pair = LayerPair(ctx, shp, seed=27)
@@ -282,7 +317,8 @@ def test_prefill_more_pairs_than_the_grouping_registers_hold(ctx):
     wr = synth.router_weight(27, 0, E, d, std=0.05).cuda()
     y, idx, w, hist = B.smoe_prefill_histogram(ctx, pair.routed, pair.shared, x, k, w_router=wr, add_residual=True)
     ridx, rw = _check_routing(ctx, x, wr, k, idx, w, hist, E)
-    assert int(hist.cpu().numpy().view(np.uint32).max()) > 192 * 8
+    assert int(hist.cpu().numpy().view(np.uint32).min()) > 160 * 12
+    assert (T * k > 16 * 1024) == (T == 5501)
     yref = O.prefill_layer(t2np(x).astype(np.float64), pair.oracle_routed(), ridx, rw.astype(np.float32).astype(np.float64),
                            pair.oracle_shared(), None, add_residual=True)
     yg = t2np(y)
@@ -337,7 +373,7 @@ def test_prefill_qwen_24_layer_chain(ctx):
 
 
 def test_prefill_random_small_shapes(ctx):
-    # a seeded sweep over prefill shapes: token counts around the 192-row tile, d_model and d_ff any
+    # a seeded sweep over prefill shapes: token counts around multiples of the 32-row fragment, d_model and d_ff any
     # multiple of 64 (ragged column tiles), every group size, with and without shared experts
     rng = np.random.default_rng(77)
     for case in range(8):
