@@ -171,10 +171,14 @@ def test_route_given_logits(ctx, E, k, T):
 
 @pytest.mark.parametrize("T,E,k,d,dt", [(256, 8, 2, 512, "bf16"), (257, 60, 4, 1032, "bf16"), (513, 70, 6, 520, "bf16"),
                                         (1025, 13, 3, 1544, "bf16"), (300, 200, 16, 40, "bf16"), (5, 9, 3, 75, "bf16"),
-                                        (256, 64, 6, 516, "f32"), (511, 5, 5, 1027, "f32"), (1030, 130, 8, 512, "f32")])
+                                        (256, 64, 6, 516, "f32"), (511, 5, 5, 1027, "f32"), (1030, 130, 8, 512, "f32"),
+                                        (300, 7, 2, 77, "bf16"), (600, 9, 3, 333, "bf16"), (1100, 9, 3, 1037, "bf16"),
+                                        (1030, 16, 4, 4096, "bf16"), (600, 16, 4, 8192, "bf16"), (515, 16, 4, 4096, "f32"),
+                                        (1, 16, 4, 8840, "bf16"), (1100, 16, 4, 8840, "bf16")])
 def test_route_token_tiles(ctx, T, E, k, d, dt):
     # one, two, four and eight tokens per work-group, ragged last work-groups, rows of no, one and several whole batches
-    # of 512 columns with and without a remainder, odd widths; fp32 sums of d terms: a few rounding steps of |w| . |x|
+    # of 512 columns with and without a remainder, odd widths, more than 64 KB of LDS (eight vectors of 4096 columns, four of 8192)
+    # up to the widest accepted; fp32 sums of d terms: a few rounding steps of |w| . |x|
     say("route tiles", T, E, k, d, dt)
     x = synth.activations(9, T, d, dt).cuda()
     wr = synth.router_weight(9, 0, E, d, std=0.05).cuda()
@@ -189,6 +193,14 @@ def test_route_token_tiles(ctx, T, E, k, d, dt):
     # the same logits through the given-logits form
     idx2, w2 = B.smoe_route(ctx, k, logits=z, bias=bias, norm_topk=True)
     assert torch.equal(idx, idx2) and torch.equal(w, w2)
+
+
+@pytest.mark.parametrize("T", [1, 1100])
+def test_route_refuses_wider_rows_for_any_number_of_tokens(ctx, T):
+    # 16 experts, bf16: 8840 columns are accepted (above), 8848 are not, also where fewer tokens share a work-group's LDS
+    x = torch.zeros((T, 8848), dtype=torch.bfloat16, device="cuda:0")
+    with pytest.raises(B.SmoeError):
+        B.smoe_route(ctx, 4, x=x, w_router=torch.zeros((16, 8848), device="cuda:0"))
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
@@ -308,7 +320,7 @@ def test_group32_layer(ctx, dt):
         say("  fused", fused, "worst max-abs-rel", worst)
 
 
-# (down work-groups of 8 output rows at 2 tokens, 16 at 5, 32 at 8, 64 at 12 and 16)
+# (down work-groups of 8 output rows up to 8 tokens, 16 at 12 and 16; wider ones: test_multi_token_down_widths)
 @pytest.mark.parametrize("T,dt", [(2, "f32"), (5, "bf16"), (8, "bf16"), (12, "f32"), (16, "bf16")])
 def test_multi_token_layer(ctx, T, dt):
     # T tokens through one layer in one pair of launches: every token must come out exactly as from
@@ -360,6 +372,10 @@ def test_multi_token_layer(ctx, T, dt):
                                            (9, 2048, 7, 1, "bf16"),      # 40 rows
                                            (11, 1920, 6, 2, "bf16"),     # 48
                                            (4, 1984, 6, 1, "bf16"),      # 16, but 124 work-groups are no multiple of eight
+                                           (8, 2048, 5, 1, "bf16"),      # 32
+                                           (8, 2048, 3, 0, "f32"),
+                                           (16, 2048, 6, 2, "bf16"),     # 64
+                                           (16, 2048, 2, 1, "f32"),
                                            (13, 3968, 4, 0, "bf16"),     # wider than the built-in widths, wide gate/up rows
                                            (16, 64, 2, 1, "bf16")])      # fewer rows than work-groups
 def test_multi_token_down_widths(ctx, T, d, k, n_sh, dt):

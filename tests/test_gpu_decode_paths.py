@@ -91,11 +91,11 @@ def test_fused_topk_ties_signed_zero_norm_scale(ctx, E, k):
 
 
 @pytest.mark.parametrize("T,f,k,f_s,dt", [(9, 3584, 8, 0, "bf16"), (12, 448, 3, 8224, "bf16"), (16, 2720, 10, 96, "f32"),
-                                          (10, 3584, 8, 8224, "bf16")])
+                                          (10, 3584, 8, 8224, "bf16"), (16, 3584, 8, 8224, "bf16")])
 def test_many_tokens_wide_d_ff(ctx, T, f, k, f_s, dt):
-    # nine or more tokens per step leave 32 gate/up work-groups per token, so a work-group owns
-    # ceil(d_ff / 32) row pairs of every slot (112 for d_ff 3584, 257 for the 8224-wide shared expert, 85
-    # for 2720): the entry -> (slot, row pair) division has to be exact for these counts too
+    # 9 / 10 / 12 / 16 tokens per step leave 56 / 48 / 40 / 32 gate/up work-groups per token, so a work-group owns
+    # ceil(d_ff / that) row pairs of every slot (64, 75 and 112 for d_ff 3584, 206, 172 and 257 for the 8224-wide shared
+    # expert, 85 for 2720): the entry -> (slot, row pair) division has to be exact for these counts too
     say("many tokens, wide d_ff", T, f, k, f_s, dt)
     d, E = 128, 12
     shp = synth.LayerShape(d, E, f, k, 32, n_shared=1 if f_s else 0, shared_d_ff=f_s, act=dt)
