@@ -141,7 +141,7 @@ struct GemmArgs {
   int group_shift;          // quantisation group = 1 << group_shift columns
   int E, k, d_model, d_ff;
   int n_col_tiles;          // column tiles of this GEMM
-  int super;                // row tiles that share a column tile before the next column tile starts
+  int super;                // row tiles that share a column tile before the next column tile starts (see smoe_prefill_histogram)
   const uint32_t* hist;     // [E] rows of an expert (written by group_kernel, like rows)
   const int32_t* rows;      // [T*k]
   const uint16_t* x;        // MODE 0: X [T, d_model] bf16
@@ -714,7 +714,11 @@ static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf
   return launch_gemm_nf<MODE, 5>(ctx, g, sc_bf16, bits, grid);
 }
 // Tile height for experts of `rows` rows on average: one tile for nearly every expert (mean plus one and a half
-// standard deviations of even routing) if five fragments can do that, else the tallest tile.
+// standard deviations of even routing) if five fragments can do that, else the tallest tile.  There is no tile of four: with
+// 97 - 116 rows per expert it gains nothing (60 experts of d_model 2048, d_ff 1408: 214.0 us against 213.5 at 97 rows, 228.5 against
+// 229.6 at 110) or loses (64 such experts 226.8 -> 238.3 us at 103 rows; d_model 1024, d_ff 512 69 -> 81 us at 112), because more experts
+// need a second one.  The mean is all the host knows.  Where routing is skewed (popularity falling as 1 / rank^1.1 or 1 / rank^2)
+// the popular experts take several short tiles: 500 / 2048 tokens top-6 over 64 experts 203 / 474 us even, 230 / 466 and 237 / 500 skewed.
 static int pick_nf(double rows) {
   const double want = rows + 1.5 * sqrt(rows);
   return want <= 32.0 ? 1 : want <= 64.0 ? 2 : want <= 96.0 ? 3 : 5;
@@ -729,7 +733,7 @@ static PrefillLayout prefill_layout(int T, int E, int k, int d_model, int d_ff, 
   size_t off = 0;
   L.rows = off;    off = up256(off + (size_t)T * k * 4);
   L.pos = off;     off = up256(off + (size_t)T * k * 4);
-  // (two areas that nothing uses any more, kept so that scratch buffers of the sizes handed out before still fit)
+  // (two areas that nothing uses: they keep what smoe_prefill_bytes returns, and with it which scratch sizes are refused, as it was)
   off = up256(off + (size_t)(E + 1) * 4);
   off = up256(off + (size_t)(4 + 4 * (E + (T * k) / 192 + 8)) * 4);
   L.h = off;       off = up256(off + (size_t)T * k * d_ff * 2);
@@ -795,6 +799,9 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
   GemmArgs g{};
   g.group_shift = __builtin_ctz((unsigned)routed->dev.group); g.rows = rows; g.hist = hist_dev;
   g.x = (const uint16_t*)x_dev; g.h = h; g.o = o; g.wgt = w_dev; g.E = E; g.k = k; g.d_model = d; g.d_ff = f;
+  // Row tiles side by side on a column tile's weights: four where an expert has several tiles, eight of the dense ones.  Between 1 and
+  // 16 it matters little: 1 / 4 / 8 give 430 / 435 / 430 us (60 experts, 273 rows each), 802 / 809 / 816 (546 rows), 565 / 553 / 541 (16 experts
+  // of d_model 4096, 500 rows); dense tiles 1 / 8 / 32: 163.7 / 158.8 / 159.2 us (173 tokens), 189 / 180 / 181 (300), 727 / 732 / 750 (4096).
   g.super = (double)T * k / E > bm ? 4 : 1;
   const int mt = max_tiles(T, E, k, bm);         // upper bound of the tile count; surplus work-groups return at once
   const int scb = routed->dev.sc_bf16, bits = routed->dev.bits;

@@ -76,8 +76,9 @@ static int launch_route_t(smoe_ctx* ctx, const RouteArgs& a, int T) {
 }
 
 int smoe_launch_route(smoe_ctx* ctx, const RouteArgs& a, int T, int act_dtype) {
-  // what is accepted does not depend on the number of tokens: the limit is that of the widest form with 64-bit
-  // selection keys per wave beside the activations
+  // What is accepted does not depend on the number of tokens.  The limit is a fixed one: eight (bf16) or four (fp32) vectors, their
+  // logits, and 64-bit selection keys for every wave, which the kernel no longer holds (their term stays, so that what was
+  // refused still is); every form needs less.
   const bool bf16 = act_dtype == SMOE_BF16;
   const int nt = bf16 ? 8 : 4;
   const size_t most = (size_t)nt * a.E * 4 + (size_t)RT_NW * a.E * 8 + RT_NW * SMOE_MAX_TOPK * 8 +

@@ -197,7 +197,7 @@ def test_route_token_tiles(ctx, T, E, k, d, dt):
 
 @pytest.mark.parametrize("T", [1, 1100])
 def test_route_refuses_wider_rows_for_any_number_of_tokens(ctx, T):
-    # 16 experts, bf16: 8840 columns are accepted (above), 8848 are not, also where fewer tokens share a work-group's LDS
+    # 16 experts, bf16: 8846 columns are the limit (8840 are accepted above), 8848 are refused, also where fewer tokens share a work-group's LDS
     x = torch.zeros((T, 8848), dtype=torch.bfloat16, device="cuda:0")
     with pytest.raises(B.SmoeError):
         B.smoe_route(ctx, 4, x=x, w_router=torch.zeros((16, 8848), device="cuda:0"))
