@@ -208,8 +208,8 @@ template <int SCB, int FMT, int NF> struct PfLds {
 // whole 128-byte line of a nibble plane) at a time into an area of the wave's own, fetched while the previous 256
 // columns, by then in registers, are multiplied.
 // Bound: with few rows per expert the weights' bytes; with many the instruction issue of the waves (about 100 vector
-// instructions of expansion to 4 * NF products of 32 cycles per step and wave, two waves per SIMD: a third would
-// need a shorter tile).  Why this shape, measured on the gate/up GEMM of 60 experts of d_model 2048, d_ff 1408 at
+// instructions of expansion to 4 * NF products of 32 cycles per step and wave, two waves per SIMD: 160 rows leave no LDS for
+// a third work-group per CU).  Why this shape, measured on the gate/up GEMM of 60 experts of d_model 2048, d_ff 1408 at
 // 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use them, every lane of a
 // load in another cache line, 215 / 183 us; 128 columns at a time through LDS, half a line, 165 / 123 us; a whole line
 // and 32 instead of 64 weight rows per wave, with the epilogue below, 149 / 94 us; products, reads and expansion dealt out
