@@ -544,30 +544,38 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   // Scales from 2^128 / 1279 on overflow c0 of the biased form: such a weight is -inf, and any product with it leaves the sums of
   // its row not finite.  So a wave that finds its first sums not finite looks for such scales among its rows and, if there
   // are any, forms all its sums again from the unbiased form, straight from memory: slow, but only ever for such weights.
+  // (The arguments are fetched anew there: kept in scalar registers over the K loop they would spill others.)
   if constexpr (BIASED) {
-    if (__any(!(fabsf(acc[0][0]) < INFINITY)) && (int)wrow < (MODE == 0 ? 2 * N : N)) {
-      const uint32_t row = wrow + wr;
-      auto scale_at = [&](size_t ee, uint32_t g) { return bf16_bits_to_f32(((const uint16_t*)(a.w.sc + ee * a.w.sc_stride))[row * (uint32_t)a.w.sng + g]); };
+    if (__any(!(fabsf(acc[0][0]) < INFINITY))) {
+      typedef __attribute__((address_space(4))) const GemmPair ArgsInMemory;
+      ArgsInMemory* args = (ArgsInMemory*)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(args));
+      const auto* b = &args->g[second ? 1 : 0];
+      const int Kb = MODE == 0 ? b->d_model : b->d_ff, shb = b->group_shift, passes = MODE == 1 && b->dense_rows ? b->n_dense : 1;
+      const uint32_t row = (uint32_t)(nt * PF_BN + wave * 32) + wr;
+      const bool inside = nt * PF_BN + wave * 32 < (MODE == 0 ? 2 * b->d_ff : b->d_model);      // (all 32 rows of a wave or none)
+      auto scale_at = [&](size_t ee, uint32_t g) { return bf16_bits_to_f32(((const uint16_t*)(b->w.sc + ee * b->w.sc_stride))[row * (uint32_t)b->w.sng + g]); };
       float top = 0.0f;
-      for (int ex = 0; ex < n_pass; ex++)
-        for (int g = 0; g < a.w.ng; g++) top = fmaxf(top, scale_at((size_t)(e + ex), g));
+      if (inside)
+        for (int ex = 0; ex < passes; ex++)
+          for (int g = 0; g < b->w.ng; g++) top = fmaxf(top, scale_at((size_t)(e + ex), g));
       if (__any(!(top * 1279.0f < INFINITY))) {
         uint32_t src[NF];                               // token rows (past the tile's last one: that row again)
 #pragma unroll
         for (int i = 0; i < NF; i++) {
           const int r = m0 + min(32 * i + n, m_cnt - 1);
-          src[i] = (MODE == 0 ? (uint32_t)(a.dense_rows ? r : a.rows[row0 + r] / a.k) : (uint32_t)(row0 + r)) * (uint32_t)K;
+          src[i] = (MODE == 0 ? (uint32_t)(b->dense_rows ? r : b->rows[row0 + r] / b->k) : (uint32_t)(row0 + r)) * (uint32_t)Kb;
 #pragma unroll
           for (int q = 0; q < 16; q++) acc[i][q] = 0.0f;
         }
-        for (int ex = 0; ex < n_pass; ex++) {
-          const size_t ee = (size_t)(e + ex);
-          const uint16_t* av = MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff;
-          const uint8_t* pm = a.w.msb + ee * a.w.plane_stride + (size_t)row * rowb;
-          const uint8_t* pl = a.w.lsb + ee * a.w.plane_stride + (size_t)row * rowb;
-          const uint8_t* pz = a.w.zp + ee * a.w.zp_stride + (size_t)row * a.w.ng;
-          for (int t = 0; t < nk; t++) {
-            const uint32_t g = (uint32_t)(t * PF_BK + 32 * hh) >> sh;
+        for (int ex = 0; ex < passes; ex++) {
+          const size_t ee = (size_t)(e + ex), plane_row = (size_t)row * ((uint32_t)(Kb >> 5) * PB32);
+          const uint16_t* av = MODE == 0 ? b->x : ex == 0 ? b->h : b->h_more + (size_t)(ex - 1) * b->dense_rows * b->d_ff;
+          const uint8_t* pm = b->w.msb + ee * b->w.plane_stride + plane_row;
+          const uint8_t* pl = b->w.lsb + ee * b->w.plane_stride + plane_row;
+          const uint8_t* pz = b->w.zp + ee * b->w.zp_stride + (size_t)row * b->w.ng;
+          for (int t = 0; t < Kb / PF_BK; t++) {
+            const uint32_t g = (uint32_t)(t * PF_BK + 32 * hh) >> shb;
             const float scale = scale_at(ee, g), c0 = -(float)pz[g] * scale;
             PlaneV m, l;
 #pragma unroll
