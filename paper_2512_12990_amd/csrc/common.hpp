@@ -46,7 +46,7 @@ struct smoe_ctx {
   int timing;
   void* timing_events;   // std::vector<hipEvent_t>*, four events per decode call
   size_t down_lds_granted[60];   // dynamic LDS already granted to each down_kernel instantiation on this device
-  size_t gemm_lds_granted[48];   // likewise for the instantiations of grouped_gemm_kernel
+  size_t gemm_lds_granted[60];   // likewise for the instantiations of grouped_gemm_kernel
   size_t route_lds_granted[8];   // likewise for the instantiations of route_batch_kernel
   // single-launch decode (smoe_ctx_single_launch)
   int one_launch;                // the mode is on

@@ -21,9 +21,9 @@ typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-#define PF_BN 128          // weight rows per work-group tile: 32 per wave
 #define PF_BK 64
-#define PF_NT 256          // threads per work-group
+// waves of a GEMM work-group (32 weight rows each) by the fragments of its tile
+static constexpr int pf_waves(int nf) { return nf > 5 ? 8 : 4; }
 
 // ------------------------------------------------------------------------------- small kernels
 #define GR_THREADS 1024
@@ -179,6 +179,12 @@ __device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, 
                : "memory");
 }
 
+// the same by the wave's first 32 lanes (all 64 are active around it)
+__device__ __forceinline__ void dma16_half(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 exec_hi, 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds\n\ts_mov_b32 exec_hi, -1" ::"v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
+               : "memory");
+}
+
 // the same for one dword / one byte (zero-extended) per lane: lane i's dword lands at lds + 4 i
 __device__ __forceinline__ void dma4(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
@@ -190,39 +196,47 @@ __device__ __forceinline__ void dma1(u32x4 rsrc, uint32_t voff, uint32_t soff, u
 }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// LDS of a GEMM work-group.  A step of a short tile (32 or 64 rows) is over before its token rows have come from L2: four
-// buffers let those be sent for three steps ahead, without costing a resident work-group (three per CU with 32 rows, two
-// with 64): 173 tokens through 64 experts 173.5 -> 166.6 us per layer.  Taller tiles have room for two.
-// (That third work-group also needs the waves' areas cut to the groups at hand; for taller tiles their size is fixed.)
+// LDS of a GEMM work-group: row buffers (one 64-column step each), the waves' weight areas.  A step of a short tile is over before its token
+// rows have come from L2, so those are sent for up to four steps ahead: as many buffers as fit beside two work-groups per CU (one with
+// eight waves, where a tile of fewer fragments has more buffers).  32 and 64 rows with two, later four buffers: 173 tokens through 64
+// experts 173.5 -> 166.6 us per layer.  (There the waves' areas are also cut to the groups at hand; elsewhere their size is fixed.)
 template <int SCB, int FMT, int NF> struct PfLds {
-  static constexpr int NBUF = NF <= 2 ? 4 : 2, ROWS = NBUF * 32 * NF * 128, PLANE = FMT == 0 ? 4096 : FMT == 1 ? 2048 : 3072;
+  static constexpr int NW = pf_waves(NF), ROWS = NF == 8 ? 81920 : NF == 5 ? 40960 : NF == 3 ? 36864 : NF * 16384, PLANE = FMT == 0 ? 4096 : FMT == 1 ? 2048 : 3072;
+  static constexpr int nbuf(int f) { return ROWS / (f * 4096) < 4 ? ROWS / (f * 4096) : 4; }      // buffers of a tile of f fragments
   static constexpr bool FIT = NF <= 2;
   static constexpr int ZP_AT = 2 * PLANE + (SCB ? 4 : 8) * 128, WAVE = ZP_AT + 8 * 128;      // two planes, scale dwords, zero-points of 32 rows and 256 columns in groups of 32
 };
 
-// One expert's 32 * NF token rows times 128 weight rows, four waves.  A wave owns all the token rows and 32 of
+// One expert's 32 * NF token rows times 32 weight rows per wave, four or (NF = 8) eight waves.  A wave owns all the token rows and 32 of
 // the weight rows; it expands its weights to bf16 in registers -- lane (n, h) holds columns 32 h .. 32 h + 31 of one
 // row of a K step (64 columns), and MFMA s of the step contracts columns {8 s ..} and {32 + 8 s ..} on both operands --
 // so every weight is expanded once per tile and LDS carries bf16 only for the token rows.  All memory reaches LDS
-// by direct loads: token rows one K step ahead (short tiles three) into as many buffers and one; planes, scales and zero-points 256 columns (a
+// by direct loads: token rows into a ring of step buffers; planes, scales and zero-points 256 columns (a
 // whole 128-byte line of a nibble plane) at a time into an area of the wave's own, fetched while the previous 256
 // columns, by then in registers, are multiplied.
-// Bound: with few rows per expert the weights' bytes; with many the instruction issue of the waves (about 100 vector
-// instructions of expansion to 4 * NF products of 32 cycles per step and wave, two waves per SIMD: 160 rows leave no LDS for
-// a third work-group per CU).  Why this shape, measured on the gate/up GEMM of 60 experts of d_model 2048, d_ff 1408 at
-// 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use them, every lane of a
-// load in another cache line, 215 / 183 us; 128 columns at a time through LDS, half a line, 165 / 123 us; a whole line
-// and 32 instead of 64 weight rows per wave, with the epilogue below, 149 / 94 us; products, reads and expansion dealt out
-// in turn, the first weights sent for before the token rows are looked up, 143 / 91 us.  (192 x 256 tiles, weights expanded
-// once more through LDS, one work-group per CU: 161 / 117 us, and 297 against 215 us on 4096 dense rows, d_ff 5632.)
+// Bound: with few rows per expert the weights' bytes.  With many, a step is a stream of 200 - 260 instructions per wave (4 F products of 32
+// cycles, 107 vector instructions of expansion, 4 F LDS reads of 1 KB), two waves per SIMD.  Time stamps in the kernel (60 experts of
+// d_model 2048, d_ff 1408, 137 rows) showed what a step cost beyond that, and the loop is built around it: 28 % of it went into sending
+// direct loads and fetching planes in one go at the head of a step (now one load behind a product, 35 - 70 cycles each), 22 % into waiting for
+// rows, the rest into products and expansion running one after the other in both waves that left a barrier together (now a fifth of the
+// expansion and a read behind every product, pinned there: the compiler sinks the work otherwise).  No load depends on a condition: past the
+// last step the range is empty, the load counts all the same, and every wait is a constant.  Cycles per step, two work-groups of four
+// waves: 1865 before, 1708 now (mean of 3 to 5 fragments); eight waves: 1785 at 4 fragments, 2657 at 8, i.e. 446 and 332 per fragment -- a weight is
+// expanded for more rows.  Of those 2657 the products are 2048, LDS traffic some 2500, the barrier 400.  Taller tiles take more of a CU at
+// once; where that leaves the chip unfilled the shorter ones are faster (gemm_cycles).  A layer of 2048 / 4096 tokens (60 experts of d_ff 1408,
+// the longer one with a shared expert of 5632): 291 -> 264 / 806 -> 709 us.  Not kept: eight waves and 160 rows (287 / 786 us), eight-wave
+// work-groups that stay and take a list of tiles, the next one's weights sent for before the epilogue (286 / 798 us against 270 / 747).
+// Earlier shapes, gate/up GEMM of 60 experts at 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use
+// them, every lane of a load in another cache line, 215 / 183 us; 128 columns at a time through LDS, half a line, 165 / 123 us; a whole line
+// and 32 instead of 64 weight rows per wave 149 / 94 us.
 template <int MODE, int SCB, int FMT, int NF>      // FMT 0: 8/4 nest, nibble planes; 1: 4/2 nest, 2-bit planes; 2: 6/3 nest, 3-bit planes
-__global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(GemmPair pair) {
+__global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_gemm_kernel(GemmPair pair) {
   constexpr int BM = 32 * NF;
   constexpr int PB32 = FMT == 0 ? 16 : FMT == 1 ? 8 : 12;      // plane bytes of 32 columns
   constexpr int PROW = 8 * PB32, PPR = PROW / 16, NPL = 32 * PROW / 1024;      // of a row and 256 columns; 16-byte pieces of that; loads per plane
   constexpr int PLANE = 32 * PROW;                             // bytes of one plane in a wave's area: MSB plane, LSB plane, scales, zero-points
   typedef PfLds<SCB, FMT, NF> Lds;
-  constexpr int NBUF = Lds::NBUF, AHEAD = NBUF - 1;
+  constexpr int NW = Lds::NW, BN = 32 * NW;
   extern __shared__ __align__(1024) uint8_t As[];              // NBUF K steps of the token rows, 128 bytes per row; the waves' areas
   const int ZP_AT = Lds::FIT ? pair.zp_at : Lds::ZP_AT;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -301,7 +315,7 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   // ---- the wave's 32 weight rows.  MODE 0: gate and up rows alternate in the bank, so they are the gate and up rows
   // of 16 output columns; lanes 0 .. 15 take the gate rows, lanes 16 .. 31 the up rows.  Rows past the matrix read
   // out of the section's range.
-  const uint32_t wrow = (uint32_t)(nt * PF_BN + wave * 32);
+  const uint32_t wrow = (uint32_t)(nt * BN + wave * 32);
   const uint32_t rowb = (uint32_t)(K >> 5) * PB32;
   const int sh = a.group_shift;
   const int n_grp = sh >= 8 ? 1 : 256 >> sh;                   // groups of 256 columns
@@ -319,12 +333,15 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   // (a row holds an even number of scales, so a pair of bf16 scales is one aligned dword)
   const uint32_t s_off = (wrow + n) * (uint32_t)a.w.sng * (SCB ? 2u : 4u) + hh * 4u, z_off = (wrow + n) * (uint32_t)a.w.ng + hh;
   const uint32_t as_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As;
-  const uint32_t wofs = NBUF * BM * 128 + (uint32_t)wave * (uint32_t)(Lds::FIT ? pair.wave_lds : Lds::WAVE);
+  const uint32_t wofs = Lds::ROWS + (uint32_t)wave * (uint32_t)(Lds::FIT ? pair.wave_lds : Lds::WAVE);
   const uint8_t* warea = As + wofs;
   const uint32_t wr = MODE == 0 ? 2 * (n & 15) + (n >> 4) : n;                 // the lane's row of the 32
   const uint32_t p_rd = wr * PROW + (FMT == 0 ? ((uint32_t)hh ^ ((wr >> 1) & 7u)) * 16 : (uint32_t)hh * PB32);
   typedef typename std::conditional<FMT == 0, u32x4, typename std::conditional<FMT == 1, u32x2, u32x3>::type>::type PlaneV;
   struct Planes { PlaneV m, l; };
+  struct Meta { uint32_t s, z; };
+  const uint32_t hb = sh == 5 ? hh : 0, odd_group = sh == 5 ? 0u : 1u;
+  const uint32_t s_rd = 2 * PLANE + wr * 4 + (SCB ? 0u : hb * 128u), z_rd = ZP_AT + wr * 4 + hb * 128u;
 
   f32x16 acc[NF];
 #pragma unroll
@@ -332,36 +349,48 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[i][r] = 0.0f;
 
-  // planes, scales and zero-points of columns 256 i .. 256 i + 255 (past the row's end: bytes of the next row, not used)
-  auto load_weights = [&](int ex, int i) __attribute__((always_inline)) {
+  // where an expert's planes, scales and zero-points are, in scalar registers (fetched from the arguments in the K loop they would make
+  // the wave wait for its LDS reads too)
+  struct Bases { const uint8_t *m, *l, *s, *z; uint32_t p_bytes, s_bytes, z_bytes; };
+  auto bases_of = [&](int ex) __attribute__((always_inline)) {
     const size_t ee = (size_t)uni(e + ex);
-    const u32x4 rm = pf_rsrc(a.w.msb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
-    const u32x4 rl = pf_rsrc(a.w.lsb + ee * a.w.plane_stride, (uint32_t)a.w.plane_stride);
-    const u32x4 rs = pf_rsrc(a.w.sc + ee * a.w.sc_stride, (uint32_t)a.w.sc_stride);
-    const u32x4 rz = pf_rsrc(a.w.zp + ee * a.w.zp_stride, (uint32_t)a.w.zp_stride);
+    Bases q{a.w.msb + ee * a.w.plane_stride, a.w.lsb + ee * a.w.plane_stride, a.w.sc + ee * a.w.sc_stride, a.w.zp + ee * a.w.zp_stride,
+            (uint32_t)a.w.plane_stride, (uint32_t)a.w.sc_stride, (uint32_t)a.w.zp_stride};
+    asm volatile("" : "+s"(q.m), "+s"(q.l), "+s"(q.s), "+s"(q.z), "+s"(q.p_bytes), "+s"(q.s_bytes), "+s"(q.z_bytes));
+    return q;
+  };
+  // planes, scales and zero-points of columns 256 i .. 256 i + 255 (past the row's end: bytes of the next row, not used)
+  auto load_meta = [&](const Bases& w, int i) __attribute__((always_inline)) {
+    const u32x4 rs = pf_rsrc(w.s, w.s_bytes), rz = pf_rsrc(w.z, w.z_bytes);
     const uint32_t g0 = (uint32_t)(i * 256) >> sh, lds = as_base + wofs;
     const int nsd = SCB ? (n_grp + 1) >> 1 : n_grp;
     for (int j = 0; j < nsd; j += 2) dma4(rs, s_off, (SCB ? (g0 >> 1) : g0) * 4u + j * 4u, lds + 2 * PLANE + j * 128u);
     for (int j = 0; j < n_grp; j += 2) dma1(rz, z_off, g0 + j, lds + ZP_AT + j * 128u);
+  };
+  // (direct loads u0 .. u1 - 1 of the 2 NPL that fetch both planes; range 0: nothing is fetched)
+  auto load_plane = [&](const Bases& w, int i, int u0, int u1, uint32_t range) __attribute__((always_inline)) {
+    const uint32_t lds = as_base + wofs;
 #pragma unroll
-    for (int q = 0; q < NPL; q++) {
-      const uint32_t so = (uint32_t)i * PROW + (uint32_t)(q / NPO) * PSTEP * rowb;
-      dma16(rm, p_off[q % NPO], so, lds + q * 1024u);
-      dma16(rl, p_off[q % NPO], so, lds + PLANE + q * 1024u);
+    for (int u = u0; u < u1; u++) {
+      const int q = u >> 1;
+      const u32x4 r = pf_rsrc((u & 1) ? w.l : w.m, range);
+      dma16(r, p_off[q % NPO], (uint32_t)i * PROW + (uint32_t)(q / NPO) * PSTEP * rowb, lds + (u & 1) * PLANE + q * 1024u);
     }
   };
-  load_weights(0, 0);                                   // on their way while the token rows are looked up
+  Bases wb = bases_of(0);
+  load_meta(wb, 0);                                      // on their way while the token rows are looked up
+  load_plane(wb, 0, 0, 2 * NPL, wb.p_bytes);
 
-  // ---- token rows: a wave's direct load q moves rows 8 (4 q + wave) .. + 7 of the tile, lane i the 16-byte
+  // ---- token rows: a wave's direct load q moves rows 8 (NW q + wave) .. + 7 of the tile, lane i the 16-byte
   // piece (i % 8) ^ (i / 8) of row i / 8 (of these eight), so that the operand reads, 32 rows of one piece, hit all banks.
   // MODE 0 gathers the rows of X (a row past the tile's last one repeats that row); MODE 1 reads consecutive
   // rows of H (past the last one: another tile's, or zeros from out of range).  Rows of the product are
   // independent and the epilogue stores none of the surplus ones.
-  constexpr int NA = MODE == 0 ? NF : 1;
-  uint32_t a_off[NA];
-#pragma unroll
-  for (int q = 0; q < NA; q++) {
-    const int r = (4 * q + wave) * 8 + (lane >> 3), c = (lane & 7) ^ (lane >> 3);
+  // (eight waves and an odd number of fragments: the last load is half a load of every wave, rows 4 wave .. of the last fragment)
+  constexpr int NA = MODE == 0 ? 4 * NF / NW : 1;
+  uint32_t a_off[NA], a_half = 0;
+  auto row_at = [&](int r) __attribute__((always_inline)) {
+    const int c = (lane & 7) ^ (r & 7);
     uint32_t src;
     if (MODE == 0) {
       const int rc = m0 + min(r, m_cnt - 1);
@@ -369,8 +398,11 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
     } else {
       src = (uint32_t)(row0 + m0 + r) * (uint32_t)a.d_ff;
     }
-    a_off[q] = src * 2u + c * 16;
-  }
+    return src * 2u + c * 16;
+  };
+#pragma unroll
+  for (int q = 0; q < NA; q++) a_off[q] = row_at((NW * q + wave) * 8 + (lane >> 3));
+  if (NW == 8 && nf > 4 && (nf & 1)) a_half = row_at(32 * (nf - 1) + 4 * wave + ((lane >> 3) & 3));
   // operand reads: lane (n, hh) takes columns 32 hh + 8 s .. + 7 of row n: piece (4 hh + s) ^ (n % 8)
   const uint32_t a_rd = n * 128 + (((4 * hh) ^ (n & 7)) * 16);
   // MODE 1: the weight of row tid of the tile, for the epilogue
@@ -380,8 +412,8 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   // codes of columns 8 s .. 8 s + 7 of the lane's 32 -> bf16 scale (q - zp).  With bf16 scales the K loop takes the codes as 1024 + q
   // (BIASED) and c0 = -(1024 + zp) scale; otherwise c0 = -zp scale.
   constexpr bool BIASED = SCB != 0;
-  auto expand = [&](auto biased_c, const PlaneV& m, const PlaneV& l, int s, float scale, float c0) __attribute__((always_inline)) {
-    uint32_t qe, qo;                          // codes of the even / odd columns, one per byte
+  // codes of the even / odd columns, one per byte
+  auto codes = [&](const PlaneV& m, const PlaneV& l, int s, uint32_t& qe, uint32_t& qo) __attribute__((always_inline)) {
     if constexpr (FMT == 0) {
       // (the planes hold n ^ 8 per nibble: taken back below)
       const uint32_t wm = m[s], wl = l[s];
@@ -411,36 +443,47 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       qe = qn & 0x0F0F0F0Fu;
       qo = (qn >> 4) & 0x0F0F0F0Fu;
     }
+  };
+  // weights of columns 2 b and 2 b + 1 of the eight
+  auto weights = [&](auto biased_c, uint32_t qe, uint32_t qo, int b, float scale, float c0) __attribute__((always_inline)) {
+    if constexpr (decltype(biased_c)::value) {
+      // the codes of two columns as the halves 1024 + q (exact in fp16), which one mixed-precision FMA each turns
+      // into s (1024 + q) - s (1024 + zp); a bf16 scale times 11 bits is exact in fp32, so this is s (q - zp) rounded once
+      const f16x2 q2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(qo, qe, 0x0C000C00u | ((4u + b) << 16) | b) ^ (FMT == 0 ? 0x64886488u : 0x64006400u));
+      return pack_bf16(fmaf((float)q2[0], scale, c0), fmaf((float)q2[1], scale, c0));
+    } else {
+      const uint32_t f = FMT == 0 ? 0x88888888u : 0u;
+      const float we = fmaf((float)(((qe ^ f) >> (8 * b)) & 0xFF), scale, c0);
+      const float wo = fmaf((float)(((qo ^ f) >> (8 * b)) & 0xFF), scale, c0);
+      return pack_bf16(we, wo);
+    }
+  };
+  auto expand = [&](auto biased_c, const PlaneV& m, const PlaneV& l, int s, float scale, float c0) __attribute__((always_inline)) {
+    uint32_t qe, qo;
+    codes(m, l, s, qe, qo);
     u32x4 out;
 #pragma unroll
-    for (int b = 0; b < 4; b++) {
-      if constexpr (decltype(biased_c)::value) {
-        // the codes of two columns as the halves 1024 + q (exact in fp16), which one mixed-precision FMA each turns
-        // into s (1024 + q) - s (1024 + zp); a bf16 scale times 11 bits is exact in fp32, so this is s (q - zp) rounded once
-        const f16x2 q2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(qo, qe, 0x0C000C00u | ((4u + b) << 16) | b) ^ (FMT == 0 ? 0x64886488u : 0x64006400u));
-        out[b] = pack_bf16(fmaf((float)q2[0], scale, c0), fmaf((float)q2[1], scale, c0));
-      } else {
-        const uint32_t f = FMT == 0 ? 0x88888888u : 0u;
-        const float we = fmaf((float)(((qe ^ f) >> (8 * b)) & 0xFF), scale, c0);
-        const float wo = fmaf((float)(((qo ^ f) >> (8 * b)) & 0xFF), scale, c0);
-        out[b] = pack_bf16(we, wo);
-      }
-    }
+    for (int b = 0; b < 4; b++) out[b] = weights(biased_c, qe, qo, b, scale, c0);
     return __builtin_bit_cast(bf16x8, out);
   };
   const int n_pass = MODE == 1 && a.dense_rows ? a.n_dense : 1;
   const std::integral_constant<bool, BIASED> biased{};
   auto kloop = [&](auto nf_c) __attribute__((always_inline)) {
     constexpr int F = decltype(nf_c)::value;
+    constexpr int NBUF = Lds::nbuf(F), STEP = F * 4096;      // row buffers, bytes of one
+    constexpr int RF = 4 * F / NW, RQ = RF + ((4 * F) % NW != 0);      // row loads of a step and wave (the last may be half a load)
     for (int ex = 0; ex < n_pass; ex++) {
       if (ex) __syncthreads();                          // every wave is done with the LDS rows of the last pass
       const u32x4 ra = pf_rsrc(MODE == 0 ? a.x : ex == 0 ? h : a.h_more + (size_t)(ex - 1) * a.dense_rows * a.d_ff, a.a_bytes);
-      auto load_rows = [&](int t) __attribute__((always_inline)) {
-        const uint32_t lds = as_base + (uint32_t)(t & (NBUF - 1)) * (BM * 128u);
+      auto load_rows = [&](int t, uint32_t buf, int q0, int q1) __attribute__((always_inline)) {
+        u32x4 r = ra;
+        r[2] = t < nk ? ra[2] : 0u;                     // past the last step nothing is fetched, but the load counts
 #pragma unroll
-        for (int q = 0; q < F; q++)
-          dma16(ra, a_off[MODE == 0 ? q : 0], (uint32_t)t * (PF_BK * 2) + (MODE == 0 ? 0u : (uint32_t)q * 64u * (uint32_t)a.d_ff),
-                lds + (uint32_t)(4 * q + wave) * 1024u);
+        for (int q = q0; q < q1; q++) {
+          const uint32_t lds = as_base + buf + (uint32_t)wave * 1024u + q * (NW * 1024u);
+          if (q < RF) dma16(r, a_off[MODE == 0 ? q < NA ? q : 0 : 0], (uint32_t)t * (PF_BK * 2) + (MODE == 0 ? 0u : (uint32_t)q * (NW * 16u) * (uint32_t)a.d_ff), lds);
+          else dma16_half(r, a_half, (uint32_t)t * (PF_BK * 2), lds - (uint32_t)wave * 512u);
+        }
       };
       auto read_planes = [&](int b, Planes& p) __attribute__((always_inline)) {
         const uint8_t* q = warea + (FMT == 0 ? p_rd ^ (b * 32u) : p_rd + b * 2u * PB32);
@@ -453,93 +496,150 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
           p.l = *(const PlaneV*)(q + PLANE);
         }
       };
-      // scale and offset (weight = scale * code + offset) of the lane's row in step t
-      auto read_meta = [&](int t, float& sc, float& c0) __attribute__((always_inline)) {
-        const uint32_t g = (uint32_t)(t * PF_BK + (sh == 5 ? 32 * hh : 0)) >> sh, gl = g & (uint32_t)(n_grp - 1);      // group, its number inside the 256 columns
-        const uint32_t sw = *(const uint32_t*)(warea + 2 * PLANE + (SCB ? gl >> 1 : gl) * 128u + wr * 4);
-        const uint32_t zp = *(const uint32_t*)(warea + ZP_AT + gl * 128u + wr * 4) & 0xFFu;
-        sc = SCB ? __uint_as_float((g & 1u) ? sw & 0xFFFF0000u : sw << 16) : __uint_as_float(sw);
-        c0 = -(float)((BIASED ? 1024u : 0u) + zp) * sc;
+      // scale and zero-point of the lane's row in a step, as they lie in LDS; scale_of: scale and offset (weight = scale * code + offset).
+      // Groups of 32: the two halves of a wave are in different groups (hb).
+      auto read_meta = [&](int b, Meta& m) __attribute__((always_inline)) {
+        const uint32_t gl = (uint32_t)(b * PF_BK) >> sh;      // group inside the 256 columns
+        m.s = *(const uint32_t*)(warea + s_rd + (SCB ? gl >> 1 : gl) * 128u);
+        m.z = *(const uint32_t*)(warea + z_rd + gl * 128u);
       };
-      // bf: the first quarter's weights, already expanded; returns those of the next step.  While a quarter is multiplied, the
-      // token rows of the next one are read and its weights expanded; the schedule deals one read and a fifth (a third, ...)
-      // of the expansion to every product, because a wave issues in order and gets less than every second slot of its SIMD.
-      auto multiply = [&](auto last_c, int t, bf16x8 bf, const Planes& p, float sc, float c0, const Planes& pn, float scn, float c0n) __attribute__((always_inline)) {
-        const uint8_t* rows = As + (t & (NBUF - 1)) * (BM * 128);
-        bf16x8 af[2][F];
-#pragma unroll
-        for (int i = 0; i < F; i++) af[0][i] = *(const bf16x8*)(rows + a_rd + i * 4096);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-          if (s < 3)
-#pragma unroll
-            for (int i = 0; i < F; i++) af[(s + 1) & 1][i] = *(const bf16x8*)(rows + (a_rd ^ ((s + 1) * 16)) + i * 4096);
-          bf16x8 bn = bf;
-          if (s < 3) bn = expand(biased, p.m, p.l, s + 1, sc, c0);
-          else if (!decltype(last_c)::value) bn = expand(biased, pn.m, pn.l, 0, scn, c0n);      // (the last step of a chunk does not have the next planes yet)
-#pragma unroll
-          for (int i = 0; i < F; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][i], bf, acc[i], 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < F; i++) {
-            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                   // a product
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                 // an LDS read
-            __builtin_amdgcn_sched_group_barrier(0x2, (26 + F - 1) / F, 0);    // vector instructions
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          bf = bn;
+      auto scale_of = [&](int t, const Meta& m, float& sc, float& c0) __attribute__((always_inline)) {
+        if (SCB) {                                      // (two bf16 scales share a dword)
+          const uint32_t left = (16u - 16u * (((uint32_t)(t * PF_BK) >> sh) & odd_group)) - 16u * hb;
+          sc = __uint_as_float((m.s << left) & 0xFFFF0000u);
+        } else {
+          sc = __uint_as_float(m.s);
         }
-        return bf;
+        c0 = -(float)((BIASED ? 1024u : 0u) + (m.z & 0xFFu)) * sc;
       };
-      // The direct loads are the only memory operations of the loop, so the waits count them.  Every wave has its share
-      // of the rows of step t in LDS (and, every fourth step, its weights) before the barrier at the top of step t, and
-      // has finished step t - 1, whose buffer the rows of step t + AHEAD then overwrite.  Loads complete in order, and
-      // younger than the rows of step t are only those of the next AHEAD - 1 steps and, in the first AHEAD steps after they
-      // were sent for, the next weights (at least 2 * NPL loads): so many may be left out.  Near the end, where there
-      // are fewer, nothing is.
-      if (ex) load_weights(ex, 0);
+      // A direct load keeps the texture path busy for 13 cycles or more and a wave for several issue slots, so they are dealt out to the products: a
+      // step's rows to those of Q3 behind the barrier; the next 256 columns' weights, once the present ones have left LDS for the registers, to Q1
+      // and Q2 of a chunk's first step and Q0 .. Q2 of its second (WS: loads sent before each of these quarters, metadata first).  Tall tiles
+      // (two row buffers) take the planes of steps 2 and 3 to registers one step later, which saves eight, and send for the next in step 1.
+      constexpr int WB = NBUF == 2 ? 1 : 0;
+      constexpr int WS[6] = {0, NBUF > 2 ? NPL / 2 : NPL, NBUF > 2 ? NPL : 2 * NPL, NBUF > 2 ? (4 * NPL + 2) / 3 : 2 * NPL, NBUF > 2 ? (5 * NPL + 2) / 3 : 2 * NPL, 2 * NPL};
+      bf16x8 af[F], bf;
+      Planes p[4];
+      Meta mt[4];
+      float sc, c0;                                     // of the step whose weights are being expanded
+      // One quarter: the F products of 16 columns.  Behind every product come the read of the token rows of its fragment for the next
+      // quarter (at `next`) and a share of the expansion of that quarter's weights: a wave issues in order, and two waves that
+      // leave a barrier together would otherwise both multiply and then both expand.  `extra` adds the direct loads.  In the last quarter of
+      // a step (ARRIVE >= 0: what may be outstanding) the next rows are those of another step: a barrier comes first, behind the second
+      // product, when the last reads of this step are back.
+      auto quarter = [&](auto arrive_c, const uint8_t* next, const Planes& pn, int sn, auto extra) __attribute__((always_inline)) {
+        constexpr int ARRIVE = decltype(arrive_c)::value, BI = ARRIVE < 0 ? -1 : F > 1 ? 1 : 0;
+        uint32_t qe, qo;
+        u32x4 bn;
 #pragma unroll
-      for (int t = 0; t < AHEAD; t++)
-        if (t < nk) load_rows(t);
-      auto arrive = [&](auto left_c, bool all) __attribute__((always_inline)) {
-        if (all) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(decltype(left_c)::value) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      };
-      constexpr int YOUNG = (AHEAD - 1) * F;
-      for (int t = 0; t < nk; t += 4) {
-        arrive(std::integral_constant<int, YOUNG>(), t + AHEAD - 1 < nk);
-        if (t + AHEAD < nk) load_rows(t + AHEAD);
-        Planes p[4];
-        float sc[4], c0[4];
+        for (int i = 0; i < F; i++) {
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf, acc[i], 0, 0, 0);
+          if (i == BI) {
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ARRIVE < 0 ? 0 : ARRIVE) : "memory");
 #pragma unroll
-        for (int b = 0; b < 4; b++) { read_planes(b, p[b]); read_meta(t + b, sc[b], c0[b]); }
-        // (the weights have left LDS for the registers: the next ones may come)
-#pragma unroll
-        for (int b = 0; b < 4; b++) asm volatile("" : "+v"(sc[b]), "+v"(c0[b]), "+v"(p[b].m), "+v"(p[b].l));
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const bool more = t + 4 < nk;
-        if (more) load_weights(ex, (t >> 2) + 1);
-        bf16x8 bf = expand(biased, p[0].m, p[0].l, 0, sc[0], c0[0]);
-        bf = multiply(std::false_type(), t, bf, p[0], sc[0], c0[0], p[1], sc[1], c0[1]);
-        auto next = [&](auto b_c) __attribute__((always_inline)) {
-          constexpr int b = decltype(b_c)::value, n1 = b < 3 ? b + 1 : b;
-          if (t + b < nk) {
-            arrive(std::integral_constant<int, YOUNG + (b <= AHEAD ? 2 * NPL : 0)>(), more && t + b + AHEAD - 1 < nk);
-            if (t + b + AHEAD < nk) load_rows(t + b + AHEAD);
-            bf = multiply(std::integral_constant<bool, b == 3>(), t + b, bf, p[b], sc[b], c0[b], p[n1], sc[n1], c0[n1]);
+            for (int j = 0; j <= BI; j++) af[j] = *(const bf16x8*)(next + j * 4096);
+          } else if (i > BI) {
+            af[i] = *(const bf16x8*)(next + i * 4096);
           }
+          extra(i);
+#pragma unroll
+          for (int j = 0; j < 5; j++)
+            if (j * F / 5 == i) {
+              if (j == 0) {
+                codes(pn.m, pn.l, sn, qe, qo);
+                asm volatile("" : "+v"(qe), "+v"(qo));  // (pinned here: without it the work sinks to where it is used)
+              } else {
+                uint32_t w = weights(biased, qe, qo, j - 1, sc, c0);
+                asm volatile("" : "+v"(w));
+                bn[j - 1] = w;
+              }
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        bf = __builtin_bit_cast(bf16x8, bn);
+      };
+      const std::integral_constant<int, -1> inside{};
+      if (ex) { wb = bases_of(ex); load_meta(wb, 0); load_plane(wb, 0, 0, 2 * NPL, wb.p_bytes); }
+      uint32_t cur = 0;                                 // buffer of the present step
+#pragma unroll
+      for (int t = 0; t < NBUF; t++) load_rows(t, t * STEP, 0, RQ);
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NBUF - 1) * RQ) : "memory");
+#pragma unroll
+      for (int b = 0; b < 4; b++) { read_planes(b, p[b]); read_meta(b, mt[b]); }
+      scale_of(0, mt[0], sc, c0);
+#pragma unroll
+      for (int i = 0; i < F; i++) af[i] = *(const bf16x8*)(As + a_rd + i * 4096);
+      bf = expand(biased, p[0].m, p[0].l, 0, sc, c0);
+      for (int t0 = 0; t0 < nk; t0 += 4) {
+        const int c1 = (t0 >> 2) + 1;
+        const uint32_t wrange = t0 + 4 < nk ? wb.p_bytes : 0u;      // (the last 256 columns: nothing more to fetch)
+        auto step = [&](auto b_c) __attribute__((always_inline)) {
+          constexpr int b = decltype(b_c)::value, n1 = (b + 1) & 3;
+          const int t = t0 + b;
+          uint32_t at = cur + a_rd;                     // (buffers are multiples of 128 bytes: the quarters differ by an exclusive or)
+          asm volatile("" : "+v"(at));
+          const uint32_t nxt = cur == (NBUF - 1) * STEP ? 0 : cur + STEP;
+          // the quarter's share w of the weights, dealt to its products
+          auto deal = [&](int w, int i) __attribute__((always_inline)) {
+            const int n_w = WS[w + 1] - WS[w];
+            load_plane(wb, c1, WS[w] + n_w * i / F, WS[w] + n_w * (i + 1) / F, wrange);
+          };
+          quarter(inside, As + (at ^ 16u), p[b], 1, [&](int i) __attribute__((always_inline)) {
+            if (NBUF > 2 && b == 1) deal(2, i);
+            if (NBUF == 2 && b == 1) {
+              if (i == 0) { read_planes(2, p[2]); read_meta(2, mt[2]); }
+              if (i == 1) { read_planes(3, p[3]); read_meta(3, mt[3]); }
+            }
+          });
+          if (b == WB) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the weights have left LDS for the registers: the next ones may come
+          quarter(inside, As + (at ^ 32u), p[b], 2, [&](int i) __attribute__((always_inline)) {
+            if (b == WB && i == 0) load_meta(wb, c1);
+            if (b == WB) deal(0, i);
+            if (b == WB + 1 && NBUF > 2) deal(3, i);
+          });
+          if (b == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * RQ) : "memory");      // the next weights are there
+          quarter(inside, As + (at ^ 48u), p[b], 3, [&](int i) __attribute__((always_inline)) {
+            if (b == WB) deal(1, i);
+            if (b == WB + 1 && NBUF > 2) deal(4, i);
+            if (b == 3 && i == 0) { read_planes(0, p[0]); read_meta(0, mt[0]); }
+          });
+          // younger than the rows of step t + 1: those of NBUF - 2 steps, and of the next weights what was sent after those rows
+          constexpr int YW = NBUF == 2 ? (b == WB ? 2 + WS[5] : 0)
+                                       : b == 0 ? 2 + WS[2] : b < NBUF - 1 ? 2 + WS[5] : b == NBUF - 1 ? WS[5] - WS[2] : 0;
+          scale_of(t + 1, mt[n1], sc, c0);
+          quarter(std::integral_constant<int, (NBUF - 2) * RQ + YW>(), As + nxt + a_rd, p[n1], 0, [&](int i) __attribute__((always_inline)) {
+            constexpr int G0 = F > 2 ? 1 : F - 1;       // (behind the barrier)
+            if (i >= G0) load_rows(t + NBUF, cur, RQ * (i - G0) / (F - G0), RQ * (i - G0 + 1) / (F - G0));
+            if (b == 3)
+#pragma unroll
+              for (int j = 1; j < (NBUF == 2 ? 2 : 4); j++)
+                if ((j - 1) * F / 3 == i) { read_planes(j, p[j]); read_meta(j, mt[j]); }
+          });
+          cur = nxt;
         };
-        next(std::integral_constant<int, 1>());
-        next(std::integral_constant<int, 2>());
-        next(std::integral_constant<int, 3>());
+        step(std::integral_constant<int, 0>());
+        if (t0 + 1 < nk) step(std::integral_constant<int, 1>());
+        if (t0 + 2 < nk) step(std::integral_constant<int, 2>());
+        if (t0 + 3 < nk) step(std::integral_constant<int, 3>());
       }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (no load is on its way to LDS any more)
     }
   };
-  if (NF >= 5 && nf == 5) kloop(std::integral_constant<int, (NF >= 5 ? 5 : 1)>());
-  else if (NF >= 4 && nf == 4) kloop(std::integral_constant<int, (NF >= 4 ? 4 : 1)>());
-  else if (NF >= 3 && nf == 3) kloop(std::integral_constant<int, (NF >= 3 ? 3 : 1)>());
-  else if (NF >= 2 && nf == 2) kloop(std::integral_constant<int, (NF >= 2 ? 2 : 1)>());
-  else kloop(std::integral_constant<int, 1>());
+  // (a tall tile's rows beyond its last fragment are a few repeated ones: below four fragments nothing is gained by leaving them out)
+  if constexpr (NF == 8) {
+    if (nf == 8) kloop(std::integral_constant<int, 8>());
+    else if (nf == 7) kloop(std::integral_constant<int, 7>());
+    else if (nf == 6) kloop(std::integral_constant<int, 6>());
+    else if (nf == 5) kloop(std::integral_constant<int, 5>());
+    else kloop(std::integral_constant<int, 4>());
+  } else {
+    if (NF >= 5 && nf == 5) kloop(std::integral_constant<int, (NF >= 5 ? 5 : 1)>());
+    else if (NF >= 4 && nf == 4) kloop(std::integral_constant<int, (NF >= 4 ? 4 : 1)>());
+    else if (NF >= 3 && nf == 3) kloop(std::integral_constant<int, (NF >= 3 ? 3 : 1)>());
+    else if (NF >= 2 && nf == 2) kloop(std::integral_constant<int, (NF >= 2 ? 2 : 1)>());
+    else kloop(std::integral_constant<int, 1>());
+  }
 
   // Scales from 2^128 / 1279 on overflow c0 of the biased form: such a weight is -inf, and any product with it leaves the sums of
   // its row not finite.  So a wave that finds its first sums not finite looks for such scales among its rows and, if there
@@ -552,8 +652,8 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
       asm volatile("" : "+s"(args));
       const auto* b = &args->g[second ? 1 : 0];
       const int Kb = MODE == 0 ? b->d_model : b->d_ff, shb = b->group_shift, passes = MODE == 1 && b->dense_rows ? b->n_dense : 1;
-      const uint32_t row = (uint32_t)(nt * PF_BN + wave * 32) + wr;
-      const bool inside = nt * PF_BN + wave * 32 < (MODE == 0 ? 2 * b->d_ff : b->d_model);      // (all 32 rows of a wave or none)
+      const uint32_t row = (uint32_t)(nt * BN + wave * 32) + wr;
+      const bool inside = nt * BN + wave * 32 < (MODE == 0 ? 2 * b->d_ff : b->d_model);      // (all 32 rows of a wave or none)
       auto scale_at = [&](size_t ee, uint32_t g) { return bf16_bits_to_f32(((const uint16_t*)(b->w.sc + ee * b->w.sc_stride))[row * (uint32_t)b->w.sng + g]); };
       float top = 0.0f;
       if (inside)
@@ -603,24 +703,42 @@ __global__ __launch_bounds__(PF_NT, NF == 1 ? 3 : 2) void grouped_gemm_kernel(Ge
   if constexpr (MODE == 0) {
     // registers r and r + 8 of lanes 0 .. 15 (gate) and 16 .. 31 (up) are exchanged so that a lane holds gate and up of one
     // element; the bf16 tile is then turned in LDS, so that a row of it, 64 columns, leaves as one 128-byte line
-    constexpr int HLD = 144;                            // bytes of a row in LDS
+    constexpr int HLD = NW * 32 + 16, HP = NW * 2;      // bytes of a row in LDS, 16-byte pieces of its columns
     const uint32_t col = (uint32_t)wave * 16 + (n & 15), rb = 4 * hh + 16 * (n >> 4);
 #pragma unroll
     for (int i = 0; i < NF; i++) {
       if (i >= nf) continue;
+      float lo = 0.0f;
 #pragma unroll
       for (int r = 0; r < 8; r++) {
         const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][r]), __float_as_uint(acc[i][r + 8]), false, false);
-        const float g = __uint_as_float(sw[0]), u = __uint_as_float(sw[1]);
-        const float hv = g / (1.0f + __expf(-g)) * u;      // (a true division: the reciprocal unit flushes what is below 2^-126, gates from -87.4 down)
+        acc[i][r] = __uint_as_float(sw[0]);             // gate
+        acc[i][r + 8] = __uint_as_float(sw[1]);         // up
+        lo = fminf(lo, acc[i][r]);
+      }
+      auto put = [&](int r, float hv) __attribute__((always_inline)) {
         *(uint16_t*)(As + (i * 32 + 8 * (r >> 2) + (r & 3) + rb) * HLD + col * 2) = (uint16_t)pack_bf16(hv, hv);
+      };
+      // u g / (1 + e^-g): the reciprocal unit's result and one Newton step (8 instructions instead of a division's 18; this is half of the
+      // epilogue), but a true division where a gate is so low that the reciprocal, below 2^-126, would be taken for 0 (from -87.4 down)
+      if (__any(lo < -80.0f)) {
+#pragma unroll
+        for (int r = 0; r < 8; r++) put(r, acc[i][r] / (1.0f + __expf(-acc[i][r])) * acc[i][r + 8]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 8; r++) {
+          const float d = 1.0f + __expf(-acc[i][r]), q = __builtin_amdgcn_rcpf(d);
+          put(r, acc[i][r] * fmaf(fmaf(-d, q, 1.0f), q, q) * acc[i][r + 8]);
+        }
       }
     }
     __syncthreads();
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(h + row_first * a.d_ff, 0, (int)((uint32_t)m_cnt * (uint32_t)a.d_ff * 2u), 0x00020000);
     for (int q = 0; q < nf; q++) {
-      const uint32_t r = q * 32 + (tid >> 3), c = tid & 7;
-      __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)(As + r * HLD + c * 16), ro, (int)((r * (uint32_t)a.d_ff + nt * (PF_BN / 2) + c * 8) * 2u), 0, 0);
+      const uint32_t r = q * 32 + tid / HP, c = tid % HP;
+      // (a tile of 128 columns may reach past the matrix)
+      const uint32_t at = nt * (BN / 2) + c * 8 < (uint32_t)a.d_ff ? (r * (uint32_t)a.d_ff + nt * (BN / 2) + c * 8) * 2u : 0xFFFFFFF0u;
+      __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)(As + r * HLD + c * 16), ro, (int)at, 0, 0);
     }
   } else {
     float* row_wt = (float*)As;
@@ -696,15 +814,15 @@ static int launch_gemm_t(smoe_ctx* ctx, GemmPair& g, int grid) {
   typedef PfLds<SCB, FMT, NF> Lds;
   g.zp_at = 2 * Lds::PLANE + (nsd + 1) / 2 * 256;
   g.wave_lds = g.zp_at + (n_grp + 1) / 2 * 256;
-  const size_t lds = (size_t)Lds::ROWS + 4 * (size_t)(Lds::FIT ? g.wave_lds : Lds::WAVE);
+  const size_t lds = (size_t)Lds::ROWS + Lds::NW * (size_t)(Lds::FIT ? g.wave_lds : Lds::WAVE);
   if (lds > 64u * 1024u) {       // beyond the default per-work-group limit: granted once per device
-    size_t& granted = ctx->gemm_lds_granted[((MODE * 2 + SCB) * 3 + FMT) * 4 + (NF == 5 ? 3 : NF - 1)];
+    size_t& granted = ctx->gemm_lds_granted[((MODE * 2 + SCB) * 3 + FMT) * 5 + (NF == 8 ? 4 : NF == 5 ? 3 : NF - 1)];
     if (lds > granted) {
       HIPCHK(ctx, hipFuncSetAttribute((const void*)grouped_gemm_kernel<MODE, SCB, FMT, NF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
       granted = lds;
     }
   }
-  grouped_gemm_kernel<MODE, SCB, FMT, NF><<<grid, PF_NT, lds, ctx->stream>>>(g);
+  grouped_gemm_kernel<MODE, SCB, FMT, NF><<<grid, 64 * Lds::NW, lds, ctx->stream>>>(g);
   return SMOE_OK;
 }
 template <int MODE, int NF>
@@ -719,17 +837,62 @@ static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf
   if (nf == 1) return launch_gemm_nf<MODE, 1>(ctx, g, sc_bf16, bits, grid);
   if (nf == 2) return launch_gemm_nf<MODE, 2>(ctx, g, sc_bf16, bits, grid);
   if (nf == 3) return launch_gemm_nf<MODE, 3>(ctx, g, sc_bf16, bits, grid);
-  return launch_gemm_nf<MODE, 5>(ctx, g, sc_bf16, bits, grid);
+  if (nf == 5) return launch_gemm_nf<MODE, 5>(ctx, g, sc_bf16, bits, grid);
+  return launch_gemm_nf<MODE, 8>(ctx, g, sc_bf16, bits, grid);
 }
-// Tile height for experts of `rows` rows on average: one tile for nearly every expert (mean plus one and a half
-// standard deviations of even routing) if five fragments can do that, else the tallest tile.  There is no tile of four: with
-// 97 - 116 rows per expert it gains nothing (60 experts of d_model 2048, d_ff 1408: 214.0 us against 213.5 at 97 rows, 228.5 against
-// 229.6 at 110) or loses (64 such experts 226.8 -> 238.3 us at 103 rows; d_model 1024, d_ff 512 69 -> 81 us at 112), because more experts
-// need a second one.  The mean is all the host knows.  Where routing is skewed (popularity falling as 1 / rank^1.1 or 1 / rank^2)
-// the popular experts take several short tiles: 500 / 2048 tokens top-6 over 64 experts 203 / 474 us even, 230 / 466 and 237 / 500 skewed.
-static int pick_nf(double rows) {
-  const double want = rows + 1.5 * sqrt(rows);
-  return want <= 32.0 ? 1 : want <= 64.0 ? 2 : want <= 96.0 ? 3 : 5;
+// Tile height, in fragments of 32 rows.  Experts of few rows (up to 64 with one and a half standard deviations of even routing) take one
+// tile of 32 or 64: their weights' bytes bound them.  Above that three heights compete: 96 and 160 rows with four waves, two work-groups
+// per CU, and 256 with eight, one per CU, which expands a weight once for more rows but fills the chip in larger pieces.  Which of them is
+// faster hangs on how many tiles there are, so it is estimated, in cycles, from what the K loops measured: a step of a 256-row tile
+// (256 weight rows) takes 1150 + 190 F cycles at F fragments (1785 at 4, 2657 at 8), two of the four-wave tiles side by side 1350 + 113 F
+// (1601 at 3, 1826 at 5, not counting the weights' share of HBM), start and end of a tile 22000 and 9000.  Chosen so, microseconds per layer (160 / 256 rows): 60 experts of
+// d_model 2048, d_ff 1408, top-4, 2200 tokens 316 / 297, with a shared expert of 5632 and 4096 tokens 786 / 725; 24 experts of d_model 2560,
+// d_ff 2048, top-8, 1000 tokens 399 / 330; but 8 such experts, top-2, shared 2816, 1500 tokens 165 / 188; 16 of d_model 1024, d_ff 1024,
+// top-4, 1000 tokens 67 / 80.  There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second
+// one.  The mean is all the host knows; the spread assumed around it (three tenths) is that of mildly skewed routing.
+struct GemmSize { double experts, rows; int N, K; bool even; };      // even: every expert has just these rows
+static double gemm_cycles(int nf, const GemmSize* g, int n, int n_cu) {
+  const bool tall = nf > 5;
+  double items = 0, work = 0, longest = 0;
+  for (int i = 0; i < n; i++) {
+    const double h = 32.0 * nf, spread = 0.3 * g[i].rows + 1.0;
+    double tiles = ceil(g[i].rows / h);                 // of an expert, on average
+    if (!g[i].even && g[i].rows <= 64.0 * h) {
+      tiles = 1.0;
+      for (int j = 1; j * h < 2.0 * g[i].rows; j++) tiles += 1.0 / (1.0 + exp(1.7 * (j * h - g[i].rows) / spread));
+    }
+    const double f = std::min((double)nf, g[i].rows / (32.0 * tiles) + 0.5), steps = g[i].K / 64.0;
+    const double it = g[i].experts * tiles * ((g[i].N + 32 * pf_waves(nf) - 1) / (32 * pf_waves(nf)));
+    const double c = tall ? steps * (1150.0 + 190.0 * f) + 22e3 : steps * (1350.0 + 113.0 * f) + 9e3;
+    items += it;
+    work += it * c;
+    longest = std::max(longest, c);
+  }
+  // rounds: how often the chip is filled; the more there are, the less an unfilled last one counts
+  const double q = items / (tall ? n_cu : 2 * n_cu), whole = floor(q), part = q - whole;
+  const double rounds = tall ? (q <= 3.0 ? ceil(q) : q + 0.4) : whole + (part <= 0.0 ? 0.0 : part <= 0.5 ? 0.8 : 1.0) + (q > 2.0 ? 0.3 : 0.0);
+  return std::max(work / items * rounds, longest * (tall || q > 1.0 ? 1.0 : 0.8));
+}
+// both GEMMs of up to two sets of experts in common launches: {gate/up, down} of each
+static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, double* cycles) {
+  *cycles = 0;
+  const double want = g[0][0].rows + 1.5 * sqrt(g[0][0].rows);
+  if (want <= 64.0) return want <= 32.0 ? 1 : 2;
+  int best = 0;
+  for (int nf : {3, 5, 8}) {
+    if (nf == 8) {                                      // (its tiles have to fill the chip one and a half times over: less is left to the estimate's error)
+      double items = 0;
+      for (int i = 0; i < n; i++) items += g[i][0].experts * ceil(g[i][0].rows / 256.0) * ((g[i][0].N + 255) / 256);
+      if (items < 1.5 * n_cu) break;
+    }
+    double c = 0;
+    for (int m = 0; m < 2; m++) {
+      GemmSize s[2] = {g[0][m], g[n - 1][m]};
+      c += gemm_cycles(nf, s, n, n_cu);
+    }
+    if (!best || c < *cycles) { best = nf; *cycles = c; }
+  }
+  return best;
 }
 
 struct PrefillLayout { size_t rows, pos, h, o, gamma, h_s, o_s, total; };
@@ -799,7 +962,19 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
 
   RouteArgs ra{E, k, d, logits_dev, x_dev, w_router_dev, nullptr, norm_topk, routed_scale, nullptr, idx_dev, w_dev};
   { const int rc = smoe_launch_route(ctx, ra, T, SMOE_BF16); if (rc) return rc; }
-  const int nf = pick_nf((double)T * k / E), bm = 32 * nf;
+  const GemmSize sizes[2][2] = {{{(double)E, (double)T * k / E, 2 * f, d, false}, {(double)E, (double)T * k / E, d, f, false}},
+                                {{shared ? (double)shared->desc.n_experts : 0.0, (double)T, 2 * f_s, d, true}, {1.0, (double)T, d, shared ? f_s * shared->desc.n_experts : 0, true}}};
+  double c_r, c_s = 0, c_both = 0;
+  int nf = pick_nf(sizes, 1, ctx->n_cu, &c_r);
+  const int nfs = shared ? pick_nf(sizes + 1, 1, ctx->n_cu, &c_s) : 0;
+  // taller tiles: one height for both sets, in common launches, if that is estimated to be no slower
+  const bool same = shared && shared->dev.sc_bf16 == routed->dev.sc_bf16 && shared->dev.bits == routed->dev.bits;
+  bool join = false;
+  if (same && nf >= 3 && nfs >= 3) {
+    const int nfb = pick_nf(sizes, 2, ctx->n_cu, &c_both);
+    if (c_both <= c_r + c_s + 30e3) { nf = nfb; join = true; }      // (two launches less)
+  }
+  const int bm = 32 * nf;
   float* gamma = shared ? (float*)(s + L.gamma) : nullptr;
   group_kernel<<<E + (shared ? (T + GR_THREADS / 64 - 1) / (GR_THREADS / 64) : 0), GR_THREADS, 0, st>>>(
       idx_dev, T * k, E, hist_dev, rows, pos, (const uint16_t*)x_dev, (const uint16_t*)shared_gate_w_dev, T, d, gamma);
@@ -817,8 +992,9 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
   GemmPair gu{}, dn{};
   gu.g[1] = dn.g[1] = g;
   gu.g[1].a_bytes = (uint32_t)((size_t)T * d * 2); dn.g[1].a_bytes = (uint32_t)((size_t)T * k * f * 2);      // (below 4 GiB: checked above)
-  gu.g[1].w = routed->dev.gu; gu.g[1].n_col_tiles = (2 * f + PF_BN - 1) / PF_BN;
-  dn.g[1].w = routed->dev.dn; dn.g[1].n_col_tiles = (d + PF_BN - 1) / PF_BN;
+  gu.g[1].w = routed->dev.gu; const int bn = 32 * pf_waves(nf);
+  gu.g[1].n_col_tiles = (2 * f + bn - 1) / bn;
+  dn.g[1].w = routed->dev.dn; dn.g[1].n_col_tiles = (d + bn - 1) / bn;
   const int gu_grid = grid_of(mt, gu.g[1].n_col_tiles), dn_grid = grid_of(mt, dn.g[1].n_col_tiles);
   float* o_s = nullptr;
   if (!shared) {
@@ -833,16 +1009,14 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
     q.x = (const uint16_t*)x_dev; q.h = (uint16_t*)(s + L.h_s); q.o = o_s; q.wgt = gamma; q.E = shared->desc.n_experts; q.k = 1; q.d_model = d; q.d_ff = f_s;
     q.dense_rows = T; q.super = 8;
     const int ns = shared->desc.n_experts;
-    const bool same = shared->dev.sc_bf16 == scb && shared->dev.bits == bits;
     // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
     // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both
     // want the same tile height, or if at the routed experts' (lower) height there is little to expand: a dense tile
     // expands its weights again, 600 million of them in about 55 us over the chip, which is what launches of their own lose to
     // their empty ends.  64 experts of d_ff 512, one shared of 1024, d_model 1024, 500 tokens: 101 -> 72 us; 96 experts, two
     // shared of 3840, d_model 2560, 500 tokens, all joined, would be 482 -> 515.
-    const int nfs = pick_nf((double)T);
     const double again = 3.0 * d * f_s * shared->desc.n_experts * ((T + bm - 1) / bm);
-    const bool join = same && (nf == nfs || T <= 8 * bm || (T <= 24 * bm && again <= 600e6));
+    if (same && (nf < 3 || nfs < 3)) join = nf == nfs || T <= 8 * bm || (T <= 24 * bm && again <= 600e6);
     // H of one shared expert has its own place.  That of others waits in Y, which nothing else writes before the last
     // kernel, if Y is not X and they fit there; else in the rows of O until the routed experts' down GEMM
     // writes those: then the shared experts' down GEMM comes before it, and as many experts as fit are worked out together.
@@ -854,11 +1028,11 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
     for (int e0 = 0; e0 < ns; e0 += at_once) {
       q.dense_expert = e0; q.n_dense = std::min(at_once, ns - e0); q.accumulate = e0 > 0;
       const bool j0 = join && e0 == 0, j1 = j0 && (in_y || ns == 1);
-      const int nq = j0 ? nf : nfs, rt = (T + 32 * nq - 1) / (32 * nq);
+      const int nq = j0 ? nf : nfs, bq = 32 * pf_waves(nq), rt = (T + 32 * nq - 1) / (32 * nq);
       GemmArgs qg = q, qd = q;
       qg.a_bytes = (uint32_t)((size_t)T * d * 2); qd.a_bytes = (uint32_t)((size_t)T * f_s * 2);
-      qg.w = shared->dev.gu; qg.n_col_tiles = (2 * f_s + PF_BN - 1) / PF_BN;
-      qd.w = shared->dev.dn; qd.n_col_tiles = (d + PF_BN - 1) / PF_BN;
+      qg.w = shared->dev.gu; qg.n_col_tiles = (2 * f_s + bq - 1) / bq;
+      qd.w = shared->dev.dn; qd.n_col_tiles = (d + bq - 1) / bq;
       const int gg = grid_of(rt * q.n_dense, qg.n_col_tiles), gd = grid_of(rt, qd.n_col_tiles);
       if (j0) {
         gu.g[0] = qg; gu.nb0 = gg;

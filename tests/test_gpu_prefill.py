@@ -117,6 +117,39 @@ def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
 
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank,std", [
+    (2999, 16, 4, 1024, 1024, 128, 0, 0, (8, 4), "bf16", 0.02),    # three tiles per expert, seven and eight fragments
+    (2501, 24, 4, 1088, 1088, 64, 0, 0, (8, 4), "bf16", 0.05),     # 17 K steps; a last column tile of 64 outputs
+    (2501, 24, 4, 1088, 1088, 32, 0, 0, (8, 4), "f32", 0.05),      # fp32 scales, groups of 32
+    (2003, 24, 6, 1536, 1024, 32, 0, 0, (6, 3), "bf16", 0.3),      # skewed routing: four to eight fragments
+    (2003, 24, 6, 1536, 1024, 256, 0, 0, (4, 2), "bf16", 0.3),
+    (1803, 48, 4, 2048, 1472, 128, 0, 0, (8, 4), "bf16", 0.02),    # one tile for most experts: four to six fragments
+    (3001, 24, 6, 1088, 1472, 64, 1, 960, (8, 4), "bf16", 0.05),   # a shared expert's dense tiles in the same launches
+])
+def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, std):
+    """Tiles of 256 rows (eight waves), which a layer takes when they fill the chip, against the 32- and 64-row tiles of the same
+    tokens in small calls: a row's sums run in the same order at every tile height, so the outputs are the same bits."""
+    say("prefill tall tiles", T, E, k, d, f, G, n_sh, f_s, nest, bank)
+    g = torch.Generator(device="cuda").manual_seed(77)
+    draw = lambda *s: torch.randn(s, generator=g, device="cuda")
+    dt = torch.float32 if bank == "f32" else torch.bfloat16
+
+    def make(n, ff):
+        b = B.Bank(ctx, n, d, ff, G, bank, bank, nest[0], nest[1])
+        for e in range(n):
+            B.smoe_quantize_slice(ctx, b, e, *(((draw(*s) * 0.02).to(dt))[None].contiguous() for s in ((ff, d), (ff, d), (d, ff))))
+        return b
+
+    routed, shared = make(E, f), make(n_sh, f_s) if n_sh else None
+    x = draw(T, d).bfloat16()
+    wr = draw(E, d) * std
+    y, idx, w, hist = B.smoe_prefill_histogram(ctx, routed, shared, x, k, w_router=wr, add_residual=True)
+    step = max(1, 24 * E // k)                                     # about 24 rows per expert
+    for t in range(0, T, step):
+        ys, ids, ws, _ = B.smoe_prefill_histogram(ctx, routed, shared, x[t:t + step].contiguous(), k, w_router=wr, add_residual=True)
+        assert torch.equal(ids, idx[t:t + step]) and torch.equal(ws, w[t:t + step]), t
+        assert torch.equal(ys, y[t:t + step]), t
+
 
 @pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,s_nest,s_bank,s_G", [
     # 64 experts top-1 want 32-row tiles, the shared experts 160-row ones.  Up to 24 short tiles of tokens the shared experts' tiles ride
