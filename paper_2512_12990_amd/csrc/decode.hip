@@ -81,7 +81,7 @@ struct DecodeArgs {
 // issued in the first instructions without waiting for a kernel-argument fetch.
 struct RouteIn {
   const float* logits; const float* bias; const uint8_t* mask;   // [E] each; bias / mask may be null
-  int E, k, do_route;              // do_route 0: idx_in / w_in of DecodeArgs hold the decision
+  int E, k, do_route;              // do_route 0: idx_in / w_in of DecodeArgs hold the decision; 2 (host side): logits is the router matrix
 };
 
 // Kernel-argument fetch: KARGS_FETCH issues one scalar load per 64-byte line of the argument
@@ -654,13 +654,55 @@ template <bool WT, typename T> __device__ __forceinline__ void put_shared(T* p, 
   else *p = v;
 }
 
+// Router logits of the token by every gate/up work-group for itself (MV: `logits` is the router matrix [E, d]), four experts of a wave
+// at a time, 512 columns each.  A lane adds its columns l, l + 64, ... in that order by fused multiply-add and the wave sum follows, as in
+// router_logits_kernel: the same bits.  This replaces a launch by E d 4 bytes out of L2 per
+// work-group: for small matrices (router_in_gateup).
+#define MV_R 4
+#define MV_C 8
+struct MvBatch { uint32_t w[MV_R][MV_C], x[MV_C]; };
+template <int ACT>
+__device__ __forceinline__ void mv_load(MvBatch& b, const float* w_router, const void* x, int E, int d, int e0, int i0, int lane) {
+#pragma unroll
+  for (int c = 0; c < MV_C; c++) {
+    const int i = min(i0 + c * 64 + lane, d - 1);      // (raw results only: a column past the end re-reads the last one, masked in mv_logits)
+    b.x[c] = ACT == SMOE_BF16 ? (uint32_t)((const uint16_t*)x)[i] : ((const uint32_t*)x)[i];
+#pragma unroll
+    for (int r = 0; r < MV_R; r++) b.w[r][c] = ((const uint32_t*)w_router)[(size_t)min(e0 + r * DEC_NW, E - 1) * d + i];
+  }
+}
+// (b: the first batch, already sent for)
+template <int ACT>
+__device__ __forceinline__ void mv_logits(MvBatch& b, const float* w_router, const void* x, int E, int d, int wave, int lane, float* z) {
+  for (int e0 = wave; e0 < E; e0 += MV_R * DEC_NW) {
+    float p[MV_R] = {};
+    for (int i0 = 0; i0 < d; i0 += MV_C * 64) {
+      if (e0 != wave || i0) mv_load<ACT>(b, w_router, x, E, d, e0, i0, lane);
+#pragma unroll
+      for (int c = 0; c < MV_C; c++) {
+        const float xf = __uint_as_float(ACT == SMOE_BF16 ? b.x[c] << 16 : b.x[c]);
+#pragma unroll
+        for (int r = 0; r < MV_R; r++) {
+          const float q = fmaf(__uint_as_float(b.w[r][c]), xf, p[r]);
+          p[r] = i0 + c * 64 + lane < d ? q : p[r];
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < MV_R; r++) {
+      const float t = wave_sum(p[r]);
+      if (lane == 0 && e0 + r * DEC_NW < E) z[e0 + r * DEC_NW] = t;
+    }
+  }
+}
+
 // The gate/up phase of one work-group (the body of gateup_kernel, and the first half of the
 // single-launch kernel).  KARG_BYTES: size of the calling kernel's argument segment.  WT: h and the
 // routing record are stored write-through at device scope (see put_shared).
-template <int ACT, int SCB, int FMT, int KARG_BYTES, bool WT>
+template <int ACT, int SCB, int FMT, int KARG_BYTES, bool WT, bool MV>
 __device__ __forceinline__ void gateup_body(const float* logits, const float* bias, const uint8_t* mask, const void* x_in, int E, int k,
                                             int do_route, int d_model, int n_wg, int n_se, DecodeArgs& a, int* sel_lds, int* prec_lds,
-                                            uint8_t* xvec, float2* xcs, unsigned* const* sync, unsigned* par) {
+                                            uint8_t* xvec, float2* xcs, unsigned* const* sync, unsigned* par, float* z_lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   // Several tokens in one launch: grid (8, tokens, work-groups / 8), so that the work-groups that
   // read the same weight rows for different tokens are dispatched together on one XCD and share
@@ -683,9 +725,18 @@ __device__ __forceinline__ void gateup_body(const float* logits, const float* bi
   Raw8 xraw = {};
   RouteRegs rr = {};
   if (stager) load8_raw<ACT>(x_in, (size_t)xt * 8, xraw);
-  route_load(in, lane, rr, router);
+  route_load(in, lane, rr, router);      // (MV: the logits read here are not used)
+  MvBatch mv;
+  if (MV) mv_load<ACT>(mv, logits, x_in, E, d, wave, 0, lane);
   KARGS_FETCH(KARG_BYTES);      // four pointers and six 4-byte leading parameters, then the struct(s)
   __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+  if (MV) {
+    mv_logits<ACT>(mv, logits, x_in, E, d, wave, lane, z_lds);
+    lds_barrier();
+    if (router)
+#pragma unroll
+      for (int j = 0; j < 4; j++) rr.z[j] = lane + 64 * j < E ? z_lds[lane + 64 * j] : 0.0f;
+  }
   // (single launch: the parity of the hand-over, needed when the work-group arrives -- see grid_wait)
   if (WT) *par = __hip_atomic_load(*sync + ONE_PARITY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (consumed at the end of the phase)
   if (tok) {
@@ -853,15 +904,16 @@ __device__ __forceinline__ void gateup_body(const float* logits, const float* bi
   }
 }
 
-template <int ACT, int SCB, int FMT>
+template <int ACT, int SCB, int FMT, bool MV>
 __global__ __launch_bounds__(DEC_NT) void gateup_kernel(const float* logits, const float* bias, const uint8_t* mask, const void* x_in,
                                                         int E, int k, int do_route, int d_model, int n_wg, int n_se,
                                                         DecodeArgs a) {
   __shared__ int sel_lds[SMOE_MAX_TOPK], prec_lds[SMOE_MAX_TOPK];
   __shared__ __align__(16) uint8_t xvec[StageTraits<ACT>::COMBO_BYTES];
   __shared__ float2 xcs[64];
-  gateup_body<ACT, SCB, FMT, DEC_LEAD_BYTES + (int)sizeof(DecodeArgs), false>(logits, bias, mask, x_in, E, k, do_route, d_model, n_wg, n_se, a,
-                                                                             sel_lds, prec_lds, xvec, xcs, nullptr, nullptr);
+  __shared__ float z_lds[MV ? SMOE_MAX_EXPERTS : 1];
+  gateup_body<ACT, SCB, FMT, DEC_LEAD_BYTES + (int)sizeof(DecodeArgs), false, MV>(logits, bias, mask, x_in, E, k, do_route, d_model, n_wg, n_se, a,
+                                                                                 sel_lds, prec_lds, xvec, xcs, nullptr, nullptr, z_lds);
 }
 
 // ---------------------------------------------------------------------------------- gate/up kernel, wide rows
@@ -1256,8 +1308,8 @@ __global__ __launch_bounds__(DEC_NT, ACT == SMOE_F32 ? 2 : 4) void decode_one_ke
   __shared__ float2 xcs[64];
   extern __shared__ __align__(16) uint8_t dyn[];
   unsigned par = 0;
-  gateup_body<ACT, SCB, FMT, DEC_LEAD_BYTES + (int)sizeof(DecodeArgs) + (int)sizeof(OneArgs), true>(logits, bias, mask, x_in, E, k, do_route, d_model,
-                                                                                           n_wg, n_se, a, sel_lds, prec_lds, xvec, xcs, &o.sync, &par);
+  gateup_body<ACT, SCB, FMT, DEC_LEAD_BYTES + (int)sizeof(DecodeArgs) + (int)sizeof(OneArgs), true, false>(logits, bias, mask, x_in, E, k, do_route, d_model,
+                                                                                           n_wg, n_se, a, sel_lds, prec_lds, xvec, xcs, &o.sync, &par, nullptr);
   // every wave's part of h (and work-group 0's routing record) acknowledged before the work-group counts itself in
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   par = (unsigned)uni((int)par) & 1u;
@@ -1367,7 +1419,7 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
       hipExtLaunchKernelGGL((gateup_wide_kernel<ACT, SCB, FMT, DEC_WIDE_KS>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
                             in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
     else
-      hipExtLaunchKernelGGL((gateup_kernel<ACT, SCB, FMT>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
+      hipExtLaunchKernelGGL((gateup_kernel<ACT, SCB, FMT, false>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
                             in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
     hipExtLaunchKernelGGL(down, g2, blk, (unsigned)lds, ctx->stream, ev[2], ev[3], 0, recw, (const float*)a.h,
                           n_combo_s, n_pieces, psh_arg, a.f_s, a.f_r, a.ks_s, a.ks_r, a.inv_ks_s, a.inv_ks_r, nsf, a);
@@ -1378,9 +1430,12 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
     else if (wide)
       gateup_wide_kernel<ACT, SCB, FMT, DEC_WIDE_KS><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route,
                                                                              a.d_model, n_wg, n_se, a);
+    else if (!MULTI && in.do_route == 2)
+      gateup_kernel<ACT, SCB, FMT, !MULTI><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route, a.d_model,
+                                                                    n_wg, n_se, a);
     else
-      gateup_kernel<ACT, SCB, FMT><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route, a.d_model, n_wg, n_se,
-                                                           a);
+      gateup_kernel<ACT, SCB, FMT, false><<<g1, blk, 0, ctx->stream>>>(in.logits, in.bias, in.mask, a.x, in.E, in.k, in.do_route, a.d_model,
+                                                                   n_wg, n_se, a);
     down<<<g2, blk, lds, ctx->stream>>>(recw, (const float*)a.h, n_combo_s, n_pieces, psh_arg, a.f_s, a.f_r, a.ks_s,
                                                          a.ks_r, a.inv_ks_s, a.inv_ks_r, nsf, a);
   }
@@ -1514,6 +1569,16 @@ extern "C" int smoe_expert_ffn(smoe_ctx* ctx, const smoe_bank* routed, const smo
   return launch_decode(ctx, routed, shared, act_dtype, k, in, a, 1, ctx->ws, ctx->ws_bytes);
 }
 
+// The router mat-vec joins the gate/up launch (mv_logits) where little is read for it: rows in rounds of 32, all work-groups together.  Microseconds
+// per call, launch of its own / joined: 8 experts of d_model 256, 32 work-groups (0.3 M entries) 12.9 / 10.1; 8 of 512, 128 work-groups (2.1 M)
+// 13.2 / 10.3; 16 of 1024, 128 (4.2 M) 13.1 / 11.6; 16 of 512, 384 (6.3 M) 13.8 / 13.0; but 8 of 1280, 256 (10.5 M) 12.1 / 12.2; 12 of 768,
+// 512 (12.6 M) 13.2 / 13.4; 16 of 1024, 512 (16.8 M) 12.3 / 13.1.
+static bool router_in_gateup(const smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank* shared, int k) {
+  const size_t entries = (size_t)((routed->desc.n_experts + 31) / 32 * 32) * routed->desc.d_model;
+  const size_t rows = (size_t)std::max(k, 0) * routed->desc.d_ff + (shared ? (size_t)shared->desc.n_experts * shared->desc.d_ff : 0);
+  const size_t n_wg = std::min((size_t)2 * ctx->n_cu, (rows + DEC_NW - 1) / DEC_NW);
+  return routed->desc.d_model <= 2048 && entries <= 65536 && entries * n_wg <= 8500000;
+}
 static int decode_layer_impl(smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank* shared, const void* x_dev,
                              int act_dtype, int k, const float* logits_dev, const float* w_router_dev,
                              const float* bias_dev, int norm_topk, float routed_scale,
@@ -1528,7 +1593,11 @@ static int decode_layer_impl(smoe_ctx* ctx, const smoe_bank* routed, const smoe_
     return SMOE_EALIGN;
   if (!ws || ws_bytes < (size_t)WS_H_OFF) return SMOE_ESIZE;
   const float* logits = logits_dev;
-  if (!logits) {
+  // (with the single launch, and timed, the router keeps a launch of its own)
+  const bool in_gateup = !logits && !ctx->one_launch && !ctx->timing && router_in_gateup(ctx, routed, shared, k);
+  if (in_gateup) {
+    logits = w_router_dev;
+  } else if (!logits) {
     // router mat-vec into the workspace, then the gate/up prologue selects from those logits
     float* zws = (float*)(ws + WS_IDX_OFF);
     HIPCHK(ctx, hipSetDevice(ctx->device));
@@ -1539,7 +1608,7 @@ static int decode_layer_impl(smoe_ctx* ctx, const smoe_bank* routed, const smoe_
   DecodeArgs a{};
   a.norm_topk = norm_topk; a.routed_scale = routed_scale;
   a.tau = tau_head; a.x = x_dev; a.shared_gate_w = shared_gate_w_dev;
-  const RouteIn in{logits, bias_dev, slice_mask_dev, 0, 0, 1};
+  const RouteIn in{logits, bias_dev, slice_mask_dev, 0, 0, in_gateup ? 2 : 1};
   a.idx_out = idx_out_dev; a.w_out = w_out_dev; a.prec_out = prec_out_dev; a.y = y_dev; a.add_residual = add_residual;
   return launch_decode(ctx, routed, shared, act_dtype, k, in, a, 1, ws, ws_bytes);
 }

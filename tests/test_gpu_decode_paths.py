@@ -189,3 +189,33 @@ def test_stream_read_measurement_aid(ctx):
     assert lib.smoe_stream_read(ctx.h, None, C.c_size_t(1 << 20), 16, p(sink)) == -1
     assert lib.smoe_stream_read(ctx.h, C.c_void_p(buf.data_ptr() + 4), C.c_size_t(1 << 10), 16, p(sink)) == -3
     assert lib.smoe_stream_read(ctx.h, p(buf), C.c_size_t(1 << 20), 0, p(sink)) == -2
+
+
+@pytest.mark.parametrize("act,E,d,f,k,n_sh,f_s,G", [
+    ("f32", 8, 256, 128, 2, 0, 0, 64),        # router mat-vec inside the gate/up launch: one expert per wave
+    ("bf16", 3, 64, 64, 3, 1, 64, 32),        # fewer experts than waves, one column per lane
+    ("bf16", 37, 192, 64, 5, 0, 0, 64),       # five rows of some waves, a second round of four
+    ("f32", 100, 160, 64, 4, 2, 96, 32),      # more than 64 experts; columns not a multiple of a batch
+    ("bf16", 32, 2048, 64, 1, 0, 0, 128),     # the longest rows, the most entries that join
+    ("bf16", 256, 64, 64, 8, 0, 0, 64),       # the most experts
+    ("bf16", 33, 2048, 64, 1, 0, 0, 128),     # one expert more: a launch of its own
+    ("bf16", 16, 512, 1216, 4, 0, 0, 64),     # as many work-groups as there can be join ...
+    ("bf16", 16, 1024, 1024, 4, 0, 0, 64),    # ... with rows of this length they do not
+])
+def test_router_inside_the_gateup_launch(ctx, act, E, d, f, k, n_sh, f_s, G):
+    """One token with the router matrix given: the same selection, weights and outputs, bit for bit, as with the
+    logits that smoe_route computes from it (whose sums run in the same order)."""
+    say("router inside gate/up", act, E, d, f, k, n_sh, f_s, G)
+    pair = LayerPair(ctx, synth.LayerShape(d, E, f, k, G, n_shared=n_sh, shared_d_ff=f_s, act=act), seed=63)
+    x = synth.activations(63, 1, d, act).cuda()
+    wr = synth.router_weight(63, 0, E, d, std=0.05).cuda()
+    mask = torch.randint(0, 4, (E,), generator=torch.Generator().manual_seed(5), dtype=torch.uint8).cuda()
+    bias = (mask > 0).float()
+    _, _, z = B.smoe_route(ctx, k, x=x, w_router=wr, want_logits=True)
+    out = []
+    for kw in (dict(w_router=wr), dict(logits=z)):
+        y, idx, w, prec = torch.empty_like(x), torch.empty((1, k), dtype=torch.int32, device="cuda"), torch.empty((1, k), device="cuda"), torch.zeros((1, k), dtype=torch.uint8, device="cuda")
+        B.smoe_decode_layer(ctx, pair.routed, pair.shared, x, k, bias=bias, slice_mask=mask, add_residual=True, y=y, idx_out=idx, w_out=w, prec_out=prec, **kw)
+        out.append((y, idx, w, prec))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
