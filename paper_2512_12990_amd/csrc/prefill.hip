@@ -222,7 +222,7 @@ template <int SCB, int FMT, int NF> struct PfLds {
 // expansion and a read behind every product, pinned there: the compiler sinks the work otherwise).  No load depends on a condition: past the
 // last step the range is empty, the load counts all the same, and every wait is a constant.  Cycles per step, two work-groups of four
 // waves: 1865 before, 1708 now (mean of 3 to 5 fragments); eight waves: 1785 at 4 fragments, 2657 at 8, i.e. 446 and 332 per fragment -- a weight is
-// expanded for more rows.  Of those 2657 the products are 2048, LDS traffic some 2500, the barrier 400.  Taller tiles take more of a CU at
+// expanded for more rows.  Of those 2657 the products are 2048, the barrier 400.  Taller tiles take more of a CU at
 // once; where that leaves the chip unfilled the shorter ones are faster (gemm_cycles).  A layer of 2048 / 4096 tokens (60 experts of d_ff 1408,
 // the longer one with a shared expert of 5632): 291 -> 264 / 806 -> 709 us.  Not kept: eight waves and 160 rows (287 / 786 us), eight-wave
 // work-groups that stay and take a list of tiles, the next one's weights sent for before the epilogue (286 / 798 us against 270 / 747).
@@ -382,7 +382,9 @@ __global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_ge
   load_plane(wb, 0, 0, 2 * NPL, wb.p_bytes);
 
   // ---- token rows: a wave's direct load q moves rows 8 (NW q + wave) .. + 7 of the tile, lane i the 16-byte
-  // piece (i % 8) ^ (i / 8) of row i / 8 (of these eight), so that the operand reads, 32 rows of one piece, hit all banks.
+  // piece (i % 8) ^ (r / 2 % 8) of row r = i / 8 (of these eight): sixteen lanes of an operand read, sixteen rows of one piece, then fall into
+  // the sixteen 16-byte slots of the LDS's 64 banks (with r % 8 rows r and r + 8 collide: half of all LDS
+  // cycles were conflicts; 2048 / 4096 tokens 270 -> 267 / 721 -> 716 us per layer).
   // MODE 0 gathers the rows of X (a row past the tile's last one repeats that row); MODE 1 reads consecutive
   // rows of H (past the last one: another tile's, or zeros from out of range).  Rows of the product are
   // independent and the epilogue stores none of the surplus ones.
@@ -390,7 +392,7 @@ __global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_ge
   constexpr int NA = MODE == 0 ? 4 * NF / NW : 1;
   uint32_t a_off[NA], a_half = 0;
   auto row_at = [&](int r) __attribute__((always_inline)) {
-    const int c = (lane & 7) ^ (r & 7);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
     uint32_t src;
     if (MODE == 0) {
       const int rc = m0 + min(r, m_cnt - 1);
@@ -403,8 +405,8 @@ __global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_ge
 #pragma unroll
   for (int q = 0; q < NA; q++) a_off[q] = row_at((NW * q + wave) * 8 + (lane >> 3));
   if (NW == 8 && nf > 4 && (nf & 1)) a_half = row_at(32 * (nf - 1) + 4 * wave + ((lane >> 3) & 3));
-  // operand reads: lane (n, hh) takes columns 32 hh + 8 s .. + 7 of row n: piece (4 hh + s) ^ (n % 8)
-  const uint32_t a_rd = n * 128 + (((4 * hh) ^ (n & 7)) * 16);
+  // operand reads: lane (n, hh) takes columns 32 hh + 8 s .. + 7 of row n: piece (4 hh + s) ^ (n / 2 % 8)
+  const uint32_t a_rd = n * 128 + (((4 * hh) ^ ((n >> 1) & 7)) * 16);
   // MODE 1: the weight of row tid of the tile, for the epilogue
   float my_wt = 0.0f;
   if (MODE == 1 && tid < m_cnt) my_wt = a.wgt[a.dense_rows ? m0 + tid : a.rows[row0 + m0 + tid]];
