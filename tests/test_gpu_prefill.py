@@ -281,6 +281,24 @@ def test_prefill_swiglu_of_gates_far_below_zero(ctx):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
 
 
+def test_prefill_row_beside_an_extreme_gate(ctx):
+    # a token whose gates go far beyond +-80 among ordinary ones: the rows beside it are the same bits as without it
+    T, d, f, G = 4096, 256, 4096, 128
+    say("prefill, rows beside extreme gates")
+    g = torch.Generator(device="cuda").manual_seed(73)
+    bank = B.Bank(ctx, 1, d, f, G, "bf16", "bf16")
+    B.smoe_quantize_slice(ctx, bank, 0, *((torch.randn((1,) + s, generator=g, device="cuda") * c).bfloat16()
+                                          for s, c in (((f, d), 0.15), ((f, d), 0.15), ((d, f), 0.02))))
+    x = torch.randn((T, d), generator=g, device="cuda").bfloat16()
+    z = torch.zeros((T, 1), device="cuda")
+    outlier = torch.arange(T, device="cuda") % 32 == 5           # one in every fragment of 32 rows
+    xo = torch.where(outlier[:, None], x * 100.0, x)
+    y, yo = (B.smoe_prefill_histogram(ctx, bank, None, v, 1, logits=z)[0] for v in (x, xo))
+    assert torch.isfinite(yo.float()).all()
+    assert not torch.equal(y[outlier], yo[outlier])
+    assert torch.equal(y[~outlier], yo[~outlier])
+
+
 @pytest.mark.parametrize("big,T,d,f,G,n_sh,nest", [
     ("up", 3, 128, 64, 64, 0, (8, 4)),       # a tile of three rows
     ("up", 700, 576, 128, 32, 0, (4, 2)),    # tall tiles, a partial 256-column chunk
