@@ -657,7 +657,7 @@ template <bool WT, typename T> __device__ __forceinline__ void put_shared(T* p, 
 // Router logits of the token by every gate/up work-group for itself (MV: `logits` is the router matrix [E, d]), four experts of a wave
 // at a time, 512 columns each.  A lane adds its columns l, l + 64, ... in that order by fused multiply-add and the wave sum follows, as in
 // router_logits_kernel: the same bits.  This replaces a launch by E d 4 bytes out of L2 per
-// work-group: for small matrices (router_in_gateup).
+// work-group, and a launch less to send: where that pays (router_in_gateup).
 #define MV_R 4
 #define MV_C 8
 struct MvBatch { uint32_t w[MV_R][MV_C], x[MV_C]; };
@@ -1569,15 +1569,21 @@ extern "C" int smoe_expert_ffn(smoe_ctx* ctx, const smoe_bank* routed, const smo
   return launch_decode(ctx, routed, shared, act_dtype, k, in, a, 1, ctx->ws, ctx->ws_bytes);
 }
 
-// The router mat-vec joins the gate/up launch (mv_logits) where little is read for it: rows in rounds of 32, all work-groups together.  Microseconds
-// per call, launch of its own / joined: 8 experts of d_model 256, 32 work-groups (0.3 M entries) 12.9 / 10.1; 8 of 512, 128 work-groups (2.1 M)
-// 13.2 / 10.3; 16 of 1024, 128 (4.2 M) 13.1 / 11.6; 16 of 512, 384 (6.3 M) 13.8 / 13.0; but 8 of 1280, 256 (10.5 M) 12.1 / 12.2; 12 of 768,
-// 512 (12.6 M) 13.2 / 13.4; 16 of 1024, 512 (16.8 M) 12.3 / 13.1.
+// The router mat-vec joins the gate/up launch (mv_logits) where that is faster than a launch of its own, eager and in a replayed graph: every
+// work-group then makes all logits for itself, in batches of 32 experts times 512 columns, each a round trip to L2 that nothing hides.  One batch always
+// pays; two where a CU has one work-group and they read little together; three or more never.  Microseconds per call, launch of its own / joined, eager,
+// then replayed (stacks of 8 layers):
+//   one batch:  8 experts of d_model 256, fp32, 32 work-groups 10.7 / 9.8, 10.9 / 9.8; 32 of 512, 256: 11.2 / 10.8, 11.8 / 10.9; 512: 18.8 / 18.4, 19.6 / 19.0
+//   two:        64 of 512, 128: 11.7 / 11.2, 11.7 / 11.5; 256: 11.5 / 11.6, 12.0 / 12.2; 16 of 1024, 128 (4.2 million entries) 11.9 / 10.8, 11.6 / 11.1;
+//               32 of 1024, fp32, 256 (8.4 million) 12.3 / 12.7, 13.2 / 13.3; 8 of 640, 288: 12.0 / 12.9, 12.8 / 13.4; 60 of 256, 512: 12.9 / 14.7, 13.5 / 15.0
+//   more:       8 of 1536, 32: 11.0 / 11.1, 11.3 / 11.7; 48 of 1024, 32: 11.2 / 12.1, 11.5 / 12.6; 128 of 256, 256: 14.2 / 16.6, 14.6 / 16.9;
+//               256 of 64, 64: 13.7 / 19.2, 14.0 / 19.2
 static bool router_in_gateup(const smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank* shared, int k) {
-  const size_t entries = (size_t)((routed->desc.n_experts + 31) / 32 * 32) * routed->desc.d_model;
+  const size_t rounds = (size_t)(routed->desc.n_experts + MV_R * DEC_NW - 1) / (MV_R * DEC_NW), d = (size_t)routed->desc.d_model;
+  const size_t batches = rounds * ((d + MV_C * 64 - 1) / (MV_C * 64));
   const size_t rows = (size_t)std::max(k, 0) * routed->desc.d_ff + (shared ? (size_t)shared->desc.n_experts * shared->desc.d_ff : 0);
   const size_t n_wg = std::min((size_t)2 * ctx->n_cu, (rows + DEC_NW - 1) / DEC_NW);
-  return routed->desc.d_model <= 2048 && entries <= 65536 && entries * n_wg <= 8500000;
+  return batches <= 1 || (batches == 2 && n_wg <= (size_t)ctx->n_cu && rounds * (MV_R * DEC_NW) * d * n_wg <= 5000000);
 }
 static int decode_layer_impl(smoe_ctx* ctx, const smoe_bank* routed, const smoe_bank* shared, const void* x_dev,
                              int act_dtype, int k, const float* logits_dev, const float* w_router_dev,

@@ -191,20 +191,35 @@ def test_stream_read_measurement_aid(ctx):
     assert lib.smoe_stream_read(ctx.h, p(buf), C.c_size_t(1 << 20), 0, p(sink)) == -2
 
 
-@pytest.mark.parametrize("act,E,d,f,k,n_sh,f_s,G", [
-    ("f32", 8, 256, 128, 2, 0, 0, 64),        # router mat-vec inside the gate/up launch: one expert per wave
-    ("bf16", 3, 64, 64, 3, 1, 64, 32),        # fewer experts than waves, one column per lane
-    ("bf16", 37, 192, 64, 5, 0, 0, 64),       # five rows of some waves, a second round of four
-    ("f32", 100, 160, 64, 4, 2, 96, 32),      # more than 64 experts; columns not a multiple of a batch
-    ("bf16", 32, 2048, 64, 1, 0, 0, 128),     # the longest rows, the most entries that join
-    ("bf16", 256, 64, 64, 8, 0, 0, 64),       # the most experts
-    ("bf16", 33, 2048, 64, 1, 0, 0, 128),     # one expert more: a launch of its own
-    ("bf16", 16, 512, 1216, 4, 0, 0, 64),     # as many work-groups as there can be join ...
-    ("bf16", 16, 1024, 1024, 4, 0, 0, 64),    # ... with rows of this length they do not
+WS_LOGITS = 16 << 10      # where a workspace holds the logits that a router launch of its own leaves
+
+
+def _logits_in_workspace(ctx, E):
+    off = (-ctx.workspace.data_ptr()) % 256 + WS_LOGITS
+    return ctx.workspace[off : off + 4 * E].view(torch.float32)
+
+
+@pytest.mark.parametrize("act,E,d,f,k,n_sh,f_s,G,joined", [
+    ("f32", 8, 256, 128, 2, 0, 0, 64, True),        # router mat-vec inside the gate/up launch: one expert per wave
+    ("bf16", 3, 64, 64, 3, 1, 64, 32, True),        # fewer experts than waves, one column per lane
+    ("bf16", 37, 192, 64, 5, 0, 0, 64, True),       # five rows of some waves, a second round of four
+    ("f32", 100, 160, 64, 4, 2, 96, 32, False),     # four rounds
+    ("bf16", 32, 2048, 64, 1, 0, 0, 128, False),    # four batches of columns
+    ("bf16", 256, 64, 64, 8, 0, 0, 64, False),      # the most experts
+    ("bf16", 33, 2048, 64, 1, 0, 0, 128, False),
+    ("bf16", 16, 512, 1216, 4, 0, 0, 64, True),     # one batch: as many work-groups as there can be
+    ("bf16", 16, 1024, 1024, 4, 0, 0, 64, False),   # two batches: not with two work-groups per CU ...
+    ("f32", 32, 1024, 64, 2, 0, 0, 64, True),       # ... but with few; the longest rows that join
+    ("bf16", 9, 544, 64, 2, 0, 0, 32, True),        # a second batch of half a wave's columns
+    ("bf16", 64, 512, 256, 4, 0, 0, 64, True),      # the most experts that join
+    ("bf16", 65, 64, 64, 2, 0, 0, 64, False),       # one more: three rounds
+    ("bf16", 64, 512, 512, 4, 0, 0, 64, False),     # 8.4 million entries read
+    ("bf16", 4, 1088, 64, 2, 0, 0, 64, False),      # three batches of columns
 ])
-def test_router_inside_the_gateup_launch(ctx, act, E, d, f, k, n_sh, f_s, G):
+def test_router_inside_the_gateup_launch(ctx, act, E, d, f, k, n_sh, f_s, G, joined):
     """One token with the router matrix given: the same selection, weights and outputs, bit for bit, as with the
-    logits that smoe_route computes from it (whose sums run in the same order)."""
+    logits that smoe_route computes from it (whose sums run in the same order); only a router launch of its own leaves
+    logits in the workspace."""
     say("router inside gate/up", act, E, d, f, k, n_sh, f_s, G)
     pair = LayerPair(ctx, synth.LayerShape(d, E, f, k, G, n_shared=n_sh, shared_d_ff=f_s, act=act), seed=63)
     x = synth.activations(63, 1, d, act).cuda()
@@ -214,8 +229,11 @@ def test_router_inside_the_gateup_launch(ctx, act, E, d, f, k, n_sh, f_s, G):
     _, _, z = B.smoe_route(ctx, k, x=x, w_router=wr, want_logits=True)
     out = []
     for kw in (dict(w_router=wr), dict(logits=z)):
+        _logits_in_workspace(ctx, E).fill_(float("nan"))
         y, idx, w, prec = torch.empty_like(x), torch.empty((1, k), dtype=torch.int32, device="cuda"), torch.empty((1, k), device="cuda"), torch.zeros((1, k), dtype=torch.uint8, device="cuda")
         B.smoe_decode_layer(ctx, pair.routed, pair.shared, x, k, bias=bias, slice_mask=mask, add_residual=True, y=y, idx_out=idx, w_out=w, prec_out=prec, **kw)
         out.append((y, idx, w, prec))
+        left = _logits_in_workspace(ctx, E)
+        assert bool(torch.isnan(left).all()) if joined or "logits" in kw else torch.equal(left, z[0])
     for a, b in zip(*out):
         assert torch.equal(a, b)
