@@ -89,6 +89,9 @@ const char* smoe_strerror(int status);
 int smoe_last_hip_error(const smoe_ctx* ctx); /* hipError_t of the last failing HIP call, else 0 */
 /* Measurement aid, no part of the method.  While enabled, smoe_expert_ffn / smoe_decode_layer record
  * a start and a stop HIP event with each of their two kernel dispatches (gate/up, down) on the ctx stream.
+ * The kernels are those of the call without the aid: where the router mat-vec is part of the gate/up launch
+ * (a small router matrix and no given logits) its time is part of the gate/up time; elsewhere it is a launch of its
+ * own, which is not timed.
  * smoe_ctx_timing_read synchronises the stream, returns the summed durations in microseconds and the
  * number of calls recorded since the last read, and releases the events. */
 int smoe_ctx_timing(smoe_ctx* ctx, int enable);

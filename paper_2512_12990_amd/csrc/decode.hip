@@ -1418,6 +1418,9 @@ static int launch_decode_t(smoe_ctx* ctx, const RouteIn& in, DecodeArgs& a, int 
     else if (wide)
       hipExtLaunchKernelGGL((gateup_wide_kernel<ACT, SCB, FMT, DEC_WIDE_KS>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
                             in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
+    else if (!MULTI && in.do_route == 2)
+      hipExtLaunchKernelGGL((gateup_kernel<ACT, SCB, FMT, !MULTI>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
+                            in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
     else
       hipExtLaunchKernelGGL((gateup_kernel<ACT, SCB, FMT, false>), g1, blk, 0, ctx->stream, ev[0], ev[1], 0, in.logits, in.bias, in.mask, a.x,
                             in.E, in.k, in.do_route, a.d_model, n_wg, n_se, a);
@@ -1599,8 +1602,8 @@ static int decode_layer_impl(smoe_ctx* ctx, const smoe_bank* routed, const smoe_
     return SMOE_EALIGN;
   if (!ws || ws_bytes < (size_t)WS_H_OFF) return SMOE_ESIZE;
   const float* logits = logits_dev;
-  // (with the single launch, and timed, the router keeps a launch of its own)
-  const bool in_gateup = !logits && !ctx->one_launch && !ctx->timing && router_in_gateup(ctx, routed, shared, k);
+  // (with the single launch the router keeps a launch of its own)
+  const bool in_gateup = !logits && !ctx->one_launch && router_in_gateup(ctx, routed, shared, k);
   if (in_gateup) {
     logits = w_router_dev;
   } else if (!logits) {

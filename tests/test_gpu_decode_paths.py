@@ -237,3 +237,23 @@ def test_router_inside_the_gateup_launch(ctx, act, E, d, f, k, n_sh, f_s, G, joi
         assert bool(torch.isnan(left).all()) if joined or "logits" in kw else torch.equal(left, z[0])
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+def test_timing_aid_times_the_kernels_of_the_untimed_call(ctx):
+    # a layer whose router mat-vec is part of the gate/up launch: with the aid on no router launch leaves logits either
+    E, d, f, k = 8, 256, 128, 2
+    pair = LayerPair(ctx, synth.LayerShape(d, E, f, k, 64, act="bf16"), seed=64)
+    x = synth.activations(64, 1, d, "bf16").cuda()
+    wr = synth.router_weight(64, 0, E, d, std=0.05).cuda()
+    out = []
+    for timed in (False, True):
+        _logits_in_workspace(ctx, E).fill_(float("nan"))
+        ctx.timing(timed)
+        try:
+            out.append(B.smoe_decode_layer(ctx, pair.routed, None, x, k, w_router=wr))
+            gateup_us, down_us, n = ctx.timing_read()
+        finally:
+            ctx.timing(False)
+        assert n == int(timed) and (gateup_us > 0.0 and down_us > 0.0) == timed
+        assert bool(torch.isnan(_logits_in_workspace(ctx, E)).all()), timed
+    assert torch.equal(*out)
