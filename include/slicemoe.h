@@ -230,6 +230,11 @@ int smoe_decode_layer_multi(smoe_ctx* ctx, const smoe_bank* routed, const smoe_b
 /* Bytes of device scratch smoe_prefill_histogram needs for T tokens; shared_d_ff = d_ff of the shared
  * experts (0 without a shared bank). */
 int smoe_prefill_bytes(int T, int E, int k, int d_model, int d_ff, int shared_d_ff, size_t* scratch_bytes);
+/* Host only, for tests and measurements.  How smoe_prefill_histogram cuts such a layer on a device of n_cu compute units:
+ * token rows of the tallest tile of the routed and of the shared experts' GEMMs (0 without a shared bank) out of 32, 64, 96, 160
+ * and 256, and whether the shared experts' tiles are part of the routed experts' launches. */
+int smoe_prefill_tiles(const smoe_bank_desc* routed, const smoe_bank_desc* shared, int T, int k, int n_cu, int* routed_rows,
+                       int* shared_rows, int* joined);
 /* T tokens through one layer, every expert HIGH: routes each token (as smoe_route), counts
  * hist_dev[e] = number of (token, slot) pairs sent to expert e (uint32 [E], overwritten), runs the
  * experts as a grouped GEMM over the tokens of each expert, and writes

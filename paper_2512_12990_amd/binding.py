@@ -49,7 +49,7 @@ EXPORTS = [
     "smoe_ctx_timing_read", "smoe_stream_read", "smoe_ctx_single_launch", "smoe_ctx_single_launch_status",
     "smoe_bank_bytes", "smoe_bank_create", "smoe_bank_destroy", "smoe_quantize_slice", "smoe_export_codes",
     "smoe_route", "smoe_expert_ffn", "smoe_decode_layer", "smoe_decode_layer_multi", "smoe_static_scratch_bytes", "smoe_decode_layer_static",
-    "smoe_prefill_bytes", "smoe_prefill_histogram", "smoe_topn_slices",
+    "smoe_prefill_bytes", "smoe_prefill_tiles", "smoe_prefill_histogram", "smoe_topn_slices",
     "smoe_cache_create", "smoe_cache_destroy", "smoe_cache_init_order", "smoe_cache_snapshot",
     "smoe_cache_access", "smoe_cache_snapshot_all", "smoe_cache_access_all", "smoe_cache_stats_get", "smoe_cache_order",
     "smoe_system_spec_paper", "smoe_cost_model",
@@ -299,6 +299,14 @@ def smoe_prefill_bytes(T, E, k, d_model, d_ff, shared_d_ff=0) -> int:
     _chk(lib().smoe_prefill_bytes(C.c_int(T), C.c_int(E), C.c_int(k), C.c_int(d_model), C.c_int(d_ff),
                                   C.c_int(shared_d_ff), C.byref(n)), "smoe_prefill_bytes")
     return n.value
+
+
+def smoe_prefill_tiles(routed: BankDesc, shared: Optional[BankDesc], T: int, k: int, n_cu: int):
+    """(token rows of the tallest tile of the routed experts, of the shared experts, shared tiles in the routed launches)"""
+    r, s, j = C.c_int(), C.c_int(), C.c_int()
+    _chk(lib().smoe_prefill_tiles(C.byref(routed), C.byref(shared) if shared is not None else None, C.c_int(T), C.c_int(k), C.c_int(n_cu),
+                                  C.byref(r), C.byref(s), C.byref(j)), "smoe_prefill_tiles")
+    return r.value, s.value, bool(j.value)
 
 
 def smoe_prefill_histogram(ctx: Ctx, routed: Bank, shared: Optional[Bank], x: torch.Tensor, k: int, logits=None,

@@ -903,6 +903,33 @@ static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, double* cycles) {
   return best;
 }
 
+// Tile heights (in fragments) of the routed and the shared experts, and whether the shared experts' tiles ride in the routed experts' launches
+// (then at the routed experts' height).
+struct PrefillPlan { int nf, nfs; bool join; };
+static PrefillPlan plan_prefill(int T, int k, int E, int d, int f, int ns, int f_s, bool same, int n_cu) {
+  const GemmSize sizes[2][2] = {{{(double)E, (double)T * k / E, 2 * f, d, false}, {(double)E, (double)T * k / E, d, f, false}},
+                                {{(double)ns, (double)T, 2 * f_s, d, true}, {1.0, (double)T, d, f_s * ns, true}}};
+  double c_r, c_s = 0, c_both = 0;
+  PrefillPlan p{pick_nf(sizes, 1, n_cu, &c_r), ns ? pick_nf(sizes + 1, 1, n_cu, &c_s) : 0, false};
+  if (!ns || !same) return p;      // (same: both banks have one nest and one scale type)
+  if (p.nf >= 3 && p.nfs >= 3) {
+    // taller tiles: one height for both sets, in common launches, if that is estimated to be no slower
+    const int nfb = pick_nf(sizes, 2, n_cu, &c_both);
+    if (c_both <= c_r + c_s + 30e3) { p.nf = nfb; p.join = true; }      // (two launches less)
+  } else {
+    // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
+    // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both
+    // want the same tile height, or if at the routed experts' (lower) height there is little to expand: a dense tile
+    // expands its weights again, 600 million of them in about 55 us over the chip, which is what launches of their own lose to
+    // their empty ends.  64 experts of d_ff 512, one shared of 1024, d_model 1024, 500 tokens: 101 -> 72 us; 96 experts, two
+    // shared of 3840, d_model 2560, 500 tokens, all joined, would be 482 -> 515.
+    const int bm = 32 * p.nf;
+    const double again = 3.0 * d * f_s * ns * ((T + bm - 1) / bm);
+    p.join = p.nf == p.nfs || T <= 8 * bm || (T <= 24 * bm && again <= 600e6);
+  }
+  return p;
+}
+
 struct PrefillLayout { size_t rows, pos, h, o, gamma, h_s, o_s, total; };
 
 static inline int max_tiles(int T, int E, int k, int bm) { return E + (T * k) / bm; }
@@ -931,6 +958,19 @@ extern "C" int smoe_prefill_bytes(int T, int E, int k, int d_model, int d_ff, in
   if (!scratch_bytes) return SMOE_EINVAL;
   if (T <= 0 || E <= 0 || k <= 0 || k > E || d_model <= 0 || d_ff <= 0 || shared_d_ff < 0) return SMOE_ESHAPE;
   *scratch_bytes = prefill_layout(T, E, k, d_model, d_ff, shared_d_ff).total;
+  return SMOE_OK;
+}
+
+extern "C" int smoe_prefill_tiles(const smoe_bank_desc* routed, const smoe_bank_desc* shared, int T, int k, int n_cu, int* routed_rows,
+                                  int* shared_rows, int* joined) {
+  if (!routed || !routed_rows || !shared_rows || !joined) return SMOE_EINVAL;
+  if (T <= 0 || k <= 0 || k > routed->n_experts || routed->d_model <= 0 || routed->d_ff <= 0 || n_cu <= 0) return SMOE_ESHAPE;
+  if (shared && (shared->n_experts <= 0 || shared->d_model != routed->d_model || shared->d_ff <= 0)) return SMOE_ESHAPE;
+  const PrefillPlan p = plan_prefill(T, k, routed->n_experts, routed->d_model, routed->d_ff, shared ? shared->n_experts : 0, shared ? shared->d_ff : 0,
+                                     shared && shared->scale_dtype == routed->scale_dtype && shared->b_low == routed->b_low, n_cu);
+  *routed_rows = 32 * p.nf;
+  *shared_rows = 32 * (p.join ? p.nf : p.nfs);
+  *joined = p.join;
   return SMOE_OK;
 }
 
@@ -970,18 +1010,10 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
 
   RouteArgs ra{E, k, d, logits_dev, x_dev, w_router_dev, nullptr, norm_topk, routed_scale, nullptr, idx_dev, w_dev};
   { const int rc = smoe_launch_route(ctx, ra, T, SMOE_BF16); if (rc) return rc; }
-  const GemmSize sizes[2][2] = {{{(double)E, (double)T * k / E, 2 * f, d, false}, {(double)E, (double)T * k / E, d, f, false}},
-                                {{shared ? (double)shared->desc.n_experts : 0.0, (double)T, 2 * f_s, d, true}, {1.0, (double)T, d, shared ? f_s * shared->desc.n_experts : 0, true}}};
-  double c_r, c_s = 0, c_both = 0;
-  int nf = pick_nf(sizes, 1, ctx->n_cu, &c_r);
-  const int nfs = shared ? pick_nf(sizes + 1, 1, ctx->n_cu, &c_s) : 0;
-  // taller tiles: one height for both sets, in common launches, if that is estimated to be no slower
-  const bool same = shared && shared->dev.sc_bf16 == routed->dev.sc_bf16 && shared->dev.bits == routed->dev.bits;
-  bool join = false;
-  if (same && nf >= 3 && nfs >= 3) {
-    const int nfb = pick_nf(sizes, 2, ctx->n_cu, &c_both);
-    if (c_both <= c_r + c_s + 30e3) { nf = nfb; join = true; }      // (two launches less)
-  }
+  const PrefillPlan plan = plan_prefill(T, k, E, d, f, shared ? shared->desc.n_experts : 0, f_s,
+                                        shared && shared->dev.sc_bf16 == routed->dev.sc_bf16 && shared->dev.bits == routed->dev.bits, ctx->n_cu);
+  const int nf = plan.nf, nfs = plan.nfs;
+  const bool join = plan.join;
   const int bm = 32 * nf;
   float* gamma = shared ? (float*)(s + L.gamma) : nullptr;
   group_kernel<<<E + (shared ? (T + GR_THREADS / 64 - 1) / (GR_THREADS / 64) : 0), GR_THREADS, 0, st>>>(
@@ -1017,14 +1049,6 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
     q.x = (const uint16_t*)x_dev; q.h = (uint16_t*)(s + L.h_s); q.o = o_s; q.wgt = gamma; q.E = shared->desc.n_experts; q.k = 1; q.d_model = d; q.d_ff = f_s;
     q.dense_rows = T; q.super = 8;
     const int ns = shared->desc.n_experts;
-    // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
-    // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both
-    // want the same tile height, or if at the routed experts' (lower) height there is little to expand: a dense tile
-    // expands its weights again, 600 million of them in about 55 us over the chip, which is what launches of their own lose to
-    // their empty ends.  64 experts of d_ff 512, one shared of 1024, d_model 1024, 500 tokens: 101 -> 72 us; 96 experts, two
-    // shared of 3840, d_model 2560, 500 tokens, all joined, would be 482 -> 515.
-    const double again = 3.0 * d * f_s * shared->desc.n_experts * ((T + bm - 1) / bm);
-    if (same && (nf < 3 || nfs < 3)) join = nf == nfs || T <= 8 * bm || (T <= 24 * bm && again <= 600e6);
     // H of one shared expert has its own place.  That of others waits in Y, which nothing else writes before the last
     // kernel, if Y is not X and they fit there; else in the rows of O until the routed experts' down GEMM
     // writes those: then the shared experts' down GEMM comes before it, and as many experts as fit are worked out together.

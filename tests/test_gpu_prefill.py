@@ -29,6 +29,12 @@ def ctx():
     c.close()
 
 
+def tiles(routed, shared, T, k):
+    """(rows of the routed experts' tallest tile, of the shared experts', shared tiles in the routed launches)"""
+    return B.smoe_prefill_tiles(routed.desc, shared.desc if shared else None, T, k,
+                                torch.cuda.get_device_properties(0).multi_processor_count)
+
+
 def _check_routing(ctx, x, wr, k, idx, w, hist, E):
     _, _, z = B.smoe_route(ctx, k, x=x, w_router=wr, want_logits=True)
     ridx, rw = O.route(z.cpu().numpy(), None, k)          # top-k of the GPU's own fp32 logits
@@ -41,15 +47,16 @@ def _check_routing(ctx, x, wr, k, idx, w, hist, E):
     return ridx, rw
 
 
-@pytest.mark.parametrize("T,E,k,d,f,G", [(200, 6, 2, 256, 128, 64), (37, 5, 3, 128, 192, 32), (450, 3, 1, 128, 64, 64),
-                                          (70, 4, 2, 4096, 128, 128)])
-def test_prefill_small_all_tokens(ctx, T, E, k, d, f, G):
+@pytest.mark.parametrize("T,E,k,d,f,G,rows", [(200, 6, 2, 256, 128, 64, 96), (37, 5, 3, 128, 192, 32, 32), (450, 3, 1, 128, 64, 64, 96),
+                                               (70, 4, 2, 4096, 128, 128, 64)])
+def test_prefill_small_all_tokens(ctx, T, E, k, d, f, G, rows):
     # 200 tokens over 6 experts: three fragments per tile, the last one ragged; 37 tokens: a single partial fragment;
-    # 450 tokens over 3 experts top-1: about 150 rows per expert, tiles of five fragments; d_model 4096: two
+    # 450 tokens over 3 experts top-1: about 150 rows per expert, two tiles of two or three fragments; d_model 4096: two
     # experts per token out of four, wide rows
     say("prefill small", T, E, k, d, f, G)
     shp = synth.LayerShape(d, E, f, k, G, act="bf16")
     pair = LayerPair(ctx, shp, seed=21)
+    assert tiles(pair.routed, None, T, k)[0] == rows
     x = synth.activations(21, T, d, "bf16").cuda()
     wr = synth.router_weight(21, 0, E, d, std=0.05).cuda()
     for resid in (False, True):
@@ -72,6 +79,7 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     say("prefill with shared experts", n_shared, f_s, gate)
     shp = synth.LayerShape(d, E, f, k, G, n_shared=n_shared, shared_d_ff=f_s, shared_gate=gate, act="bf16")
     pair = LayerPair(ctx, shp, seed=23)
+    assert tiles(pair.routed, pair.shared, T, k) == (96, 96, True)
     x = synth.activations(23, T, d, "bf16").cuda()
     wr = synth.router_weight(23, 0, E, d, std=0.05).cuda()
     wsg = synth.shared_gate_weight(23, 0, d, "bf16", std=0.05).cuda() if gate else None
@@ -93,20 +101,28 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     assert O.max_abs_rel(t2np(yd), t2np(y[t])) <= TOL
 
 
-@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank", [
-    (40, 4, 2, 64, 64, 32, 0, 0, (8, 4), "bf16"),        # one K step per GEMM, one fragment per tile
-    (130, 6, 2, 192, 320, 64, 1, 192, (8, 4), "f32"),    # odd numbers of K steps, two fragments, shared tiles in the same launches; fp32 scales
-    (33, 130, 5, 576, 128, 32, 2, 64, (8, 4), "bf16"),   # tile search over more than two lanes' worth of experts, most of them empty; nine steps
-    (400, 5, 1, 128, 448, 128, 2, 320, (6, 3), "f32"),   # three fragments; seven steps (a partial 256-column chunk); two shared experts
-    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16"), # five fragments, four tiles per expert; the shared expert's tiles as tall, in the same launches
-    (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16"),  # a group wider than the row; three shared experts at once
-    (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16"),      # shared experts whose H does not fit beside O: one after the other
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank,rows", [
+    (40, 4, 2, 64, 64, 32, 0, 0, (8, 4), "bf16", 32),        # one K step per GEMM, one fragment per tile
+    (130, 6, 2, 192, 320, 64, 1, 192, (8, 4), "f32", 64),    # odd numbers of K steps, two fragments, shared tiles in the same launches; fp32 scales
+    (33, 130, 5, 576, 128, 32, 2, 64, (8, 4), "bf16", 32),   # tile search over more than two lanes' worth of experts, most of them empty; nine steps
+    (400, 5, 1, 128, 448, 128, 2, 320, (6, 3), "f32", 96),   # three fragments; seven steps (a partial 256-column chunk); two shared experts
+    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16", 160), # five fragments, four tiles per expert; the shared expert's tiles as tall, in the same launches
+    (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16", 96),  # a group wider than the row; three shared experts at once
+    (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16", 32),      # shared experts whose H does not fit beside O: one after the other
+    # tiles of five fragments (several per expert, of four and five), each nest and scale type; five to eight steps per GEMM
+    (1601, 6, 3, 320, 320, 64, 0, 0, (8, 4), "bf16", 160),
+    (1601, 8, 2, 448, 448, 32, 0, 0, (8, 4), "f32", 160),
+    (2001, 6, 2, 384, 384, 128, 0, 0, (6, 3), "bf16", 160),
+    (501, 6, 6, 512, 512, 32, 0, 0, (6, 3), "f32", 160),     # every expert takes every token
+    (1601, 8, 2, 320, 448, 64, 0, 0, (4, 2), "f32", 160),
+    (700, 24, 4, 320, 320, 64, 2, 192, (8, 4), "bf16", 160), # one tile per expert, two shared experts beside them
 ])
-def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
+def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, rows):
     # tolerance: that of every bf16 prefill test
     say("prefill tile shapes", T, E, k, d, f, G, n_sh, f_s, nest, bank)
     shp = synth.LayerShape(d, E, f, k, G, n_shared=n_sh, shared_d_ff=f_s, act=bank, b_high=nest[0], b_low=nest[1])
     pair = LayerPair(ctx, shp, seed=51)
+    assert tiles(pair.routed, pair.shared, T, k)[0] == rows
     x = synth.activations(51, T, d, "bf16").cuda()
     wr = synth.router_weight(51, 0, E, d, std=0.05).cuda()
     y, idx, w, hist = B.smoe_prefill_histogram(ctx, pair.routed, pair.shared, x, k, w_router=wr, add_residual=True)
@@ -117,19 +133,30 @@ def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank):
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
 
-@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank,std", [
-    (2999, 16, 4, 1024, 1024, 128, 0, 0, (8, 4), "bf16", 0.02),    # three tiles per expert, seven and eight fragments
-    (2501, 24, 4, 1088, 1088, 64, 0, 0, (8, 4), "bf16", 0.05),     # 17 K steps; a last column tile of 64 outputs
-    (2501, 24, 4, 1088, 1088, 32, 0, 0, (8, 4), "f32", 0.05),      # fp32 scales, groups of 32
-    (2003, 24, 6, 1536, 1024, 32, 0, 0, (6, 3), "bf16", 0.3),      # skewed routing: four to eight fragments
-    (2003, 24, 6, 1536, 1024, 256, 0, 0, (4, 2), "bf16", 0.3),
-    (1803, 48, 4, 2048, 1472, 128, 0, 0, (8, 4), "bf16", 0.02),    # one tile for most experts: four to six fragments
-    (3001, 24, 6, 1088, 1472, 64, 1, 960, (8, 4), "bf16", 0.05),   # a shared expert's dense tiles in the same launches
+def _zipf_logits(g, T, E, alpha):
+    """Logits whose top-k picks experts with popularity 1 / rank^alpha, without replacement."""
+    lp = -alpha * torch.log(torch.arange(1, E + 1, device="cuda").float())[torch.randperm(E, generator=g, device="cuda")]
+    return lp - torch.log(-torch.log(torch.rand((T, E), generator=g, device="cuda").clamp(1e-9, 1.0 - 1e-6)))
+
+
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,nest,bank,alpha,rows", [
+    (2999, 16, 4, 1024, 1024, 128, 0, 0, (8, 4), "bf16", 0.0, 256),    # three tiles per expert, seven and eight fragments
+    (2501, 24, 4, 1088, 1088, 64, 0, 0, (8, 4), "bf16", 0.0, 256),     # 17 K steps; a last column tile of 64 outputs
+    (2501, 24, 4, 1088, 1088, 32, 0, 0, (8, 4), "f32", 0.0, 256),      # fp32 scales, groups of 32
+    (2003, 24, 6, 1536, 1024, 32, 0, 0, (6, 3), "bf16", 1.1, 256),     # skewed routing: tiles of one to eight fragments
+    (2003, 24, 6, 1536, 1024, 256, 0, 0, (4, 2), "bf16", 1.1, 256),
+    (1803, 48, 4, 2048, 1472, 128, 0, 0, (8, 4), "bf16", 0.0, 256),    # one tile for most experts: four to six fragments
+    (3001, 24, 6, 1088, 1472, 64, 1, 960, (8, 4), "bf16", 0.0, 256),   # a shared expert's dense tiles in the same launches
+    (1601, 8, 2, 448, 448, 32, 0, 0, (8, 4), "bf16", 1.1, 160),        # tiles of one to five fragments
+    (1601, 8, 2, 448, 448, 64, 0, 0, (8, 4), "f32", 1.1, 160),
+    (2001, 6, 2, 384, 384, 32, 0, 0, (6, 3), "f32", 1.1, 160),
+    (2001, 6, 2, 384, 384, 128, 0, 0, (4, 2), "bf16", 1.1, 160),
+    (700, 24, 4, 320, 384, 64, 1, 192, (6, 3), "bf16", 0.6, 160),      # a shared expert beside them
 ])
-def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, std):
-    """Tiles of 256 rows (eight waves), which a layer takes when they fill the chip, against the 32- and 64-row tiles of the same
-    tokens in small calls: a row's sums run in the same order at every tile height, so the outputs are the same bits."""
-    say("prefill tall tiles", T, E, k, d, f, G, n_sh, f_s, nest, bank)
+def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha, rows):
+    """Tiles of 160 and of 256 rows (eight waves, which a layer takes when they fill the chip) against the 32- and 64-row tiles of the
+    same tokens in small calls: a row's sums run in the same order at every tile height, so the outputs are the same bits."""
+    say("prefill tall tiles", T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha)
     g = torch.Generator(device="cuda").manual_seed(77)
     draw = lambda *s: torch.randn(s, generator=g, device="cuda")
     dt = torch.float32 if bank == "f32" else torch.bfloat16
@@ -142,37 +169,43 @@ def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, std):
 
     routed, shared = make(E, f), make(n_sh, f_s) if n_sh else None
     x = draw(T, d).bfloat16()
-    wr = draw(E, d) * std
-    y, idx, w, hist = B.smoe_prefill_histogram(ctx, routed, shared, x, k, w_router=wr, add_residual=True)
+    wr = draw(E, d) * 0.05 if not alpha else None
+    z = _zipf_logits(g, T, E, alpha) if alpha else None
+    call = lambda a, b: B.smoe_prefill_histogram(ctx, routed, shared, x[a:b].contiguous(), k, logits=None if z is None else z[a:b].contiguous(),
+                                                 w_router=wr, add_residual=True)
+    y, idx, w, hist = call(0, T)
+    assert tiles(routed, shared, T, k)[0] == rows
     step = max(1, 24 * E // k)                                     # about 24 rows per expert
+    assert tiles(routed, shared, step, k)[0] <= 64
     for t in range(0, T, step):
-        ys, ids, ws, _ = B.smoe_prefill_histogram(ctx, routed, shared, x[t:t + step].contiguous(), k, w_router=wr, add_residual=True)
+        ys, ids, ws, _ = call(t, t + step)
         assert torch.equal(ids, idx[t:t + step]) and torch.equal(ws, w[t:t + step]), t
         assert torch.equal(ys, y[t:t + step]), t
 
 
-@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,s_nest,s_bank,s_G", [
-    # 64 experts top-1 want 32-row tiles, the shared experts 160-row ones.  Up to 24 short tiles of tokens the shared experts' tiles ride
-    # in the routed launches (768 tokens), beyond that they have launches of their own (769, 900)
-    (768, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64),
-    (769, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64),
-    (900, 64, 1, 256, 64, 64, 2, 128, (8, 4), "bf16", 64),     # own launches; the second shared expert's H waits in Y
-    (900, 64, 1, 128, 64, 32, 2, 192, (8, 4), "bf16", 32),     # ... in the rows of O
-    (900, 64, 1, 64, 64, 64, 2, 192, (8, 4), "bf16", 64),      # ... does not fit there: one after the other
+@pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,s_nest,s_bank,s_G,heights", [
+    # 64 experts top-1 want 32-row tiles, the shared experts taller ones (96 rows, the widest 160).  Up to 24 short tiles of tokens the
+    # shared experts' tiles ride in the routed launches (768 tokens), beyond that they have launches of their own (769, 900)
+    (768, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64, (32, 32, True)),
+    (769, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64, (32, 96, False)),
+    (900, 64, 1, 256, 64, 64, 2, 128, (8, 4), "bf16", 64, (32, 96, False)),     # own launches; the second shared expert's H waits in Y
+    (900, 64, 1, 128, 64, 32, 2, 192, (8, 4), "bf16", 32, (32, 96, False)),     # ... in the rows of O
+    (900, 64, 1, 64, 64, 64, 2, 192, (8, 4), "bf16", 64, (32, 96, False)),      # ... does not fit there: one after the other
     # from nine short tiles on, also only as long as the dense tiles expand at most 600 million weights again
-    (760, 64, 1, 2048, 64, 128, 1, 4032, (8, 4), "bf16", 128),
-    (760, 64, 1, 2048, 64, 128, 1, 4160, (8, 4), "bf16", 128),
+    (760, 64, 1, 2048, 64, 128, 1, 4032, (8, 4), "bf16", 128, (32, 32, True)),
+    (760, 64, 1, 2048, 64, 128, 1, 4160, (8, 4), "bf16", 128, (32, 160, False)),
     # a shared bank of another nest or scale type cannot ride along, one of another group can
-    (130, 6, 2, 192, 128, 64, 2, 64, (4, 2), "bf16", 64),
-    (130, 6, 2, 192, 128, 64, 1, 192, (8, 4), "f32", 32),
-    (130, 6, 2, 192, 128, 32, 1, 192, (8, 4), "bf16", 128),
+    (130, 6, 2, 192, 128, 64, 2, 64, (4, 2), "bf16", 64, (64, 96, False)),
+    (130, 6, 2, 192, 128, 64, 1, 192, (8, 4), "f32", 32, (64, 96, False)),
+    (130, 6, 2, 192, 128, 32, 1, 192, (8, 4), "bf16", 128, (64, 64, True)),
 ])
-def test_prefill_shared_experts_beside_the_routed_ones(ctx, T, E, k, d, f, G, n_sh, f_s, s_nest, s_bank, s_G):
+def test_prefill_shared_experts_beside_the_routed_ones(ctx, T, E, k, d, f, G, n_sh, f_s, s_nest, s_bank, s_G, heights):
     # tolerance: that of every bf16 prefill test; the wide layers on a sample of the tokens
     say("prefill, shared launches", T, E, k, d, f, G, n_sh, f_s, s_nest, s_bank, s_G)
     rp = LayerPair(ctx, synth.LayerShape(d, E, f, k, G, act="bf16"), seed=53)
     sp = LayerPair(ctx, synth.LayerShape(d, E, f, k, s_G, n_shared=n_sh, shared_d_ff=f_s, act=s_bank, b_high=s_nest[0], b_low=s_nest[1]),
                    seed=53, routed=False)
+    assert tiles(rp.routed, sp.shared, T, k) == heights
     x = synth.activations(53, T, d, "bf16").cuda()
     wr = synth.router_weight(53, 0, E, d, std=0.05).cuda()
     y, idx, w, hist = B.smoe_prefill_histogram(ctx, rp.routed, sp.shared, x, k, w_router=wr, add_residual=True)
@@ -291,6 +324,7 @@ def test_prefill_row_beside_an_extreme_gate(ctx):
                                           for s, c in (((f, d), 0.15), ((f, d), 0.15), ((d, f), 0.02))))
     x = torch.randn((T, d), generator=g, device="cuda").bfloat16()
     z = torch.zeros((T, 1), device="cuda")
+    assert tiles(bank, None, T, 1)[0] == 160
     outlier = torch.arange(T, device="cuda") % 32 == 5           # one in every fragment of 32 rows
     xo = torch.where(outlier[:, None], x * 100.0, x)
     y, yo = (B.smoe_prefill_histogram(ctx, bank, None, v, 1, logits=z)[0] for v in (x, xo))
@@ -299,14 +333,16 @@ def test_prefill_row_beside_an_extreme_gate(ctx):
     assert torch.equal(y[~outlier], yo[~outlier])
 
 
-@pytest.mark.parametrize("big,T,d,f,G,n_sh,nest", [
-    ("up", 3, 128, 64, 64, 0, (8, 4)),       # a tile of three rows
-    ("up", 700, 576, 128, 32, 0, (4, 2)),    # tall tiles, a partial 256-column chunk
-    ("up", 90, 256, 64, 128, 0, (6, 3)),
-    ("down", 40, 192, 320, 128, 2, (8, 4)),  # two shared experts summed by one work-group; a ragged column tile
-    ("down", 230, 64, 256, 512, 1, (6, 3)),
+@pytest.mark.parametrize("big,T,d,f,G,n_sh,nest,rows", [
+    ("up", 3, 128, 64, 64, 0, (8, 4), 32),       # a tile of three rows
+    ("up", 700, 576, 128, 32, 0, (4, 2), 96),    # eight tiles of three fragments, a partial 256-column chunk
+    ("up", 90, 256, 64, 128, 0, (6, 3), 96),
+    ("down", 40, 192, 320, 128, 2, (8, 4), 64),  # two shared experts summed by one work-group; a ragged column tile
+    ("down", 230, 64, 256, 512, 1, (6, 3), 96),
+    ("up", 1500, 64, 2112, 64, 0, (8, 4), 160),  # tiles of five fragments
+    ("down", 3001, 128, 576, 32, 0, (6, 3), 160),
 ])
-def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest):
+def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest, rows):
     # weights of up to 2^126 in magnitude: a group's range is 2^127, its scale at least 2^119, and 1024 scales overflow fp32 while
     # every weight scale * (code - zero point) is finite.  The activations are small enough for h and y to be ordinary numbers.
     say("prefill, largest scales", big, T, d, f, G, n_sh, nest)
@@ -318,12 +354,36 @@ def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest):
         return [m[n].bfloat16() for n in ("gate", "up", "down")]
     bank, ref = _layer_of(ctx, [expert()], G, nest)
     shared, sref = _layer_of(ctx, [expert() for _ in range(n_sh)], G, nest) if n_sh else (None, [])
+    assert tiles(bank, shared, T, 1)[0] == rows
     x = (torch.randn(T, d, generator=g) * 2.0 ** (-100 if big == "up" else -50)).bfloat16()
     y, idx, w, _ = B.smoe_prefill_histogram(ctx, bank, shared, x.cuda(), 1, logits=torch.zeros(T, 1).cuda())
     yref = O.prefill_layer(t2np(x).astype(np.float64), ref, idx.cpu().numpy(), w.cpu().numpy().astype(np.float64), sref)
     yg = t2np(y)
     for t in range(T):
         assert O.max_abs_rel(yg[t], yref[t]) <= TOL, t
+
+
+@pytest.mark.parametrize("big", ["up", "down"])
+def test_prefill_largest_scales_in_tall_tiles(ctx, big):
+    # the same weights in tiles of 256 rows, against 32-row tiles of the same tokens: the same bits
+    T, E, k, d, f, G = 2501, 24, 4, 1088, 1088, 64
+    say("prefill, largest scales in tall tiles", big)
+    g = torch.Generator(device="cuda").manual_seed(74)
+    bank = B.Bank(ctx, E, d, f, G, "bf16", "bf16")
+    for e in range(E):
+        m = {n: torch.randn((1,) + s, generator=g, device="cuda") * 0.02 for n, s in (("gate", (f, d)), ("up", (f, d)), ("down", (d, f)))}
+        m[big] = (2.0 * torch.rand(m[big].shape, generator=g, device="cuda") - 1.0) * 2.0 ** 126
+        B.smoe_quantize_slice(ctx, bank, e, *(m[n].bfloat16().contiguous() for n in ("gate", "up", "down")))
+    x = (torch.randn(T, d, generator=g, device="cuda") * 2.0 ** (-100 if big == "up" else -50)).bfloat16()
+    z = _zipf_logits(g, T, E, 0.6)
+    assert tiles(bank, None, T, k)[0] == 256
+    y = B.smoe_prefill_histogram(ctx, bank, None, x, k, logits=z)[0]
+    assert torch.isfinite(y.float()).all() and bool(y.any())
+    step = 24 * E // k
+    assert tiles(bank, None, step, k)[0] == 32
+    for t in range(0, T, step):
+        ys = B.smoe_prefill_histogram(ctx, bank, None, x[t:t + step].contiguous(), k, logits=z[t:t + step].contiguous())[0]
+        assert torch.equal(ys, y[t:t + step]), t
 
 
 def test_prefill_qwen_layer_full_size_sampled_tokens(ctx):
@@ -359,7 +419,7 @@ def test_prefill_qwen_layer_full_size_sampled_tokens(ctx):
 def test_prefill_more_pairs_than_the_grouping_registers_hold(ctx, T):
     # 5501 tokens top-3 = 16503 (token, slot) pairs: every thread of the grouping kernel owns a run of 20 (the last one shorter),
     # more than the 16 it keeps in registers, so the pairs are read one by one in both passes; 4100 tokens are 12300 pairs
-    # in runs of 16, the longest that stay in registers.  Every expert gets more than a dozen 160-row tiles.
+    # in runs of 16, the longest that stay in registers.  Every expert gets more than twenty 96-row tiles.
     E, k, d, f, G = 5, 3, 128, 64, 32
     say("prefill, long pair list", T, E, k)
     shp = synth.LayerShape(d, E, f, k, G, n_shared=1, shared_d_ff=64, act="bf16")
@@ -368,7 +428,8 @@ def test_prefill_more_pairs_than_the_grouping_registers_hold(ctx, T):
     wr = synth.router_weight(27, 0, E, d, std=0.05).cuda()
     y, idx, w, hist = B.smoe_prefill_histogram(ctx, pair.routed, pair.shared, x, k, w_router=wr, add_residual=True)
     ridx, rw = _check_routing(ctx, x, wr, k, idx, w, hist, E)
-    assert int(hist.cpu().numpy().view(np.uint32).min()) > 160 * 12
+    assert tiles(pair.routed, pair.shared, T, k) == (96, 96, True)
+    assert int(hist.cpu().numpy().view(np.uint32).min()) > 96 * 20
     assert (T * k > 16 * 1024) == (T == 5501)
     yref = O.prefill_layer(t2np(x).astype(np.float64), pair.oracle_routed(), ridx, rw.astype(np.float32).astype(np.float64),
                            pair.oracle_shared(), None, add_residual=True)

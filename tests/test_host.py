@@ -201,6 +201,28 @@ int main() {
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
 
 
+def test_prefill_tiles_validation_and_heights():
+    def bank(n, f, d=2048, nest=(8, 4), scale="bf16"):
+        return B.BankDesc(n, d, f, 128, nest[0], nest[1], B.BF16, B._DT[scale], 0)
+
+    lib, i = B.lib(), C.c_int()
+    out = (C.byref(i), C.byref(i), C.byref(i))
+    assert lib.smoe_prefill_tiles(None, None, 10, 1, 256, *out) == -1
+    assert lib.smoe_prefill_tiles(C.byref(bank(8, 64)), None, 10, 1, 256, None, *out[1:]) == -1
+    for T, k, n_cu in ((0, 1, 256), (10, 0, 256), (10, 9, 256), (10, 1, 0)):
+        assert lib.smoe_prefill_tiles(C.byref(bank(8, 64)), None, T, k, n_cu, *out) == -2
+    assert lib.smoe_prefill_tiles(C.byref(bank(8, 64)), C.byref(bank(1, 64, d=1024)), 10, 1, 256, *out) == -2
+    # one tile of 32 or 64 rows for experts of few; the shared experts in the same launches, not with another nest or scale type
+    dsv2, shared = bank(64, 1408), bank(2, 1408)
+    assert B.smoe_prefill_tiles(dsv2, shared, 173, 6, 256) == (32, 32, True)
+    assert B.smoe_prefill_tiles(dsv2, shared, 500, 6, 256)[0] == 64
+    assert B.smoe_prefill_tiles(dsv2, bank(2, 1408, nest=(6, 3)), 173, 6, 256)[2] is False
+    assert B.smoe_prefill_tiles(dsv2, bank(2, 1408, scale="f32"), 173, 6, 256)[2] is False
+    # many rows per expert: tall tiles
+    assert B.smoe_prefill_tiles(bank(60, 1408), bank(1, 5632), 4096, 4, 256) == (256, 256, True)
+    assert B.smoe_prefill_tiles(bank(60, 1408), None, 1500, 4, 256) == (160, 0, False)
+
+
 def test_library_handle_is_published_with_its_signatures(monkeypatch):
     """A second host thread may call lib() while the first one is still inside it: it must either load the library itself or get
     a handle on which every signature is set (without them ctypes passes a device pointer as a 32-bit int)."""
