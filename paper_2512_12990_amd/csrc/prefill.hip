@@ -853,57 +853,104 @@ static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf
 }
 // Tile height, in fragments of 32 rows.  Experts of few rows (up to 64 with one and a half standard deviations of even routing) take one
 // tile of 32 or 64: their weights' bytes bound them.  Above that three heights compete: 96 and 160 rows with four waves, two work-groups
-// per CU, and 256 with eight, one per CU, which expands a weight once for more rows but fills the chip in larger pieces.  Which of them is
-// faster hangs on how many tiles there are, so it is estimated, in cycles, from what the K loops measured: a step of a 256-row tile
-// (256 weight rows) takes 1150 + 190 F cycles at F fragments (1785 at 4, 2657 at 8), two of the four-wave tiles side by side 1350 + 113 F
-// (1601 at 3, 1826 at 5, not counting the weights' share of HBM), start and end of a tile 22000 and 9000.  Chosen so, microseconds per layer (160 / 256 rows): 60 experts of
-// d_model 2048, d_ff 1408, top-4, 2200 tokens 316 / 297, with a shared expert of 5632 and 4096 tokens 786 / 725; 24 experts of d_model 2560,
-// d_ff 2048, top-8, 1000 tokens 399 / 330; but 8 such experts, top-2, shared 2816, 1500 tokens 165 / 188; 16 of d_model 1024, d_ff 1024,
-// top-4, 1000 tokens 67 / 80.  There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second
-// one.  The mean is all the host knows; the spread assumed around it (three tenths) is that of mildly skewed routing.
+// per CU, and 256 with eight, one per CU, which expands a weight once for more rows but fills the chip in larger pieces, and in which the short tiles
+// of unpopular experts are alone on a CU and multiply at least four fragments.  (Leaving the surplus ones out there would save up to 5 % of a skewed
+// layer.  There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second one.)
+// Which is fastest hangs on how many tiles there are and how they fill the chip, so a layer's time is estimated.  The numbers are not those of the K loop
+// but a fit, in arbitrary units, to the measured ratios of 298 layers of all three nests (d_model 256 - 2560, d_ff 128 - 2048, 8 - 96 experts, popularity even
+// to 1/rank^2): 256 against 160 rows with an error of 6 %, 96 against 160 rows of 5 %, the same for every nest.
 struct GemmSize { double experts, rows; int N, K; bool even; };      // even: every expert has just these rows
-static double gemm_cycles(int nf, const GemmSize* g, int n, int n_cu) {
+struct Tiles { double n, frags; };                      // per expert: tiles, mean fragments that one multiplies
+static Tiles tiles_around(int nf, double rows, double deviation) {
+  const double h = 32.0 * nf;
+  double tiles = ceil(rows / h);
+  if (deviation > 0.0 && rows <= 64.0 * h) {
+    tiles = 1.0;
+    for (int j = 1; j * h < rows + 3.0 * deviation + 1.0; j++) tiles += 1.0 / (1.0 + exp(1.7 * (j * h - rows) / deviation));
+  }
+  const double frags = std::min((double)nf, rows / (32.0 * tiles) + 0.5);
+  return {tiles, nf > 5 && deviation > 0.0 ? std::max(frags, 4.0) : frags};
+}
+// Rows per expert when popularity falls as 1 / rank^1.1 and a token takes k different experts: T (1 - e^(-c w)), c such that they add up.
+struct SkewedRows {
+  int n = 0;
+  float rows[SMOE_MAX_EXPERTS];
+  void fill(float T, float k, int E) {
+    n = std::min(E, SMOE_MAX_EXPERTS);
+    float w[SMOE_MAX_EXPERTS], c = 0.0f;
+    for (int r = 0; r < n; r++) w[r] = exp2f(-1.1f * log2f(r + 1.0f));
+    for (int it = 0; it < 6; it++) {                    // Newton's method from below: the sum is concave in c
+      float sum = 0.0f, slope = 1e-6f;
+      for (int r = 0; r < n; r++) { const float q = expf(-c * w[r]); sum += 1.0f - q; slope += q * w[r]; }
+      c += std::max(0.0f, k - sum) / slope;
+    }
+    for (int r = 0; r < n; r++) rows[r] = T * (1.0f - expf(-c * w[r]));
+  }
+};
+static Tiles tiles_skewed(int nf, const SkewedRows& s) {
+  int tiles = 0, frags = 0;
+  for (int r = 0; r < s.n; r++) {
+    const int f = std::max(1, (int)ceilf(s.rows[r] / 32.0f)), t = (f + nf - 1) / nf;
+    tiles += t;
+    frags += nf > 5 ? std::max(f, 4 * t) : f;
+  }
+  return {(double)tiles / s.n, (double)frags / tiles};
+}
+static double gemm_cost(int nf, const GemmSize* g, const Tiles* t, int n, int n_cu) {
   const bool tall = nf > 5;
   double items = 0, work = 0, longest = 0;
   for (int i = 0; i < n; i++) {
-    const double h = 32.0 * nf, spread = 0.3 * g[i].rows + 1.0;
-    double tiles = ceil(g[i].rows / h);                 // of an expert, on average
-    if (!g[i].even && g[i].rows <= 64.0 * h) {
-      tiles = 1.0;
-      for (int j = 1; j * h < 2.0 * g[i].rows; j++) tiles += 1.0 / (1.0 + exp(1.7 * (j * h - g[i].rows) / spread));
-    }
-    const double f = std::min((double)nf, g[i].rows / (32.0 * tiles) + 0.5), steps = g[i].K / 64.0;
-    const double it = g[i].experts * tiles * ((g[i].N + 32 * pf_waves(nf) - 1) / (32 * pf_waves(nf)));
-    const double c = tall ? steps * (1150.0 + 190.0 * f) + 22e3 : steps * (1350.0 + 113.0 * f) + 9e3;
+    const double steps = g[i].K / 64.0, it = g[i].experts * t[i].n * ((g[i].N + 32 * pf_waves(nf) - 1) / (32 * pf_waves(nf)));
+    const double c = tall ? steps * (1100.0 + 190.0 * t[i].frags) + 5000.0 : steps * (910.0 + 215.0 * t[i].frags) + 2600.0;
     items += it;
     work += it * c;
     longest = std::max(longest, c);
   }
-  // rounds: how often the chip is filled; the more there are, the less an unfilled last one counts
-  const double q = items / (tall ? n_cu : 2 * n_cu), whole = floor(q), part = q - whole;
-  const double rounds = tall ? (q <= 3.0 ? ceil(q) : q + 0.4) : whole + (part <= 0.0 ? 0.0 : part <= 0.5 ? 0.8 : 1.0) + (q > 2.0 ? 0.3 : 0.0);
-  return std::max(work / items * rounds, longest * (tall || q > 1.0 ? 1.0 : 0.8));
-}
-// both GEMMs of up to two sets of experts in common launches: {gate/up, down} of each
-static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, double* cycles) {
-  *cycles = 0;
-  const double want = g[0][0].rows + 1.5 * sqrt(g[0][0].rows);
-  if (want <= 64.0) return want <= 32.0 ? 1 : 2;
-  int best = 0;
-  for (int nf : {3, 5, 8}) {
-    if (nf == 8) {                                      // (its tiles have to fill the chip one and a half times over: less is left to the estimate's error)
-      double items = 0;
-      for (int i = 0; i < n; i++) items += g[i][0].experts * ceil(g[i][0].rows / 256.0) * ((g[i][0].N + 255) / 256);
-      if (items < 1.5 * n_cu) break;
-    }
-    double c = 0;
-    for (int m = 0; m < 2; m++) {
-      GemmSize s[2] = {g[0][m], g[n - 1][m]};
-      c += gemm_cycles(nf, s, n, n_cu);
-    }
-    if (!best || c < *cycles) { best = nf; *cycles = c; }
+  // rounds: how often the chip is filled.  The number of tiles is not known to a percent, so the mean over 2 % either way
+  const double fill = items / (tall ? n_cu : 2 * n_cu);
+  double rounds = 0;
+  for (double q : {0.98 * fill, fill, 1.02 * fill}) {
+    const double whole = floor(q), part = q - whole;
+    rounds += tall ? (q <= 4.75 ? ceil(q) : q + 1.1) : whole + (part <= 0.0 ? 0.0 : part <= 0.5 ? 0.67 : 1.0);
   }
-  return best;
+  return std::max(work / items * rounds / 3.0, longest * (tall || fill > 1.0 ? 1.0 : 0.68));
+}
+// Height of up to two sets of experts in common launches, {gate/up, down} of each.  96 rows up to a mean plus one and a half deviations of 96, else
+// 160; the other one of these two where it is estimated to be no slower with even, with mildly uneven routing (three tenths of the mean) and with skewed
+// popularity; 256 where it is 3 % faster with even routing and, its skewed estimates being some hundredths too high, at most 2 and 6 % above with the other
+// two: the host knows the mean alone, and no kind of routing is to pay for another.  Microseconds per layer, popularity even / 1/rank^0.6 / 1/rank^1.1 / 1/rank^2, 160 rows, then 256:
+//   60 experts of d_model 2048, d_ff 1408, top-4, 2048 tokens   247 / 273 / 286 / 319, 243 / 284 / 313 / 347   -> 160
+//   the same, 3000 tokens                                       349 / 351 / 355 / 386, 297 / 329 / 357 / 423   -> 256
+//   with a shared expert of 5632, 4096 tokens                   699 / 718 / 728 / 747, 717 / 686 / 689 / 753   -> 160
+//   57 experts of 1984, 832, top-5, 2156 tokens                 245 / 234 / 245 / 240, 228 / 233 / 266 / 275   -> 160
+//   24 of 2560, 2048, top-8, 1000 tokens                        373 / 347 / 352 / 350, 302 / 342 / 350 / 348   -> 256
+static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, SkewedRows& skewed, double T, double k) {
+  const double rows = g[0][0].rows, want = rows + 1.5 * sqrt(rows);
+  if (want <= 64.0) return want <= 32.0 ? 1 : 2;
+  enum { EVEN, MILD, SKEWED };
+  auto cost = [&](int nf, int routing) {
+    Tiles t[2];
+    for (int i = 0; i < n; i++) {
+      if (g[i][0].even) t[i] = tiles_around(nf, g[i][0].rows, 0.0);
+      else t[i] = routing == SKEWED ? tiles_skewed(nf, skewed) : tiles_around(nf, rows, routing == EVEN ? sqrt(rows) : 0.3 * rows + 1.0);
+    }
+    double c = 94e3;                                    // (routing, grouping, sums)
+    for (int m = 0; m < 2; m++) {
+      const GemmSize s[2] = {g[0][m], g[n - 1][m]};
+      c += gemm_cost(nf, s, t, n, n_cu);
+    }
+    return c;
+  };
+  auto better = [&](int nf, int than, double even, double mild, double skew) {
+    if (cost(nf, EVEN) > even * cost(than, EVEN)) return false;
+    if (g[0][0].even) return true;
+    if (cost(nf, MILD) > mild * cost(than, MILD)) return false;
+    if (!skewed.n) skewed.fill((float)T, (float)k, (int)g[0][0].experts);
+    return cost(nf, SKEWED) <= skew * cost(than, SKEWED);
+  };
+  int best = want <= 96.0 ? 3 : 5;
+  if (better(8 - best, best, 1.0, 1.0, 1.0)) best = 8 - best;
+  return better(8, best, 0.97, 1.02, 1.06) ? 8 : best;
 }
 
 // Tile heights (in fragments) of the routed and the shared experts, and whether the shared experts' tiles ride in the routed experts' launches
@@ -912,13 +959,14 @@ struct PrefillPlan { int nf, nfs; bool join; };
 static PrefillPlan plan_prefill(int T, int k, int E, int d, int f, int ns, int f_s, bool same, int n_cu) {
   const GemmSize sizes[2][2] = {{{(double)E, (double)T * k / E, 2 * f, d, false}, {(double)E, (double)T * k / E, d, f, false}},
                                 {{(double)ns, (double)T, 2 * f_s, d, true}, {1.0, (double)T, d, f_s * ns, true}}};
-  double c_r, c_s = 0, c_both = 0;
-  PrefillPlan p{pick_nf(sizes, 1, n_cu, &c_r), ns ? pick_nf(sizes + 1, 1, n_cu, &c_s) : 0, false};
+  SkewedRows skewed;
+  PrefillPlan p{pick_nf(sizes, 1, n_cu, skewed, T, k), ns ? pick_nf(sizes + 1, 1, n_cu, skewed, T, k) : 0, false};
   if (!ns || !same) return p;      // (same: both banks have one nest and one scale type)
   if (p.nf >= 3 && p.nfs >= 3) {
-    // taller tiles: one height for both sets, in common launches, if that is estimated to be no slower
-    const int nfb = pick_nf(sizes, 2, n_cu, &c_both);
-    if (c_both <= c_r + c_s + 30e3) { p.nf = nfb; p.join = true; }      // (two launches less)
+    // taller tiles: one height for both sets, in common launches (of 48 layers none was faster with launches of their own at the better of both
+    // choices: 64 experts and two shared of d_ff 1408, d_model 2048, 2048 tokens 420 / 387 us)
+    p.nf = pick_nf(sizes, 2, n_cu, skewed, T, k);
+    p.join = true;
   } else {
     // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
     // tokens, most of a launch of their own: 173 tokens, two shared experts of d_ff 1408: 200 us of 422 were theirs), if both

@@ -106,7 +106,7 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     (130, 6, 2, 192, 320, 64, 1, 192, (8, 4), "f32", 64),    # odd numbers of K steps, two fragments, shared tiles in the same launches; fp32 scales
     (33, 130, 5, 576, 128, 32, 2, 64, (8, 4), "bf16", 32),   # tile search over more than two lanes' worth of experts, most of them empty; nine steps
     (400, 5, 1, 128, 448, 128, 2, 320, (6, 3), "f32", 96),   # three fragments; seven steps (a partial 256-column chunk); two shared experts
-    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16", 160), # five fragments, four tiles per expert; the shared expert's tiles as tall, in the same launches
+    (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16", 96), # six tiles per expert; the shared expert's tiles as tall, in the same launches
     (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16", 96),  # a group wider than the row; three shared experts at once
     (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16", 32),      # shared experts whose H does not fit beside O: one after the other
     # tiles of five fragments (several per expert, of four and five), each nest and scale type; five to eight steps per GEMM
@@ -115,7 +115,8 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     (2001, 6, 2, 384, 384, 128, 0, 0, (6, 3), "bf16", 160),
     (501, 6, 6, 512, 512, 32, 0, 0, (6, 3), "f32", 160),     # every expert takes every token
     (1601, 8, 2, 320, 448, 64, 0, 0, (4, 2), "f32", 160),
-    (700, 24, 4, 320, 320, 64, 2, 192, (8, 4), "bf16", 160), # one tile per expert, two shared experts beside them
+    (700, 12, 4, 320, 384, 64, 2, 192, (8, 4), "bf16", 160), # two tiles per expert, two shared experts beside them
+    (2001, 6, 2, 384, 384, 64, 0, 0, (4, 2), "bf16", 160),
 ])
 def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, rows):
     # tolerance: that of every bf16 prefill test
@@ -145,13 +146,13 @@ def _zipf_logits(g, T, E, alpha):
     (2501, 24, 4, 1088, 1088, 32, 0, 0, (8, 4), "f32", 0.0, 256),      # fp32 scales, groups of 32
     (2003, 24, 6, 1536, 1024, 32, 0, 0, (6, 3), "bf16", 1.1, 256),     # skewed routing: tiles of one to eight fragments
     (2003, 24, 6, 1536, 1024, 256, 0, 0, (4, 2), "bf16", 1.1, 256),
-    (1803, 48, 4, 2048, 1472, 128, 0, 0, (8, 4), "bf16", 0.0, 256),    # one tile for most experts: four to six fragments
-    (3001, 24, 6, 1088, 1472, 64, 1, 960, (8, 4), "bf16", 0.0, 256),   # a shared expert's dense tiles in the same launches
+    (1100, 24, 4, 1472, 960, 128, 0, 0, (8, 4), "bf16", 0.0, 256),     # one tile per expert: five to seven fragments
+    (1803, 24, 6, 832, 960, 64, 1, 320, (8, 4), "bf16", 0.0, 256),     # a shared expert's dense tiles in the same launches
     (1601, 8, 2, 448, 448, 32, 0, 0, (8, 4), "bf16", 1.1, 160),        # tiles of one to five fragments
     (1601, 8, 2, 448, 448, 64, 0, 0, (8, 4), "f32", 1.1, 160),
     (2001, 6, 2, 384, 384, 32, 0, 0, (6, 3), "f32", 1.1, 160),
     (2001, 6, 2, 384, 384, 128, 0, 0, (4, 2), "bf16", 1.1, 160),
-    (700, 24, 4, 320, 384, 64, 1, 192, (6, 3), "bf16", 0.6, 160),      # a shared expert beside them
+    (1500, 12, 4, 320, 192, 64, 1, 192, (6, 3), "bf16", 0.6, 160),     # a shared expert beside them
 ])
 def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha, rows):
     """Tiles of 160 and of 256 rows (eight waves, which a layer takes when they fill the chip) against the 32- and 64-row tiles of the
@@ -184,7 +185,7 @@ def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha,
 
 
 @pytest.mark.parametrize("T,E,k,d,f,G,n_sh,f_s,s_nest,s_bank,s_G,heights", [
-    # 64 experts top-1 want 32-row tiles, the shared experts taller ones (96 rows, the widest 160).  Up to 24 short tiles of tokens the
+    # 64 experts top-1 want 32-row tiles, the shared experts 96-row ones.  Up to 24 short tiles of tokens the
     # shared experts' tiles ride in the routed launches (768 tokens), beyond that they have launches of their own (769, 900)
     (768, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64, (32, 32, True)),
     (769, 64, 1, 128, 64, 64, 1, 192, (8, 4), "bf16", 64, (32, 96, False)),
@@ -193,7 +194,7 @@ def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha,
     (900, 64, 1, 64, 64, 64, 2, 192, (8, 4), "bf16", 64, (32, 96, False)),      # ... does not fit there: one after the other
     # from nine short tiles on, also only as long as the dense tiles expand at most 600 million weights again
     (760, 64, 1, 2048, 64, 128, 1, 4032, (8, 4), "bf16", 128, (32, 32, True)),
-    (760, 64, 1, 2048, 64, 128, 1, 4160, (8, 4), "bf16", 128, (32, 160, False)),
+    (760, 64, 1, 2048, 64, 128, 1, 4160, (8, 4), "bf16", 128, (32, 96, False)),
     # a shared bank of another nest or scale type cannot ride along, one of another group can
     (130, 6, 2, 192, 128, 64, 2, 64, (4, 2), "bf16", 64, (64, 96, False)),
     (130, 6, 2, 192, 128, 64, 1, 192, (8, 4), "f32", 32, (64, 96, False)),
@@ -324,7 +325,6 @@ def test_prefill_row_beside_an_extreme_gate(ctx):
                                           for s, c in (((f, d), 0.15), ((f, d), 0.15), ((d, f), 0.02))))
     x = torch.randn((T, d), generator=g, device="cuda").bfloat16()
     z = torch.zeros((T, 1), device="cuda")
-    assert tiles(bank, None, T, 1)[0] == 160
     outlier = torch.arange(T, device="cuda") % 32 == 5           # one in every fragment of 32 rows
     xo = torch.where(outlier[:, None], x * 100.0, x)
     y, yo = (B.smoe_prefill_histogram(ctx, bank, None, v, 1, logits=z)[0] for v in (x, xo))
@@ -339,8 +339,8 @@ def test_prefill_row_beside_an_extreme_gate(ctx):
     ("up", 90, 256, 64, 128, 0, (6, 3), 96),
     ("down", 40, 192, 320, 128, 2, (8, 4), 64),  # two shared experts summed by one work-group; a ragged column tile
     ("down", 230, 64, 256, 512, 1, (6, 3), 96),
-    ("up", 1500, 64, 2112, 64, 0, (8, 4), 160),  # tiles of five fragments
-    ("down", 3001, 128, 576, 32, 0, (6, 3), 160),
+    ("up", 5003, 256, 320, 64, 0, (8, 4), 160),  # tiles of five fragments
+    ("down", 5003, 256, 320, 32, 0, (6, 3), 160),
 ])
 def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest, rows):
     # weights of up to 2^126 in magnitude: a group's range is 2^127, its scale at least 2^119, and 1024 scales overflow fp32 while
