@@ -406,7 +406,7 @@ __global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_ge
   };
 #pragma unroll
   for (int q = 0; q < NA; q++) a_off[q] = row_at((NW * q + wave) * 8 + (lane >> 3));
-  if (NW == 8 && nf > 4 && (nf & 1)) a_half = row_at(32 * (nf - 1) + 4 * wave + ((lane >> 3) & 3));
+  if (NW == 8 && (nf & 1)) a_half = row_at(32 * (nf - 1) + 4 * wave + ((lane >> 3) & 3));
   // operand reads: lane (n, hh) takes columns 32 hh + 8 s .. + 7 of row n: piece (4 hh + s) ^ (n / 2 % 8)
   const uint32_t a_rd = n * 128 + (((4 * hh) ^ ((n >> 1) & 7)) * 16);
   // MODE 1: the weight of row tid of the tile, for the epilogue
@@ -630,13 +630,15 @@ __global__ __launch_bounds__(64 * pf_waves(NF), NF == 1 ? 3 : 2) void grouped_ge
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (no load is on its way to LDS any more)
     }
   };
-  // (a tall tile's rows beyond its last fragment are a few repeated ones: below four fragments nothing is gained by leaving them out)
   if constexpr (NF == 8) {
     if (nf == 8) kloop(std::integral_constant<int, 8>());
     else if (nf == 7) kloop(std::integral_constant<int, 7>());
     else if (nf == 6) kloop(std::integral_constant<int, 6>());
     else if (nf == 5) kloop(std::integral_constant<int, 5>());
-    else kloop(std::integral_constant<int, 4>());
+    else if (nf == 4) kloop(std::integral_constant<int, 4>());
+    else if (nf == 3) kloop(std::integral_constant<int, 3>());
+    else if (nf == 2) kloop(std::integral_constant<int, 2>());
+    else kloop(std::integral_constant<int, 1>());
   } else {
     if (NF >= 5 && nf == 5) kloop(std::integral_constant<int, (NF >= 5 ? 5 : 1)>());
     else if (NF >= 4 && nf == 4) kloop(std::integral_constant<int, (NF >= 4 ? 4 : 1)>());
@@ -854,8 +856,7 @@ static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf
 // Tile height, in fragments of 32 rows.  Experts of few rows (up to 64 with one and a half standard deviations of even routing) take one
 // tile of 32 or 64: their weights' bytes bound them.  Above that three heights compete: 96 and 160 rows with four waves, two work-groups
 // per CU, and 256 with eight, one per CU, which expands a weight once for more rows but fills the chip in larger pieces, and in which the short tiles
-// of unpopular experts are alone on a CU and multiply at least four fragments.  (Leaving the surplus ones out there would save up to 5 % of a skewed
-// layer.  There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second one.)
+// of unpopular experts are alone on a CU.  (There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second one.)
 // Which is fastest hangs on how many tiles there are and how they fill the chip, so a layer's time is estimated.  The numbers are not those of the K loop
 // but a fit, in arbitrary units, to the measured ratios of 298 layers of all three nests (d_model 256 - 2560, d_ff 128 - 2048, 8 - 96 experts, popularity even
 // to 1/rank^2): 256 against 160 rows with an error of 6 %, 96 against 160 rows of 5 %, the same for every nest.
@@ -868,8 +869,7 @@ static Tiles tiles_around(int nf, double rows, double deviation) {
     tiles = 1.0;
     for (int j = 1; j * h < rows + 3.0 * deviation + 1.0; j++) tiles += 1.0 / (1.0 + exp(1.7 * (j * h - rows) / deviation));
   }
-  const double frags = std::min((double)nf, rows / (32.0 * tiles) + 0.5);
-  return {tiles, nf > 5 && deviation > 0.0 ? std::max(frags, 4.0) : frags};
+  return {tiles, std::min((double)nf, rows / (32.0 * tiles) + 0.5)};
 }
 // Rows per expert when popularity falls as 1 / rank^1.1 and a token takes k different experts: T (1 - e^(-c w)), c such that they add up.
 struct SkewedRows {
@@ -890,9 +890,9 @@ struct SkewedRows {
 static Tiles tiles_skewed(int nf, const SkewedRows& s) {
   int tiles = 0, frags = 0;
   for (int r = 0; r < s.n; r++) {
-    const int f = std::max(1, (int)ceilf(s.rows[r] / 32.0f)), t = (f + nf - 1) / nf;
-    tiles += t;
-    frags += nf > 5 ? std::max(f, 4 * t) : f;
+    const int f = std::max(1, (int)ceilf(s.rows[r] / 32.0f));
+    tiles += (f + nf - 1) / nf;
+    frags += f;
   }
   return {(double)tiles / s.n, (double)frags / tiles};
 }
