@@ -858,18 +858,22 @@ static int launch_gemm(smoe_ctx* ctx, GemmPair& g, int sc_bf16, int bits, int nf
 // per CU, and 256 with eight, one per CU, which expands a weight once for more rows but fills the chip in larger pieces, and in which the short tiles
 // of unpopular experts are alone on a CU.  (There is no tile of 128 rows with four waves: it gains nothing or loses, because more experts need a second one.)
 // Which is fastest hangs on how many tiles there are and how they fill the chip, so a layer's time is estimated.  The numbers are not those of the K loop
-// but a fit, in arbitrary units, to the measured ratios of 298 layers of all three nests (d_model 256 - 2560, d_ff 128 - 2048, 8 - 96 experts, popularity even
-// to 1/rank^2): 256 against 160 rows with an error of 6 %, 96 against 160 rows of 5 %, the same for every nest.
+// but a fit, in arbitrary units, to the measured ratios of 148 layers of all three nests (d_model 256 - 2560, d_ff 128 - 2048, 8 - 96 experts; cold weights,
+// calls back to back for 30 ms; popularity even to 1/rank^2): 256 against 160 rows with an error of 6 %, 96 against 160 rows of 5 %.
 struct GemmSize { double experts, rows; int N, K; bool even; };      // even: every expert has just these rows
-struct Tiles { double n, frags; };                      // per expert: tiles, mean fragments that one multiplies
-static Tiles tiles_around(int nf, double rows, double deviation) {
+struct Tiles { double n, frags, deviation; };           // tiles per expert, mean fragments of one, relative deviation of the number of tiles
+static Tiles tiles_around(int nf, const GemmSize& g, double deviation) {
   const double h = 32.0 * nf;
-  double tiles = ceil(rows / h);
-  if (deviation > 0.0 && rows <= 64.0 * h) {
+  double tiles = ceil(g.rows / h), var = 0.0;
+  if (deviation > 0.0 && g.rows <= 64.0 * h) {
     tiles = 1.0;
-    for (int j = 1; j * h < rows + 3.0 * deviation + 1.0; j++) tiles += 1.0 / (1.0 + exp(1.7 * (j * h - rows) / deviation));
+    for (int j = 1; j * h < g.rows + 3.0 * deviation + 1.0; j++) {
+      const double p = 1.0 / (1.0 + exp(1.7 * (j * h - g.rows) / deviation));
+      tiles += p;
+      var += p * (1.0 - p);
+    }
   }
-  return {tiles, std::min((double)nf, rows / (32.0 * tiles) + 0.5)};
+  return {tiles, std::min((double)nf, g.rows / (32.0 * tiles) + 0.5), sqrt(var / g.experts) / tiles};
 }
 // Rows per expert when popularity falls as 1 / rank^1.1 and a token takes k different experts: T (1 - e^(-c w)), c such that they add up.
 struct SkewedRows {
@@ -894,47 +898,48 @@ static Tiles tiles_skewed(int nf, const SkewedRows& s) {
     tiles += (f + nf - 1) / nf;
     frags += f;
   }
-  return {(double)tiles / s.n, (double)frags / tiles};
+  return {(double)tiles / s.n, (double)frags / tiles, 0.0};
 }
 static double gemm_cost(int nf, const GemmSize* g, const Tiles* t, int n, int n_cu) {
   const bool tall = nf > 5;
   double items = 0, work = 0, longest = 0;
   for (int i = 0; i < n; i++) {
     const double steps = g[i].K / 64.0, it = g[i].experts * t[i].n * ((g[i].N + 32 * pf_waves(nf) - 1) / (32 * pf_waves(nf)));
-    const double c = tall ? steps * (1100.0 + 190.0 * t[i].frags) + 5000.0 : steps * (910.0 + 215.0 * t[i].frags) + 2600.0;
+    const double c = tall ? steps * (1040.0 + 227.0 * t[i].frags) + 6000.0 : steps * (810.0 + 304.0 * t[i].frags) + 900.0;
     items += it;
     work += it * c;
     longest = std::max(longest, c);
   }
-  // rounds: how often the chip is filled.  The number of tiles is not known to a percent, so the mean over 2 % either way
-  const double fill = items / (tall ? n_cu : 2 * n_cu);
+  // rounds: how often the chip is filled; the mean over a deviation of the number of tiles either way
+  const double fill = items / (tall ? n_cu : 2 * n_cu), wide = sqrt(1.7e-4 + t[0].deviation * t[0].deviation);
   double rounds = 0;
-  for (double q : {0.98 * fill, fill, 1.02 * fill}) {
+  for (double q : {(1.0 - wide) * fill, fill, (1.0 + wide) * fill}) {
     const double whole = floor(q), part = q - whole;
-    rounds += tall ? (q <= 4.75 ? ceil(q) : q + 1.1) : whole + (part <= 0.0 ? 0.0 : part <= 0.5 ? 0.67 : 1.0);
+    rounds += tall ? (q <= 8.5 ? ceil(q) : q + 0.75) : whole + (part <= 0.0 ? 0.0 : part <= 0.5 ? 0.66 : 1.0);
   }
-  return std::max(work / items * rounds / 3.0, longest * (tall || fill > 1.0 ? 1.0 : 0.68));
+  return std::max(work / items * rounds / 3.0, longest * (tall || fill > 1.0 ? 1.0 : 0.66));
 }
-// Height of up to two sets of experts in common launches, {gate/up, down} of each.  96 rows up to a mean plus one and a half deviations of 96, else
-// 160; the other one of these two where it is estimated to be no slower with even, with mildly uneven routing (three tenths of the mean) and with skewed
-// popularity; 256 where it is 3 % faster with even routing and, its skewed estimates being some hundredths too high, at most 2 and 6 % above with the other
-// two: the host knows the mean alone, and no kind of routing is to pay for another.  Microseconds per layer, popularity even / 1/rank^0.6 / 1/rank^1.1 / 1/rank^2, 160 rows, then 256:
-//   60 experts of d_model 2048, d_ff 1408, top-4, 2048 tokens   247 / 273 / 286 / 319, 243 / 284 / 313 / 347   -> 160
-//   the same, 3000 tokens                                       349 / 351 / 355 / 386, 297 / 329 / 357 / 423   -> 256
-//   with a shared expert of 5632, 4096 tokens                   699 / 718 / 728 / 747, 717 / 686 / 689 / 753   -> 160
-//   57 experts of 1984, 832, top-5, 2156 tokens                 245 / 234 / 245 / 240, 228 / 233 / 266 / 275   -> 160
-//   24 of 2560, 2048, top-8, 1000 tokens                        373 / 347 / 352 / 350, 302 / 342 / 350 / 348   -> 256
-static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, SkewedRows& skewed, double T, double k) {
+// Height of up to two sets of experts in common launches, {gate/up, down} of each: 96 rows up to a mean plus one and a half deviations of 96, else
+// 160; the other one of these two where it is estimated to be no slower with even, with mildly uneven (a fifth of the mean) and with skewed popularity;
+// 256 where it is no slower with mildly uneven routing, within 5 % with even and within bounds with skewed popularity: the host knows the mean alone.
+// There the estimate of the tall tiles is too high, by most for the 8/4 nest (1.13 against 1.05 measured for the first line below; 1.11 and 1.13 in
+// the other nests).  Microseconds per layer, popularity even / router over hidden states / 1/rank^1.1 / 1/rank^2, 160 rows, then 256:
+//   60 experts of d_model 2048, d_ff 1408, top-4, 2048 tokens   243 / 261 / 277 / 313, 237 / 241 / 292 / 317   -> 256
+//   the same, 6/3 nest, groups of 32                            299 / 321 / 331 / 371, 303 / 303 / 374 / 391   -> 160
+//   8/4, 1500 tokens                                            219 / 221 / 239 / 266, 213 / 216 / 259 / 274   -> 160
+//   3000 tokens                                                 360 / 367 / 361 / 386, 299 / 330 / 345 / 413   -> 256
+//   with a shared expert of 5632, 4096 tokens                   709 / 736 / 737 / 756, 697 / 679 / 668 / 718   -> 256
+//   36 experts of 896, 1024, top-3, 4/2 nest, 3692 tokens       136 / 143 / 145 / 143, 165 / 131 / 127 / 184   -> 160
+static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, int bits, SkewedRows& skewed, double T, double k) {
   const double rows = g[0][0].rows, want = rows + 1.5 * sqrt(rows);
   if (want <= 64.0) return want <= 32.0 ? 1 : 2;
   enum { EVEN, MILD, SKEWED };
   auto cost = [&](int nf, int routing) {
     Tiles t[2];
-    for (int i = 0; i < n; i++) {
-      if (g[i][0].even) t[i] = tiles_around(nf, g[i][0].rows, 0.0);
-      else t[i] = routing == SKEWED ? tiles_skewed(nf, skewed) : tiles_around(nf, rows, routing == EVEN ? sqrt(rows) : 0.3 * rows + 1.0);
-    }
-    double c = 94e3;                                    // (routing, grouping, sums)
+    for (int i = 0; i < n; i++)
+      t[i] = g[i][0].even ? tiles_around(nf, g[i][0], 0.0) : routing == SKEWED ? tiles_skewed(nf, skewed)
+             : tiles_around(nf, g[i][0], routing == EVEN ? sqrt(rows) : 0.2 * rows + 1.0);
+    double c = 93e3;                                    // (routing, grouping, sums)
     for (int m = 0; m < 2; m++) {
       const GemmSize s[2] = {g[0][m], g[n - 1][m]};
       c += gemm_cost(nf, s, t, n, n_cu);
@@ -942,30 +947,33 @@ static int pick_nf(const GemmSize (*g)[2], int n, int n_cu, SkewedRows& skewed, 
     return c;
   };
   auto better = [&](int nf, int than, double even, double mild, double skew) {
-    if (cost(nf, EVEN) > even * cost(than, EVEN)) return false;
-    if (g[0][0].even) return true;
-    if (cost(nf, MILD) > mild * cost(than, MILD)) return false;
+    if (g[0][0].even) return cost(nf, EVEN) <= cost(than, EVEN);
+    if (cost(nf, EVEN) > even * cost(than, EVEN) || cost(nf, MILD) > mild * cost(than, MILD)) return false;
     if (!skewed.n) skewed.fill((float)T, (float)k, (int)g[0][0].experts);
     return cost(nf, SKEWED) <= skew * cost(than, SKEWED);
   };
   int best = want <= 96.0 ? 3 : 5;
-  if (better(8 - best, best, 1.0, 1.0, 1.0)) best = 8 - best;
-  return better(8, best, 0.97, 1.02, 1.06) ? 8 : best;
+  // (beside shared experts the estimate of 96 rows is 7 % too low once their tiles fill the chip a few times)
+  double items = 0;
+  for (int i = 0; i < n; i++) items += g[i][0].experts * ceil(g[i][0].rows / 96.0) * ((g[i][0].N + 127) / 128);
+  const double sure = n > 1 && best == 5 && items > 3.0 * n_cu ? 0.93 : 1.0;
+  if (better(8 - best, best, sure, sure, sure)) best = 8 - best;
+  return better(8, best, 1.05, 1.0, bits == 4 ? 1.2 : 1.06) ? 8 : best;
 }
 
 // Tile heights (in fragments) of the routed and the shared experts, and whether the shared experts' tiles ride in the routed experts' launches
 // (then at the routed experts' height).
 struct PrefillPlan { int nf, nfs; bool join; };
-static PrefillPlan plan_prefill(int T, int k, int E, int d, int f, int ns, int f_s, bool same, int n_cu) {
+static PrefillPlan plan_prefill(int T, int k, int E, int d, int f, int bits, int ns, int f_s, int s_bits, bool same, int n_cu) {
   const GemmSize sizes[2][2] = {{{(double)E, (double)T * k / E, 2 * f, d, false}, {(double)E, (double)T * k / E, d, f, false}},
                                 {{(double)ns, (double)T, 2 * f_s, d, true}, {1.0, (double)T, d, f_s * ns, true}}};
   SkewedRows skewed;
-  PrefillPlan p{pick_nf(sizes, 1, n_cu, skewed, T, k), ns ? pick_nf(sizes + 1, 1, n_cu, skewed, T, k) : 0, false};
+  PrefillPlan p{pick_nf(sizes, 1, n_cu, bits, skewed, T, k), ns ? pick_nf(sizes + 1, 1, n_cu, s_bits, skewed, T, k) : 0, false};
   if (!ns || !same) return p;      // (same: both banks have one nest and one scale type)
   if (p.nf >= 3 && p.nfs >= 3) {
     // taller tiles: one height for both sets, in common launches (of 48 layers none was faster with launches of their own at the better of both
     // choices: 64 experts and two shared of d_ff 1408, d_model 2048, 2048 tokens 420 / 387 us)
-    p.nf = pick_nf(sizes, 2, n_cu, skewed, T, k);
+    p.nf = pick_nf(sizes, 2, n_cu, bits, skewed, T, k);
     p.join = true;
   } else {
     // The shared experts' tiles ride in the routed experts' launches, where they fill the chip's idle end (and, with few
@@ -1017,7 +1025,8 @@ extern "C" int smoe_prefill_tiles(const smoe_bank_desc* routed, const smoe_bank_
   if (!routed || !routed_rows || !shared_rows || !joined) return SMOE_EINVAL;
   if (T <= 0 || k <= 0 || k > routed->n_experts || routed->d_model <= 0 || routed->d_ff <= 0 || n_cu <= 0) return SMOE_ESHAPE;
   if (shared && (shared->n_experts <= 0 || shared->d_model != routed->d_model || shared->d_ff <= 0)) return SMOE_ESHAPE;
-  const PrefillPlan p = plan_prefill(T, k, routed->n_experts, routed->d_model, routed->d_ff, shared ? shared->n_experts : 0, shared ? shared->d_ff : 0,
+  const PrefillPlan p = plan_prefill(T, k, routed->n_experts, routed->d_model, routed->d_ff, routed->b_low, shared ? shared->n_experts : 0,
+                                     shared ? shared->d_ff : 0, shared ? shared->b_low : 0,
                                      shared && shared->scale_dtype == routed->scale_dtype && shared->b_low == routed->b_low, n_cu);
   *routed_rows = 32 * p.nf;
   *shared_rows = 32 * (p.join ? p.nf : p.nfs);
@@ -1061,7 +1070,7 @@ extern "C" int smoe_prefill_histogram(smoe_ctx* ctx, const smoe_bank* routed, co
 
   RouteArgs ra{E, k, d, logits_dev, x_dev, w_router_dev, nullptr, norm_topk, routed_scale, nullptr, idx_dev, w_dev};
   { const int rc = smoe_launch_route(ctx, ra, T, SMOE_BF16); if (rc) return rc; }
-  const PrefillPlan plan = plan_prefill(T, k, E, d, f, shared ? shared->desc.n_experts : 0, f_s,
+  const PrefillPlan plan = plan_prefill(T, k, E, d, f, routed->dev.bits, shared ? shared->desc.n_experts : 0, f_s, shared ? shared->dev.bits : 0,
                                         shared && shared->dev.sc_bf16 == routed->dev.sc_bf16 && shared->dev.bits == routed->dev.bits, ctx->n_cu);
   const int nf = plan.nf, nfs = plan.nfs;
   const bool join = plan.join;

@@ -109,14 +109,14 @@ def test_prefill_with_shared_experts(ctx, n_shared, f_s, gate):
     (1400, 8, 3, 256, 128, 256, 1, 704, (4, 2), "bf16", 96), # six tiles per expert; the shared expert's tiles as tall, in the same launches
     (900, 7, 3, 128, 192, 512, 3, 128, (8, 4), "bf16", 96),  # a group wider than the row; three shared experts at once
     (70, 3, 1, 64, 64, 32, 3, 640, (6, 3), "bf16", 32),      # shared experts whose H does not fit beside O: one after the other
-    # tiles of five fragments (several per expert, of four and five), each nest and scale type; five to eight steps per GEMM
-    (1601, 6, 3, 320, 320, 64, 0, 0, (8, 4), "bf16", 160),
-    (1601, 8, 2, 448, 448, 32, 0, 0, (8, 4), "f32", 160),
-    (2001, 6, 2, 384, 384, 128, 0, 0, (6, 3), "bf16", 160),
-    (501, 6, 6, 512, 512, 32, 0, 0, (6, 3), "f32", 160),     # every expert takes every token
-    (1601, 8, 2, 320, 448, 64, 0, 0, (4, 2), "f32", 160),
-    (700, 12, 4, 320, 384, 64, 2, 192, (8, 4), "bf16", 160), # two tiles per expert, two shared experts beside them
-    (2001, 6, 2, 384, 384, 64, 0, 0, (4, 2), "bf16", 160),
+    # tiles of three to five fragments, each nest and scale type; three to nine steps per GEMM
+    (1601, 16, 2, 320, 384, 64, 0, 0, (8, 4), "bf16", 160),
+    (1201, 6, 4, 448, 320, 32, 0, 0, (8, 4), "f32", 160),
+    (2001, 6, 4, 384, 192, 128, 0, 0, (6, 3), "bf16", 160),
+    (1601, 16, 2, 512, 384, 32, 0, 0, (6, 3), "f32", 160),
+    (1201, 6, 4, 384, 320, 64, 0, 0, (4, 2), "bf16", 160),
+    (501, 16, 4, 320, 576, 64, 0, 0, (4, 2), "f32", 160),    # one tile per expert
+    (700, 8, 4, 448, 448, 64, 2, 192, (8, 4), "bf16", 160),  # two shared experts beside them
 ])
 def test_prefill_tile_shapes(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, rows):
     # tolerance: that of every bf16 prefill test
@@ -148,10 +148,10 @@ def _zipf_logits(g, T, E, alpha):
     (2003, 24, 6, 1536, 1024, 256, 0, 0, (4, 2), "bf16", 1.1, 256),
     (1100, 24, 4, 1472, 960, 128, 0, 0, (8, 4), "bf16", 0.0, 256),     # one tile per expert: five to seven fragments
     (1803, 24, 6, 832, 960, 64, 1, 320, (8, 4), "bf16", 0.0, 256),     # a shared expert's dense tiles in the same launches
-    (1601, 8, 2, 448, 448, 32, 0, 0, (8, 4), "bf16", 1.1, 160),        # tiles of one to five fragments
-    (1601, 8, 2, 448, 448, 64, 0, 0, (8, 4), "f32", 1.1, 160),
-    (2001, 6, 2, 384, 384, 32, 0, 0, (6, 3), "f32", 1.1, 160),
-    (2001, 6, 2, 384, 384, 128, 0, 0, (4, 2), "bf16", 1.1, 160),
+    (1601, 16, 2, 448, 384, 32, 0, 0, (8, 4), "bf16", 1.1, 160),       # tiles of one to five fragments
+    (1601, 16, 2, 320, 384, 64, 0, 0, (8, 4), "f32", 1.1, 160),
+    (1601, 16, 2, 512, 384, 32, 0, 0, (6, 3), "f32", 1.1, 160),
+    (1601, 16, 2, 384, 384, 128, 0, 0, (4, 2), "bf16", 1.1, 160),
     (1500, 12, 4, 320, 192, 64, 1, 192, (6, 3), "bf16", 0.6, 160),     # a shared expert beside them
 ])
 def test_prefill_tall_tiles(ctx, T, E, k, d, f, G, n_sh, f_s, nest, bank, alpha, rows):
@@ -339,8 +339,8 @@ def test_prefill_row_beside_an_extreme_gate(ctx):
     ("up", 90, 256, 64, 128, 0, (6, 3), 96),
     ("down", 40, 192, 320, 128, 2, (8, 4), 64),  # two shared experts summed by one work-group; a ragged column tile
     ("down", 230, 64, 256, 512, 1, (6, 3), 96),
-    ("up", 5003, 256, 320, 64, 0, (8, 4), 160),  # tiles of five fragments
-    ("down", 5003, 256, 320, 32, 0, (6, 3), 160),
+    ("up", 5003, 576, 320, 64, 0, (8, 4), 160),  # tiles of five fragments
+    ("down", 5003, 640, 320, 32, 0, (6, 3), 160),
 ])
 def test_prefill_largest_scales(ctx, big, T, d, f, G, n_sh, nest, rows):
     # weights of up to 2^126 in magnitude: a group's range is 2^127, its scale at least 2^119, and 1024 scales overflow fp32 while

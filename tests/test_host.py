@@ -219,19 +219,18 @@ def test_prefill_tiles_validation_and_heights():
     assert B.smoe_prefill_tiles(dsv2, bank(2, 1408, nest=(6, 3)), 173, 6, 256)[2] is False
     assert B.smoe_prefill_tiles(dsv2, bank(2, 1408, scale="f32"), 173, 6, 256)[2] is False
     # many rows per expert: tall tiles
-    assert B.smoe_prefill_tiles(bank(60, 1408), bank(1, 5632), 4096, 4, 256) == (160, 160, True)
-    assert B.smoe_prefill_tiles(bank(60, 1408), None, 3000, 4, 256) == (256, 0, False)
+    assert B.smoe_prefill_tiles(bank(60, 1408), bank(1, 5632), 4096, 4, 256) == (256, 256, True)
+    assert B.smoe_prefill_tiles(bank(60, 1408), None, 1500, 4, 256) == (160, 0, False)
 
 
 @pytest.mark.parametrize("E,d,f,k,T,ns,fs,nest,rows", [
-    # tall tiles that are a little faster with even routing and slower with skewed popularity (or the other way round) are not taken
-    (60, 2048, 1408, 4, 2048, 0, 0, (8, 4), 160),
+    # heights that gain with one kind of routing what they lose with another (even, as a router makes it, popularity 1 / rank^1.1)
     (60, 2048, 1408, 4, 2048, 0, 0, (6, 3), 160),
-    (57, 1984, 832, 5, 2156, 0, 0, (8, 4), 160),
+    (60, 2048, 1408, 4, 2048, 0, 0, (4, 2), 160),
     (36, 896, 1024, 3, 3692, 0, 0, (4, 2), 160),
     (33, 512, 448, 8, 328, 0, 0, (8, 4), 96),
-    (39, 768, 1024, 2, 1458, 2, 1216, (4, 2), 96),
-    # faster in both: taken
+    # faster, or no slower, with each: taken
+    (60, 2048, 1408, 4, 2048, 0, 0, (8, 4), 256),
     (60, 2048, 1408, 4, 3000, 0, 0, (8, 4), 256),
     (24, 2560, 2048, 8, 1000, 0, 0, (8, 4), 256),
     (64, 2048, 1408, 6, 2048, 2, 1408, (8, 4), 256),
