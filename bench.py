@@ -327,7 +327,7 @@ def main():
                    "d_model": shp.d_model, "n_experts": shp.n_experts, "d_ff": shp.d_ff, "top_k": shp.top_k,
                    "n_shared": shp.n_shared, "shared_d_ff": shp.shared_d_ff, "group": shp.group, "nest": "%d/%d" % (bh, bl),
                    "cached": int((mask_np & 1).sum()), "cached_high": int((mask_np == 3).sum()),
-                   "mean_high_slots": high_slots / timed_rows, "launches_per_step": 3 if wr is not None else 2,
+                   "mean_high_slots": high_slots / timed_rows, "launches_per_step": 2 if wr is None else "2 with a small router matrix, else 3",
                    "tokens_per_step": TT,
                    "launch_mode": ("HIP graph replay (%d steps per graph, the same %d steps in order)" % (m["graph_steps_per_graph"], args.steps)
                                    if args.launch == "graph" else "eager launches"),
