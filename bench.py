@@ -53,7 +53,7 @@ def main():
                          "shared expert: rows of two 64-chunk k-slices, the wide gate/up kernel); tiny = the fp32 correctness "
                          "layer (BASELINE configs[0]: d_model 256, 8 experts of d_ff 128, top-2, group 64), launch-bound")
     ap.add_argument("--router-matvec", action="store_true",
-                    help="decode (one token per step): logits from the router mat-vec W_r x (a third launch) instead of "
+                    help="decode (one token per step): logits from the router mat-vec W_r x (a third launch unless the matrix is small) instead of "
                          "supplied logits")
     ap.add_argument("--nest", choices=["84", "63", "42"], default="84",
                     help="decode: bit nest of the expert weights: 84 = 8-bit codes / 4-bit low-bit model (headline), "

@@ -226,7 +226,7 @@ template <int SCB, int FMT, int NF> struct PfLds {
 // waves: 1865 before, 1708 now (mean of 3 to 5 fragments); eight waves: 1785 at 4 fragments, 2657 at 8, i.e. 446 and 332 per fragment -- a weight is
 // expanded for more rows.  Of those 2657 the products are 2048, the barrier 400.  Taller tiles take more of a CU at
 // once; where that leaves the chip unfilled the shorter ones are faster (pick_nf).  A layer of 2048 / 4096 tokens (60 experts of d_ff 1408,
-// the longer one with a shared expert of 5632): 291 -> 250 - 264 / 806 -> 697 - 714 us.  Registers: the tall gate/up kernel of the 8/4 nest with bf16
+// the longer one with a shared expert of 5632): 291 -> 250 - 268 / 806 -> 697 - 714 us.  Registers: the tall gate/up kernel of the 8/4 nest with bf16
 // scales is at 256 and keeps five in scratch, stored before the loops and fetched after them; the down kernels keep up to 109 scalars in vector lanes.  Not kept: eight waves and 160 rows (287 / 786 us), eight-wave
 // work-groups that stay and take a list of tiles, the next one's weights sent for before the epilogue (286 / 798 us against 270 / 747).
 // Earlier shapes, gate/up GEMM of 60 experts at 137 rows each / of 64 such experts at 16 rows: planes loaded straight into the lanes that use
